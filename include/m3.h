@@ -386,7 +386,9 @@ m3_status m3_step_pro(const m3_dims *dims, const m3_prologue *pro,
  * chunked algorithm (Sec. 3.3 "Chunked Algorithm for MIMO SSMs") in reverse:
  * the chunk states are recomputed, the state gradient is passed from the last
  * chunk to the first, and each chunk's gradients are formed from its own
- * rows with bf16 MFMA and fp32 accumulation.
+ * rows with bf16 MFMA and fp32 accumulation.  A slice's chunks are split into
+ * segments so that the device is filled (the last bits then depend on its CU
+ * count); seg_chunks is ignored.
  * Outputs: dx, dB, dC shaped and typed like x, B, C (io dtype); ddt,
  * dlambda [batch][seqlen][nheads], dtheta [batch][seqlen][nheads][dstate/2]
  * (fp32; the gradient of the per-step angle); dD [nheads]; dA [nheads] (the
@@ -396,8 +398,9 @@ m3_status m3_step_pro(const m3_dims *dims, const m3_prologue *pro,
  * overwritten.  Supported (else M3_ERR_UNSUPPORTED): io bf16, dstate 128,
  * headdim 64, chunk * rank = 64 (rank 1 chunk 64, rank 2 chunk 32, rank 4
  * chunk 16), no M3_THETA_PER_HEAD; A strided per head or per token.
- * Workspace: m3_scan_bwd_workspace_bytes(dims) bytes (16-byte aligned; two
- * fp32 and two bf16 N x P maps per chunk, after the scans' control block of M3_CTL_BYTES, which
+ * Workspace: m3_scan_bwd_workspace_bytes(dims) bytes (16-byte aligned; the size
+ * of three fp32 N x P maps per chunk: the states entering the chunks and the
+ * maps of the segments, after the scans' control block of M3_CTL_BYTES, which
  * this call neither reads nor writes; no initialisation).  Token arrays may be NULL when seqlen == 0.
  * Alignment: x, B, C, dy, dx, dB, dC, the states and the workspace 16 bytes,
  * the rest 4 bytes (else M3_ERR_ALIGN).  Outputs must not overlap inputs.

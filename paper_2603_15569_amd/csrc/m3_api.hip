@@ -623,7 +623,7 @@ extern "C" m3_status m3_scan_bwd(const m3_dims *d, const void *x, const void *B,
         if (!aligned4(p)) return M3_ERR_ALIGN;
     const BwdWorkspaceLayout wl = bwd_workspace_layout(d->batch * d->nheads, nc, d->dstate, d->headdim);
     if (workspace == nullptr || workspace_bytes < wl.total) return M3_ERR_WORKSPACE;
-    BwdArgs a;
+    BwdArgs a = {};
     a.x = x; a.B = B; a.C = C; a.dy = dy;
     a.dt = dt; a.A = A; a.lam = lambda; a.theta = theta; a.D = D;
     a.init_state = init_state; a.dfinal = dfinal_state;
@@ -632,11 +632,9 @@ extern "C" m3_status m3_scan_bwd(const m3_dims *d, const void *x, const void *B,
     a.dA_per_token = d->a_stride_t != 0 ? 1 : 0;
     char *ws = static_cast<char *>(workspace);
     a.Af = reinterpret_cast<float *>(ws + wl.off_Af);
-    a.Mb = reinterpret_cast<float *>(ws + wl.off_Mb);
-    a.Sst = reinterpret_cast<float *>(ws + wl.off_Sst);
-    a.Ust = reinterpret_cast<float *>(ws + wl.off_Ust);
+    a.Ar = reinterpret_cast<float *>(ws + wl.off_Ar);
+    a.Sst = ws + wl.off_Sst;
     a.tot = reinterpret_cast<float *>(ws + wl.off_tot);
-    a.pst = reinterpret_cast<float *>(ws + wl.off_pst);
     a.dsig = reinterpret_cast<float *>(ws + wl.off_dsig);
     a.dApart = reinterpret_cast<float *>(ws + wl.off_dA);
     a.dDpart = reinterpret_cast<float *>(ws + wl.off_dD);

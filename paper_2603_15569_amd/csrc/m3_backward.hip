@@ -28,18 +28,32 @@
 //   d(dt_u A_u) = sum_{t>=u} dcum_t, dtheta_u = sum_{t>=u} dpsi_t) and the
 //   chain runs through gamma, sigma, dt, lambda and A.
 //
-// Kernels (one stream, in order):
-//   k_bwd_aggr   per chunk: M_c rotated by psi_e (A_c), sum_t e^{cum_t} C^_t dy_t^T,
-//                and the chunk totals (cum_e, psi_e)                    (MFMA)
-//   k_bwd_pass   per (slice, pair i, column p): the forward states S_{c-1},
-//                then the reverse sweep G -> U, the state terms of dpsi_e
-//                and dcum_e, and dJ/d(initial state)
-//   k_bwd_chunk  per chunk: every gradient of the chunk's tokens         (MFMA)
-//   k_bwd_finish the sigma term that crosses into the next chunk's first
-//                token; per-head sums of dA and dD (fixed order)
-// Operands are bf16 with fp32 accumulation (as the forward); the prefix
-// sums, weights and every scalar gradient are fp32.  Results are
-// deterministic: no atomics.
+// A slice's chunks are split into segments (one or more per slice, so that
+// the launch fills the device); one workgroup carries the state and its
+// gradient through its segment in registers.  Kernels (one stream, in order):
+//   k_bwd_aggr   per (segment, direction), only with several segments a
+//                slice: the segment's map of the forward state (first to last
+//                chunk) or of the state gradient (last to first), from zero,
+//                with the sums of cum_e and psi_e                     (MFMA)
+//   k_bwd_pass   per slice: the maps folded over the segments
+//   k_bwd_main   per segment: a forward sweep that stores the state entering
+//                each chunk (bf16), then the chunks last to first, each with
+//                U from the carried gradient and every gradient of its tokens
+//                                                                     (MFMA)
+//   k_bwd_finish per-head sums of dA and dD (fixed order); the sigma term
+//                that crosses a segment boundary
+// Bound: the bytes (per 64-row chunk 96 KB of inputs and gradients, 28 KB of
+// B and x read again by the forward sweep, 32 KB of bf16 states written and
+// read) and, with two waves a SIMD, the latencies of k_bwd_main's dependent
+// steps.  One fp32 map of the state per chunk and direction, written by a
+// kernel over all chunks and folded by a second one, moved 352 KB a chunk and
+// took 8.62 ms on B=8 L=4096 H=32 rank 4 and 313 us on B=4 L=2048 H=16 SISO;
+// carrying the state through a segment in registers takes 2.90 ms and 175 us.
+// Operands are bf16 with fp32 accumulation (as the forward); the carried
+// state and gradient, the prefix sums, weights and every scalar gradient are
+// fp32.  Results are deterministic: no atomics.
+#include <algorithm>
+
 #include "m3_device.h"
 #include "m3_internal.h"
 #include "m3_scan_common.h"
@@ -49,775 +63,1073 @@ namespace {
 
 using namespace scan;
 
-constexpr int kN = 128, kP = 64, kNH = 64, kRows = 64, kThr = 256;
+constexpr int kN = 128, kP = 64, kNH = 64, kRows = 64;
+constexpr int kNW = 8, kThr = kNW * kWave;
 constexpr int LDN = kN + 8;   // bf16 row strides (16-byte padding)
 constexpr int LDP = kP + 8;
+constexpr int kMap = kN * kP;
+constexpr float kLog2e = 1.44269504088896340736f;
 typedef Mma<bf16> MM;
+// four floats at 4-byte alignment (the angles' arrays need no more)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Per-chunk scalars shared by the chunk kernels (NT threads a workgroup).
-template <int Q, int NT>
-struct alignas(16) Pro {
-    static constexpr int kSeg = NT / kNH;     // token segments of the angle scans
-    float cum[Q], gam[Q], sig[Q], v[Q], ec[Q];
-    h2 cs[Q * kNH];      // cos / sin of psi_t[i]
+// Lane and wave coordinates of a 512-thread workgroup.  The carried N x P
+// state is held transposed in MFMA tiles: wave (it, ph) owns the pair tiles
+// n = 16 it + l16 (q = 0) and 64 + 16 it + l16 (q = 1) and the columns
+// p = 16 (2 ph + u) + 4 g + v, element st[q][u][v].
+struct Lane {
+    int tid, lane, wave, g, l16, it, ph;
+    __device__ __forceinline__ Lane() : Lane((int)threadIdx.x) {}
+    __device__ __forceinline__ explicit Lane(int tid_) {
+        tid = tid_;
+        lane = tid & (kWave - 1);
+        wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+        g = lane >> 4;
+        l16 = lane & 15;
+        it = wave & 3;
+        ph = wave >> 2;
+    }
+};
+typedef f32x4 State[2][2];
+
+// A chunk's scalars by row (token, rank): base-2 log-decay prefix, gamma,
+// sigma, v, e^{cum}; its total log-decay and the pairs' total angles.
+struct Tok {
+    float c2[kRows], gam[kRows], sig[kRows], v[kRows], ec[kRows];
     float psie[kNH];
-    float seg[kSeg][kNH];
+    float c2e;
 };
 
-// Chunk-local prefix sums, trapezoid weights, v_j and e^{cum_t}: the
-// log-decay by one wavefront scan over the tokens; the angles by thread
-// (pair i, token segment), all of a thread's angle loads issued together,
-// segment totals combined through LDS.  Tokens past the end of the sequence
-// get zero weights and zero angles.
-template <int Q, int NT>
-__device__ void bwd_prologue(const BwdArgs &a, int64_t b, int64_t h, int64_t t0, int nvalid,
-                             Pro<Q, NT> &sp) {
-    constexpr int TPS = (Q + Pro<Q, NT>::kSeg - 1) / Pro<Q, NT>::kSeg;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int i = tid % kNH, seg = tid / kNH;
-    const float *th = a.theta + ((b * a.L + t0) * a.H + h) * kNH + i;
-    float ps[TPS];
+// Sum over the 16 lanes of a row group (every lane receives it): four DPP
+// rotations on the VALU.
+__device__ __forceinline__ float sum16(float v) {
+    v += dpp_src<0x128, 0xf>(v);
+    v += dpp_src<0x124, 0xf>(v);
+    v += dpp_src<0x122, 0xf>(v);
+    v += dpp_src<0x121, 0xf>(v);
+    return v;
+}
+// Sum over the R lanes of a token's rank rows.
+template <int R> __device__ __forceinline__ float sum_rank(float v) {
+    if constexpr (R >= 2) v += dpp_src<0xB1, 0xf>(v);   // quad_perm: lane ^ 1
+    if constexpr (R >= 4) v += dpp_src<0x4E, 0xf>(v);   // quad_perm: lane ^ 2
+    return v;
+}
+// Inclusive suffix sums over the tokens of a 16-lane row group (R equal
+// lanes a token).
+template <int R> __device__ __forceinline__ float suffix16(float v) {
+    if constexpr (R == 1) v += dpp_src<0x101, 0xf>(v);   // row_shl:1
+    if constexpr (R <= 2) v += dpp_src<0x102, 0xf>(v);
+    v += dpp_src<0x104, 0xf>(v);
+    v += dpp_src<0x108, 0xf>(v);
+    return v;
+}
+__device__ __forceinline__ float sum_g(float v) {   // over the four 16-lane groups
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
+    return v;
+}
+__device__ __forceinline__ float sum_wave(float v) { return sum_g(sum16(v)); }
+
+// MFMA operand with its rows (the output's rows) taken from 32 columns of a
+// row-major LDS block so that a lane of the output tiles ab = 0 and 1 holds
+// the columns c0 + 8 g + 4 ab + v: eight consecutive ones.  K elements: rows
+// r0 + 8 g .. + 7 (kt), or rows r0 + 4 g .. + 3 and r0 + 16 + 4 g .. + 3
+// (kt2: the order in which two 16-row accumulator tiles hold them).
+__device__ __forceinline__ bf16x8 cat4(bf16x4 lo, bf16x4 hi) {
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ bf16x8 perm_kt(const bf16 *M, int ld, int r0, int c0, int ab, const Lane &w) {
+    const bf16 *p = M + (r0 + 8 * w.g + w.l16 / 4) * ld + c0 + 8 * (w.l16 % 4) + 4 * ab;
+    return cat4(lds_tr4(p), lds_tr4(p + 4 * ld));
+}
+__device__ __forceinline__ bf16x8 perm_kt2(const bf16 *M, int ld, int r0, int c0, int ab, const Lane &w) {
+    const bf16 *p = M + (r0 + 4 * w.g + w.l16 / 4) * ld + c0 + 8 * (w.l16 % 4) + 4 * ab;
+    return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
+}
+// The same with rows r0 .. r0 + 31 of the block as the operand's rows, K
+// along the columns.
+__device__ __forceinline__ bf16x8 perm_rows(const bf16 *M, int ld, int r0, int k0, int ab, const Lane &w) {
+    return MM::load(&M[(r0 + 8 * (w.l16 / 4) + 4 * ab + w.l16 % 4) * ld + k0 + 8 * w.g]);
+}
+
+// ---------------------------------------------------------------------------
+// Chunk prologue, in two steps with a barrier between them, each on values
+// loaded a chunk earlier.
+// ---------------------------------------------------------------------------
+template <int R> struct Shp {
+    static constexpr int Q = kRows / R;
+    static constexpr int TPS = Q / kNW;   // tokens whose angles a thread scans
+};
+
+struct Slice {   // the slice's offsets
+    int64_t b, h, tok;   // tok: (b L) H + h, the slice's first scalar
+};
+
+// Raw values of a chunk's prologue: wave w's tokens w TPS .. of the angles
+// (pair = lane), and, by wave 0 with one lane a row, the token's scalars.
+template <int R> struct RawTok {
+    float th[Shp<R>::TPS];
+    float dt, lam, A, dtn, lamn;
+};
+
+template <int R>
+__device__ __forceinline__ void load_tok(const BwdArgs &a, const Slice &s, const Lane &w, int64_t c, int nvalid,
+                                         RawTok<R> &r) {
+    constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
+    const int64_t t0 = c * Q;
+    const float *th = a.theta + (s.tok + t0 * a.H) * kNH + w.lane;
 #pragma unroll
     for (int k = 0; k < TPS; ++k) {
-        const int t = seg * TPS + k;
-        ps[k] = t < nvalid ? th[(int64_t)t * a.H * kNH] : 0.f;
+        const int t = min(w.wave * TPS + k, nvalid - 1);
+        r.th[k] = th[(int64_t)t * a.H * kNH];
     }
-    float lg = 0.f, gam = 0.f, sig = 0.f;
-    if (tid < kWave && tid < nvalid) {
-        const int64_t t = t0 + tid, k = (b * a.L + t) * a.H + h;
-        const float dtv = a.dt[k], lamv = a.lam[k];
-        lg = dtv * a.A[b * a.a_sb + t * a.a_st + h * a.a_sh];
-        gam = lamv * dtv;
-        sig = gam;
-        if (t + 1 < a.L) sig += (1.f - a.lam[k + a.H]) * a.dt[k + a.H];
+    if (w.wave == 0) {
+        const int t = min(w.lane / R, nvalid - 1);
+        const int64_t tg = t0 + t, tn = min(tg + 1, a.L - 1);
+        r.dt = a.dt[s.tok + tg * a.H];
+        r.lam = a.lam[s.tok + tg * a.H];
+        r.A = a.A[s.b * a.a_sb + tg * a.a_st + s.h * a.a_sh];
+        r.dtn = a.dt[s.tok + tn * a.H];
+        r.lamn = a.lam[s.tok + tn * a.H];
     }
+}
+
+// Step 1: each wave's angle prefix sums (in place, its total to `seg`), and
+// wave 0 the scalar tables.  Tokens past the end of the sequence get zero
+// angles and weights.
+template <int R>
+__device__ __forceinline__ void tok_scan(const BwdArgs &a, const Lane &w, int64_t c, int nvalid, RawTok<R> &r,
+                                         float (*seg)[kNH], Tok &o) {
+    constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
     float run = 0.f;
 #pragma unroll
     for (int k = 0; k < TPS; ++k) {
-        run += ps[k];
-        ps[k] = run;
+        run += w.wave * TPS + k < nvalid ? r.th[k] : 0.f;
+        r.th[k] = run;
     }
-    sp.seg[seg][i] = run;
-    if (tid < kWave) {
-        const float cum = wave_incl_scan(lg, lane);
-        if (tid < Q) {
-            sp.cum[tid] = cum;
-            sp.gam[tid] = gam;
-            sp.sig[tid] = sig;
-        }
+    seg[w.wave][w.lane] = run;
+    if (w.wave == 0) {
+        const int t = w.lane / R;
+        const bool in = t < nvalid;
+        const float cum = lane_scan(in && w.lane % R == 0 ? r.dt * r.A : 0.f);
+        const float c2 = cum * kLog2e, c2e = lane_bcast(c2, nvalid * R - 1);
+        const float gam = in ? r.lam * r.dt : 0.f;
+        float sig = gam;
+        if (in && c * Q + t + 1 < a.L) sig += (1.f - r.lamn) * r.dtn;
+        o.c2[w.lane] = c2;
+        o.gam[w.lane] = gam;
+        o.sig[w.lane] = sig;
+        o.v[w.lane] = in ? exp2_fast(c2e - c2) * sig : 0.f;
+        o.ec[w.lane] = in ? exp2_fast(c2) : 0.f;
+        if (w.lane == 0) o.c2e = c2e;
     }
-    __syncthreads();
+}
+
+// Step 2: the cos / sin table of psi_t and psi_e.
+template <int R>
+__device__ __forceinline__ void tok_table(const Lane &w, int nvalid, const RawTok<R> &r, const float (*seg)[kNH],
+                                          h2 *cs, Tok &o) {
+    constexpr int TPS = Shp<R>::TPS;
     float off = 0.f;
-    for (int s2 = 0; s2 < seg; ++s2) off += sp.seg[s2][i];
+    for (int s = 0; s < w.wave; ++s) off += seg[s][w.lane];
 #pragma unroll
     for (int k = 0; k < TPS; ++k) {
-        const int t = seg * TPS + k;
-        if (t < Q) {
-            const float psi = ps[k] + off;
-            float sn, cs;
-            sincos_fast(psi, &sn, &cs);
-            cs_put(&sp.cs[t * kNH + i], cs, sn);
-            if (t == nvalid - 1) sp.psie[i] = psi;
-        }
-    }
-    if (tid < Q) {
-        const float cume = sp.cum[nvalid - 1];
-        sp.v[tid] = tid < nvalid ? __expf(cume - sp.cum[tid]) * sp.sig[tid] : 0.f;
-        sp.ec[tid] = tid < nvalid ? __expf(sp.cum[tid]) : 0.f;
-    }
-    __syncthreads();
-}
-
-// B or C rows of the chunk rotated by -psi_t into LDS [row][LDN] (bf16);
-// rows past the end are zero.  Row = (token, rank).
-template <int R, int NT>
-__device__ void stage_rot(bf16 *dst, const bf16 *src, int64_t tokstr, int nvalid, const h2 *cs) {
-    for (int task = threadIdx.x; task < kRows * 8; task += NT) {
-        const int row = task / 8, cp = task % 8, t = row / R, r = row % R;
-        bf16x8 lo, hi;
-        if (t < nvalid) {
-            const bf16 *p = src + t * tokstr + r * kN + cp * 8;
-            lo = *reinterpret_cast<const bf16x8 *>(p);
-            hi = *reinterpret_cast<const bf16x8 *>(p + kNH);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) lo[e] = hi[e] = (bf16)0.f;
-        }
-        float c[8], s[8];
-        cs_getn<8>(&cs[t * kNH + cp * 8], c, s);   // (t < chunk: rows are within it)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float u = (float)lo[e], w = (float)hi[e];
-            lo[e] = (bf16)(c[e] * u + s[e] * w);
-            hi[e] = (bf16)(c[e] * w - s[e] * u);
-        }
-        *reinterpret_cast<bf16x8 *>(&dst[row * LDN + cp * 8]) = lo;
-        *reinterpret_cast<bf16x8 *>(&dst[row * LDN + kNH + cp * 8]) = hi;
-    }
-}
-
-// x-like rows (P wide) into LDS [row][LDP], optionally scaled per token.
-template <int R, int NT>
-__device__ void stage_rows(bf16 *dst, const bf16 *src, int64_t tokstr, int nvalid, const float *scale) {
-    for (int task = threadIdx.x; task < kRows * 8; task += NT) {
-        const int row = task / 8, cp = task % 8, t = row / R, r = row % R;
-        bf16x8 v;
-        if (t < nvalid) {
-            v = *reinterpret_cast<const bf16x8 *>(src + t * tokstr + r * kP + cp * 8);
-            if (scale) {
-                const float sc = scale[t];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (bf16)(sc * (float)v[e]);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (bf16)0.f;
-        }
-        *reinterpret_cast<bf16x8 *>(&dst[row * LDP + cp * 8]) = v;
+        const int t = w.wave * TPS + k;
+        const float psi = r.th[k] + off;
+        float sn, cn;
+        sincos_fast(psi, &sn, &cn);
+        cs_put(&cs[t * kNH + w.lane], cn, sn);
+        if (t == nvalid - 1) o.psie[w.lane] = psi;
     }
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd_aggr: A_c = R(psi_e) sum_j v_j B^_j x_j^T and Mb_c = sum_t e^{cum_t}
-// C^_t dy_t^T (N x P, fp32), chunk totals.  Wave w owns the N-row tiles w
-// and w + 4 (the two rows of a rotation pair) for all four P tiles.
+// Row staging: one thread a (row, 16-byte piece).
 // ---------------------------------------------------------------------------
+struct RowAt {   // this thread's task
+    int row, cp, t, r;
+};
+template <int R> __device__ __forceinline__ RowAt row_at(const Lane &w) {
+    RowAt k;
+    k.row = w.tid / 8;
+    k.cp = w.tid % 8;
+    k.t = k.row / R;
+    k.r = k.row % R;
+    return k;
+}
+// B or C piece pair (channels i and i + N/2) of the thread's row.
+struct Pair { bf16x8 lo, hi; };
 template <int R>
-__global__ __launch_bounds__(kThr) void k_bwd_aggr(BwdArgs a) {
-    constexpr int Q = kRows / R;
-    __shared__ Pro<Q, kThr> sp;
-    __shared__ __attribute__((aligned(16))) bf16 s_B[kRows * LDN];
-    __shared__ __attribute__((aligned(16))) bf16 s_C[kRows * LDN];
-    __shared__ __attribute__((aligned(16))) bf16 s_vX[kRows * LDP];
-    __shared__ __attribute__((aligned(16))) bf16 s_eY[kRows * LDP];
+__device__ __forceinline__ Pair load_pair(const BwdArgs &a, const Slice &s, const RowAt &k, const void *src,
+                                          int64_t t0, int nvalid) {
+    const int64_t t = t0 + min(k.t, nvalid - 1);
+    const bf16 *p = static_cast<const bf16 *>(src) + ((s.tok + t * a.H) * R + k.r) * kN + k.cp * 8;
+    return Pair{*reinterpret_cast<const bf16x8 *>(p), *reinterpret_cast<const bf16x8 *>(p + kNH)};
+}
+template <int R>
+__device__ __forceinline__ bf16x8 load_row(const BwdArgs &a, const Slice &s, const RowAt &k, const void *src,
+                                           int64_t t0, int nvalid) {
+    const int64_t t = t0 + min(k.t, nvalid - 1);
+    return *reinterpret_cast<const bf16x8 *>(static_cast<const bf16 *>(src) +
+                                             ((s.tok + t * a.H) * R + k.r) * kP + k.cp * 8);
+}
+// Rotated by -psi_t (cos c, sin s of the thread's eight pairs) into [row][LDN].
+__device__ __forceinline__ void put_rot(bf16 *dst, const RowAt &k, Pair v, const float (&c)[8], const float (&s)[8],
+                                        bool in) {
+    Pair o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float u = in ? (float)v.lo[e] : 0.f, x = in ? (float)v.hi[e] : 0.f;
+        o.lo[e] = (bf16)(c[e] * u + s[e] * x);
+        o.hi[e] = (bf16)(c[e] * x - s[e] * u);
+    }
+    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDN + k.cp * 8]) = o.lo;
+    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDN + kNH + k.cp * 8]) = o.hi;
+}
+__device__ __forceinline__ void put_row(bf16 *dst, const RowAt &k, bf16x8 v, bool in) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = in ? v[e] : (bf16)0.f;
+    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDP + k.cp * 8]) = v;
+}
+__device__ __forceinline__ void put_row_scaled(bf16 *dst, const RowAt &k, bf16x8 v, float sc, bool in) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = in ? (bf16)(sc * (float)v[e]) : (bf16)0.f;
+    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDP + k.cp * 8]) = v;
+}
 
-    const int64_t slot = blockIdx.x, bh = slot / a.nchunks, c = slot % a.nchunks;
-    const int64_t b = bh / a.H, h = bh % a.H, t0 = c * Q;
-    const int nvalid = (int)min((int64_t)Q, a.L - t0);
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int g = lane >> 4, l16 = lane & 15;
-    bwd_prologue<Q, kThr>(a, b, h, t0, nvalid, sp);
-
-    const int64_t tok0 = (b * a.L + t0) * a.H + h;
-    stage_rot<R, kThr>(s_B, static_cast<const bf16 *>(a.B) + tok0 * (R * kN), a.H * R * kN, nvalid, sp.cs);
-    stage_rot<R, kThr>(s_C, static_cast<const bf16 *>(a.C) + tok0 * (R * kN), a.H * R * kN, nvalid, sp.cs);
-    stage_rows<R, kThr>(s_vX, static_cast<const bf16 *>(a.x) + tok0 * (R * kP), a.H * R * kP, nvalid, sp.v);
-    stage_rows<R, kThr>(s_eY, static_cast<const bf16 *>(a.dy) + tok0 * (R * kP), a.H * R * kP, nvalid, sp.ec);
-    __syncthreads();
-
-    f32x4 am[2][4], bm[2][4];
+// ---------------------------------------------------------------------------
+// State in registers
+// ---------------------------------------------------------------------------
+// S <- R(sgn psi) S on the lane's pair, and S <- f S.
+__device__ __forceinline__ void rotate(State &st, float cn, float sn) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float re = st[0][u][v], im = st[1][u][v];
+            st[0][u][v] = cn * re - sn * im;
+            st[1][u][v] = sn * re + cn * im;
+        }
+}
+__device__ __forceinline__ void scale(State &st, float f) {
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int pt = 0; pt < 4; ++pt) am[q][pt] = bm[q][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < 2; ++u) st[q][u] *= f;
+}
+__device__ __forceinline__ void zero(State &st) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) st[q][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// st += rows^T (N x K) scaled-rows (K x P): K = the chunk's 64 rows.
+__device__ __forceinline__ void add_outer(State &st, const bf16 *rows, const bf16 *cols, const Lane &w) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-        bf16x8 ab[2], ac[2];
+        bf16x8 pc[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) pc[u] = load_kt(cols, LDP, ks * 32, (2 * w.ph + u) * 16, w.g, w.l16);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            ab[q] = load_kt(s_B, LDN, ks * 32, (wave + 4 * q) * 16, g, l16);
-            ac[q] = load_kt(s_C, LDN, ks * 32, (wave + 4 * q) * 16, g, l16);
-        }
+            const bf16x8 nr = load_kt(rows, LDN, ks * 32, (4 * q + w.it) * 16, w.g, w.l16);
 #pragma unroll
-        for (int pt = 0; pt < 4; ++pt) {
-            const bf16x8 bx = load_kt(s_vX, LDP, ks * 32, pt * 16, g, l16);
-            const bf16x8 by = load_kt(s_eY, LDP, ks * 32, pt * 16, g, l16);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                am[q][pt] = MM::mma(ab[q], bx, am[q][pt]);
-                bm[q][pt] = MM::mma(ac[q], by, bm[q][pt]);
-            }
+            for (int u = 0; u < 2; ++u) st[q][u] = MM::mma(pc[u], nr, st[q][u]);
         }
     }
-    const int64_t NP = kN * kP;
-    float *Af = a.Af + slot * NP, *Mb = a.Mb + slot * NP;
+}
+// fp32 maps: the API's [n][p] arrays, and the workspace's (in thread order).
+__device__ __forceinline__ void load_np(State &st, const float *m, const Lane &w) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = wave * 16 + 4 * g + v;          // pair (i, i + N/2)
-        float sn, cs;
-        sincos_fast(sp.psie[i], &sn, &cs);
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int pt = 0; pt < 4; ++pt) {
-            const int p = pt * 16 + l16;
-            const float re = am[0][pt][v], im = am[1][pt][v];
-            Af[i * kP + p] = cs * re - sn * im;
-            Af[(i + kNH) * kP + p] = sn * re + cs * im;
-            Mb[i * kP + p] = bm[0][pt][v];
-            Mb[(i + kNH) * kP + p] = bm[1][pt][v];
-        }
-    }
-    float *tot = a.tot + slot * (1 + kNH);
-    if (tid == 0) tot[0] = sp.cum[nvalid - 1];
-    if (tid < kNH) tot[1 + tid] = sp.psie[tid];
+        for (int u = 0; u < 2; ++u)
+            st[q][u] = *reinterpret_cast<const f32x4 *>(
+                &m[(64 * q + 16 * w.it + w.l16) * kP + 16 * (2 * w.ph + u) + 4 * w.g]);
+}
+__device__ __forceinline__ void store_np(const State &st, float *m, const Lane &w) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            *reinterpret_cast<f32x4 *>(
+                &m[(64 * q + 16 * w.it + w.l16) * kP + 16 * (2 * w.ph + u) + 4 * w.g]) = st[q][u];
+}
+__device__ __forceinline__ void load_map(State &st, const float *m, const Lane &w) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            st[q][u] = *reinterpret_cast<const f32x4 *>(&m[(2 * q + u) * 4 * kThr + 4 * w.tid]);
+}
+__device__ __forceinline__ void store_map(const State &st, float *m, const Lane &w) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            *reinterpret_cast<f32x4 *>(&m[(2 * q + u) * 4 * kThr + 4 * w.tid]) = st[q][u];
+}
+// The state entering a chunk, bf16 in thread order (each thread reads back
+// what it wrote).
+struct SBf { bf16x8 q[2]; };   // q: [u][v]
+__device__ __forceinline__ SBf to_bf(const State &st) {
+    SBf o;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o.q[q][4 * u + v] = (bf16)st[q][u][v];
+    return o;
+}
+__device__ __forceinline__ void store_sbf(bf16 *m, const SBf &o, const Lane &w) {
+    *reinterpret_cast<bf16x8 *>(&m[8 * w.tid]) = o.q[0];
+    *reinterpret_cast<bf16x8 *>(&m[8 * (kThr + w.tid)]) = o.q[1];
+}
+__device__ __forceinline__ SBf load_sbf(const bf16 *m, const Lane &w) {
+    return SBf{{*reinterpret_cast<const bf16x8 *>(&m[8 * w.tid]),
+                *reinterpret_cast<const bf16x8 *>(&m[8 * (kThr + w.tid)])}};
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd_pass: per (slice, pair i, column p) the forward chunk states, then the
-// reverse sweep.  A wavefront holds the 64 columns of one pair, so the state
-// terms of dpsi_e[i] and dcum_e (sums over columns) are wavefront sums.
-// Grid: slices x (N/2 * P / 256).
+// Sweep of the carried state over n chunks: forward (kFwd) from chunk c0 up,
+//   S <- R(psi_e) (e^{cum_e} S + sum_j v_j B^_j x_j^T),
+// or of its gradient from chunk c0 down,
+//   G <- e^{cum_e} R(-psi_e) G + sum_t e^{cum_t} C^_t dy_t^T.
+// With Sst, the state entering each chunk is stored (and one more after the
+// last: n + 1 stores when n covers all but the segment's last chunk).
+// Returns the sums of cum_e (base 2) and of the lane's psi_e.  Two barriers a
+// chunk; the next chunk's rows and the angles of the one after are in flight
+// while a chunk is worked on.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a, int per) {
-    const int64_t bh = blockIdx.x / per;
-    const int idx = (blockIdx.x % per) * kThr + threadIdx.x;
-    const int i = idx / kP, p = idx % kP;   // (a wavefront: one i, all p)
-    const int64_t NP = kN * kP, base = bh * a.nchunks;
-    const int o_re = i * kP + p, o_im = (i + kNH) * kP + p;
-    constexpr int DEPTH = 8;   // chunks whose loads are issued together
-    bf16 *Sb = reinterpret_cast<bf16 *>(a.Sst);   // (bf16: an MFMA operand, and the decay term below)
-    float sre = 0.f, sim = 0.f;
-    if (a.init_state) {
-        sre = a.init_state[bh * NP + o_re];
-        sim = a.init_state[bh * NP + o_im];
-    }
-    for (int64_t c0 = 0; c0 < a.nchunks; c0 += DEPTH) {
-        float ce[DEPTH], ps[DEPTH], are[DEPTH], aim[DEPTH];
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int64_t s = base + min(c0 + d, a.nchunks - 1);
-            ce[d] = a.tot[s * (1 + kNH)];
-            ps[d] = a.tot[s * (1 + kNH) + 1 + i];
-            are[d] = a.Af[s * NP + o_re];
-            aim[d] = a.Af[s * NP + o_im];
-        }
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            if (c0 + d >= a.nchunks) break;
-            const int64_t s = base + c0 + d;
-            Sb[s * NP + o_re] = (bf16)sre;
-            Sb[s * NP + o_im] = (bf16)sim;
-            const float e = __expf(ce[d]);
-            float sn, cs;
-            sincos_fast(ps[d], &sn, &cs);
-            const float nre = e * (cs * sre - sn * sim) + are[d];
-            const float nim = e * (sn * sre + cs * sim) + aim[d];
-            sre = nre;
-            sim = nim;
-        }
-    }
-    float gre = 0.f, gim = 0.f;
-    if (a.dfinal) {
-        gre = a.dfinal[bh * NP + o_re];
-        gim = a.dfinal[bh * NP + o_im];
-    }
-    float xre = sre, xim = sim;   // S_c, from the last chunk down
-    for (int64_t c1 = a.nchunks - 1; c1 >= 0; c1 -= DEPTH) {
-        float ce[DEPTH], ps[DEPTH], pre[DEPTH], pim[DEPTH], mre[DEPTH], mim[DEPTH];
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int64_t s = base + max(c1 - d, (int64_t)0);
-            ce[d] = a.tot[s * (1 + kNH)];
-            ps[d] = a.tot[s * (1 + kNH) + 1 + i];
-            pre[d] = (float)Sb[s * NP + o_re];
-            pim[d] = (float)Sb[s * NP + o_im];
-            mre[d] = a.Mb[s * NP + o_re];
-            mim[d] = a.Mb[s * NP + o_im];
-        }
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            if (c1 - d < 0) break;
-            const int64_t s = base + c1 - d;
-            float sn, cs;
-            sincos_fast(ps[d], &sn, &cs);
-            const float e = __expf(ce[d]);
-            float dps = gim * xre - gre * xim;                  // rotation of S_c by psi_e
-            const float ure = cs * gre + sn * gim, uim = -sn * gre + cs * gim;
-            float dcm = e * (ure * pre[d] + uim * pim[d]);      // decay e^{cum_e} of S_{c-1}
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                dps += __shfl_xor(dps, o, kWave);
-                dcm += __shfl_xor(dcm, o, kWave);
-            }
-            if (p == 0) {
-                a.pst[s * (2 * kNH) + i] = dps;
-                a.pst[s * (2 * kNH) + kNH + i] = dcm;
-            }
-            bf16 *Ub = reinterpret_cast<bf16 *>(a.Ust);   // (bf16: read only as an MFMA operand)
-            Ub[s * NP + o_re] = (bf16)ure;
-            Ub[s * NP + o_im] = (bf16)uim;
-            gre = e * ure + mre[d];
-            gim = e * uim + mim[d];
-            xre = pre[d];
-            xim = pim[d];
-        }
-    }
-    if (a.dinit) {
-        a.dinit[bh * NP + o_re] = gre;
-        a.dinit[bh * NP + o_im] = gim;
-    }
-}
+template <int R> struct SweepLds {
+    bf16 rows[kRows * LDN], cols[kRows * LDP];
+    h2 cs[Shp<R>::Q * kNH];
+    float seg[kNW][kNH];
+    Tok tok[4];
+};
 
-// Sum over the 16 lanes of a row group (lanes l16 = 0..15 with the same g).
-__device__ __forceinline__ float sum16(float v) {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
-// ---------------------------------------------------------------------------
-// k_bwd_chunk: every gradient of one chunk, eight waves.  Waves 0-3 own row
-// tile w as a column block (j rows: dx, dB^, the masked-score columns),
-// waves 4-7 row tile w - 4 as a row block (t rows: dC^, the y state term);
-// the two halves only read the staged operands, so they run side by side
-// (two waves a SIMD).
-// ---------------------------------------------------------------------------
-constexpr int kThrC = 512;
-template <int R>
-__global__ __launch_bounds__(kThrC) void k_bwd_chunk(BwdArgs a) {
-    constexpr int Q = kRows / R;
-    __shared__ Pro<Q, kThrC> sp;
-    __shared__ __attribute__((aligned(16))) bf16 s_B[kRows * LDN];
-    __shared__ __attribute__((aligned(16))) bf16 s_C[kRows * LDN];
-    __shared__ __attribute__((aligned(16))) bf16 s_X[kRows * LDP];
-    __shared__ __attribute__((aligned(16))) bf16 s_dY[kRows * LDP];
-    __shared__ __attribute__((aligned(16))) bf16 s_S[kN * LDP];   // S_{c-1} [n][p]
-    __shared__ __attribute__((aligned(16))) bf16 s_U[kN * LDP];   // U_c [n][p]
-    __shared__ float s_dpsi[2][kRows * kNH];                      // per row, per pair: B^ and C^ parts
-    __shared__ float s_rc[4][kRows], s_rg[4][kRows];              // per-wave row sums of the mask terms
-    __shared__ float s_cc[kRows], s_cs[kRows];                    // column sums (cum, sigma)
-    __shared__ float s_dv[kRows], s_dcy[kRows];                   // dJ/dv_j, y state term of cum_t
-    __shared__ float s_tok[3][kWave];                             // per token: dcum, dsigma, dgamma
-    __shared__ float s_red[2][4];
-    __shared__ float s_segd[kThrC / kWave - 1][kNH];                // dtheta: segment totals
-
-    const int64_t slot = blockIdx.x, bh = slot / a.nchunks, c = slot % a.nchunks;
-    const int64_t b = bh / a.H, h = bh % a.H, t0 = c * Q;
-    const int nvalid = (int)min((int64_t)Q, a.L - t0);
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int g = lane >> 4, l16 = lane & 15;
-    bwd_prologue<Q, kThrC>(a, b, h, t0, nvalid, sp);
-
-    const int64_t tok0 = (b * a.L + t0) * a.H + h;
-    const int64_t bstr = a.H * R * kN, xstr = a.H * R * kP;
-    stage_rot<R, kThrC>(s_B, static_cast<const bf16 *>(a.B) + tok0 * (R * kN), bstr, nvalid, sp.cs);
-    stage_rot<R, kThrC>(s_C, static_cast<const bf16 *>(a.C) + tok0 * (R * kN), bstr, nvalid, sp.cs);
-    stage_rows<R, kThrC>(s_X, static_cast<const bf16 *>(a.x) + tok0 * (R * kP), xstr, nvalid, nullptr);
-    stage_rows<R, kThrC>(s_dY, static_cast<const bf16 *>(a.dy) + tok0 * (R * kP), xstr, nvalid, nullptr);
-    {
-        const int64_t NP = kN * kP;
-        const bf16x4 *Sg = reinterpret_cast<const bf16x4 *>(reinterpret_cast<const bf16 *>(a.Sst) + slot * NP);
-        const bf16x4 *Ug = reinterpret_cast<const bf16x4 *>(reinterpret_cast<const bf16 *>(a.Ust) + slot * NP);
-        for (int q = tid; q < kN * kP / 4; q += kThrC) {
-            const int n = (4 * q) / kP, p = (4 * q) % kP;
-            *reinterpret_cast<bf16x4 *>(&s_S[n * LDP + p]) = Sg[q];
-            *reinterpret_cast<bf16x4 *>(&s_U[n * LDP + p]) = Ug[q];
-        }
+template <int R, bool kFwd>
+__device__ __forceinline__ void sweep(const BwdArgs &a, const Slice &s, const Lane &w, SweepLds<R> &L, int64_t c0,
+                                      int64_t n, State &st, bf16 *Sst, float *sum_c2, float *sum_psi) {
+    constexpr int Q = Shp<R>::Q;
+    const void *rsrc = kFwd ? a.B : a.C, *csrc = kFwd ? a.x : a.dy;
+    const RowAt ra = row_at<R>(w);
+    auto chunk = [&](int64_t k) { return kFwd ? c0 + k : c0 - k; };
+    auto valid = [&](int64_t c) { return (int)min((int64_t)Q, a.L - c * Q); };
+    RawTok<R> raw;
+    Pair pr;
+    bf16x8 px;
+    *sum_c2 = 0.f;
+    *sum_psi = 0.f;
+    if (n > 0) {
+        load_tok<R>(a, s, w, chunk(0), valid(chunk(0)), raw);
+        pr = load_pair<R>(a, s, ra, rsrc, chunk(0) * Q, valid(chunk(0)));
+        px = load_row<R>(a, s, ra, csrc, chunk(0) * Q, valid(chunk(0)));
+        tok_scan<R>(a, w, chunk(0), valid(chunk(0)), raw, L.seg, L.tok[0]);
+        __syncthreads();
     }
-    __syncthreads();
-    const float Dh = a.D[h];
-
-    float xdy = 0.f;
-    if (wave < 4) {
-    // ============ column block J = wave: dx and dB^ of rows j ============
-    const int J = wave;
-    f32x4 gt[4], dg[4];   // G and dG tiles (T, J): lane element (t = 16T + 4g + v, j = 16J + l16)
-#pragma unroll
-    for (int T = 0; T < 4; ++T) {
-        gt[T] = dg[T] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (T >= J) {
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                gt[T] = MM::mma(MM::load(&s_C[(T * 16 + l16) * LDN + kk * 32 + 8 * g]),
-                                MM::load(&s_B[(J * 16 + l16) * LDN + kk * 32 + 8 * g]), gt[T]);
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                dg[T] = MM::mma(MM::load(&s_dY[(T * 16 + l16) * LDP + kk * 32 + 8 * g]),
-                                MM::load(&s_X[(J * 16 + l16) * LDP + kk * 32 + 8 * g]), dg[T]);
+    for (int64_t k = -1; k < n; ++k) {
+        // (a) chunk k's state update; the table of chunk k + 1
+        if (k >= 0) {
+            const Tok &o = L.tok[k & 3];
+            if (Sst) store_sbf(Sst + chunk(k) * kMap, to_bf(st), w);
+            const float psi = o.psie[16 * w.it + w.l16], e = exp2_fast(o.c2e);
+            float sn, cn;
+            sincos_fast(psi, &sn, &cn);
+            *sum_c2 += o.c2e;
+            *sum_psi += psi;
+            if constexpr (!kFwd) rotate(st, cn, -sn);
+            scale(st, e);
+            add_outer(st, L.rows, L.cols, w);
+            if constexpr (kFwd) rotate(st, cn, sn);
         }
-    }
-    {
-        const int jrow = J * 16 + l16, tj = jrow / R;
-        const float cum_j = sp.cum[tj], sig_j = sp.sig[tj];
-        float colc = 0.f, cols = 0.f;
-#pragma unroll
-        for (int T = 0; T < 4; ++T) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int trow = T * 16 + 4 * g + v, tt = trow / R;
-                float w = 0.f, e = 0.f;
-                if (T >= J) {
-                    if (tj < tt) {
-                        e = __expf(sp.cum[tt] - cum_j);
-                        w = e * sig_j;
-                    } else if (tj == tt) {
-                        w = sp.gam[tt];
-                    }
-                }
-                const float dW = dg[T][v] * gt[T][v];      // dJ/dw_tj
-                const float val = (tj < tt) ? dW * w : 0.f;
-                const float rg = (tj == tt) ? dW : 0.f;
-                colc += val;
-                cols += (tj < tt) ? dW * e : 0.f;
-                gt[T][v] *= w;
-                dg[T][v] *= w;
-                const float rcs = sum16(val), rgs = sum16(rg);
-                if (l16 == 0) {
-                    s_rc[J][trow] = rcs;
-                    s_rg[J][trow] = rgs;
-                }
+        const int64_t c1 = chunk(k + 1);
+        const bool more = k + 1 < n;
+        const int nv1 = more ? valid(c1) : 0;
+        if (more) {
+            tok_table<R>(w, nv1, raw, L.seg, L.cs, L.tok[(k + 1) & 3]);
+            if (k + 2 < n) load_tok<R>(a, s, w, chunk(k + 2), valid(chunk(k + 2)), raw);
+        }
+        __syncthreads();
+        // (b) chunk k + 1's rows staged; the scans of chunk k + 2
+        if (more) {
+            const Tok &o = L.tok[(k + 1) & 3];
+            float c[8], sn[8];
+            cs_getn<8>(&L.cs[ra.t * kNH + ra.cp * 8], c, sn);
+            put_rot(L.rows, ra, pr, c, sn, ra.t < nv1);
+            put_row_scaled(L.cols, ra, px, kFwd ? o.v[ra.row] : o.ec[ra.row], ra.t < nv1);
+            if (k + 2 < n) {
+                const int64_t c2 = chunk(k + 2);
+                const int nv2 = valid(c2);
+                pr = load_pair<R>(a, s, ra, rsrc, c2 * Q, nv2);
+                px = load_row<R>(a, s, ra, csrc, c2 * Q, nv2);
+                tok_scan<R>(a, w, c2, nv2, raw, L.seg, L.tok[(k + 2) & 3]);
             }
-        }
-        colc += __shfl_xor(colc, 16, kWave);
-        colc += __shfl_xor(colc, 32, kWave);
-        cols += __shfl_xor(cols, 16, kWave);
-        cols += __shfl_xor(cols, 32, kWave);
-        if (g == 0) {
-            s_cc[jrow] = colc;
-            s_cs[jrow] = cols;
-        }
-    }
-    // dx_j = sum_t Gw[t][j] dy_t (K = t in pairs of row tiles; the lane's
-    // K elements are rows 4g..4g+3 of both tiles, matched by transposing reads)
-    f32x4 dxa[4], bu[4];
-#pragma unroll
-    for (int pt = 0; pt < 4; ++pt) dxa[pt] = bu[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kp = 0; kp < 2; ++kp) {
-        if (2 * kp + 1 < J) continue;
-        bf16x8 af;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            af[v] = (bf16)gt[2 * kp][v];
-            af[4 + v] = (bf16)gt[2 * kp + 1][v];
-        }
-#pragma unroll
-        for (int pt = 0; pt < 4; ++pt) {
-            const bf16 *yr = &s_dY[(32 * kp + 4 * g + l16 / 4) * LDP + pt * 16 + 4 * (l16 % 4)];
-            const bf16x4 lo = lds_tr4(yr), hi = lds_tr4(yr + 16 * LDP);
-            bf16x8 bfr;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { bfr[v] = lo[v]; bfr[4 + v] = hi[v]; }
-            dxa[pt] = MM::mma(af, bfr, dxa[pt]);
-        }
-    }
-    // (B^ U)_j, K = N
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8 ab = MM::load(&s_B[(J * 16 + l16) * LDN + kk * 32 + 8 * g]);
-#pragma unroll
-        for (int pt = 0; pt < 4; ++pt)
-            bu[pt] = MM::mma(ab, load_kt(s_U, LDP, kk * 32, pt * 16, g, l16), bu[pt]);
-    }
-    {
-        bf16 *dxg = static_cast<bf16 *>(a.dx) + tok0 * (R * kP);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int j = J * 16 + 4 * g + v, t = j / R, r = j % R;
-            const float vj = sp.v[t];
-            float dvp = 0.f;
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-                const int p = pt * 16 + l16;
-                const float xv = (float)s_X[j * LDP + p], yv = (float)s_dY[j * LDP + p];
-                dvp += xv * bu[pt][v];
-                xdy += xv * yv;
-                const float d = dxa[pt][v] + vj * bu[pt][v] + Dh * yv;
-                if (t < nvalid) dxg[t * xstr + r * kP + p] = (bf16)d;
-            }
-            dvp = sum16(dvp);
-            if (l16 == 0) s_dv[j] = dvp;
-        }
-    }
-    // dB^_j = sum_t Wd[t][j] C^_t + v_j U x_j
-    f32x4 db[8], xu[8];
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) db[nt] = xu[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kp = 0; kp < 2; ++kp) {
-        if (2 * kp + 1 < J) continue;
-        bf16x8 af;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            af[v] = (bf16)dg[2 * kp][v];
-            af[4 + v] = (bf16)dg[2 * kp + 1][v];
-        }
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) {
-            const bf16 *cr = &s_C[(32 * kp + 4 * g + l16 / 4) * LDN + nt * 16 + 4 * (l16 % 4)];
-            const bf16x4 lo = lds_tr4(cr), hi = lds_tr4(cr + 16 * LDN);
-            bf16x8 bfr;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { bfr[v] = lo[v]; bfr[4 + v] = hi[v]; }
-            db[nt] = MM::mma(af, bfr, db[nt]);
-        }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 ax = MM::load(&s_X[(J * 16 + l16) * LDP + kk * 32 + 8 * g]);
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            xu[nt] = MM::mma(ax, MM::load(&s_U[(nt * 16 + l16) * LDP + kk * 32 + 8 * g]), xu[nt]);
-    }
-    {
-        bf16 *dbg = static_cast<bf16 *>(a.dB) + tok0 * (R * kN);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int j = J * 16 + 4 * g + v, t = j / R, r = j % R;
-            const float vj = sp.v[t];
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int i = nt * 16 + l16;
-                const float re = db[nt][v] + vj * xu[nt][v], im = db[nt + 4][v] + vj * xu[nt + 4][v];
-                const float bre = (float)s_B[j * LDN + i], bim = (float)s_B[j * LDN + i + kNH];
-                s_dpsi[0][j * kNH + i] = re * bim - im * bre;
-                float cs, sn;
-                cs_get(sp.cs[t * kNH + i], cs, sn);
-                if (t < nvalid) {
-                    dbg[t * bstr + r * kN + i] = (bf16)(cs * re - sn * im);
-                    dbg[t * bstr + r * kN + i + kNH] = (bf16)(sn * re + cs * im);
-                }
-            }
-        }
-    }
-
-    } else {
-    // ============ row block T = wave - 4: dC^ of rows t ============
-    const int T = wave - 4;
-    f32x4 gT[4];   // dG^T tiles (J, T): lane element (j = 16J + 4g + v, t = 16T + l16)
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        gT[Jt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (Jt <= T) {
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                gT[Jt] = MM::mma(MM::load(&s_X[(Jt * 16 + l16) * LDP + kk * 32 + 8 * g]),
-                                 MM::load(&s_dY[(T * 16 + l16) * LDP + kk * 32 + 8 * g]), gT[Jt]);
-            const int tt = (T * 16 + l16) / R;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int tj = (Jt * 16 + 4 * g + v) / R;
-                float w = 0.f;
-                if (tj < tt) w = __expf(sp.cum[tt] - sp.cum[tj]) * sp.sig[tj];
-                else if (tj == tt) w = sp.gam[tt];
-                gT[Jt][v] *= w;
-            }
-        }
-    }
-    f32x4 dc[8], t2[8];
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) dc[nt] = t2[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int jp = 0; jp < 2; ++jp) {
-        if (2 * jp > T) continue;
-        bf16x8 af;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            af[v] = (bf16)gT[2 * jp][v];
-            af[4 + v] = (bf16)gT[2 * jp + 1][v];
-        }
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) {
-            const bf16 *br = &s_B[(32 * jp + 4 * g + l16 / 4) * LDN + nt * 16 + 4 * (l16 % 4)];
-            const bf16x4 lo = lds_tr4(br), hi = lds_tr4(br + 16 * LDN);
-            bf16x8 bfr;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { bfr[v] = lo[v]; bfr[4 + v] = hi[v]; }
-            dc[nt] = MM::mma(af, bfr, dc[nt]);
-        }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 ay = MM::load(&s_dY[(T * 16 + l16) * LDP + kk * 32 + 8 * g]);
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            t2[nt] = MM::mma(ay, MM::load(&s_S[(nt * 16 + l16) * LDP + kk * 32 + 8 * g]), t2[nt]);
-    }
-    {
-        bf16 *dcg = static_cast<bf16 *>(a.dC) + tok0 * (R * kN);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int trow = T * 16 + 4 * g + v, t = trow / R, r = trow % R;
-            const float ec = sp.ec[t];
-            float dcy = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt) dcy += (float)s_C[trow * LDN + nt * 16 + l16] * t2[nt][v];
-            dcy = sum16(dcy);
-            if (l16 == 0) s_dcy[trow] = ec * dcy;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int i = nt * 16 + l16;
-                const float re = dc[nt][v] + ec * t2[nt][v], im = dc[nt + 4][v] + ec * t2[nt + 4][v];
-                const float cre = (float)s_C[trow * LDN + i], cim = (float)s_C[trow * LDN + i + kNH];
-                s_dpsi[1][trow * kNH + i] = re * cim - im * cre;
-                float cs, sn;
-                cs_get(sp.cs[t * kNH + i], cs, sn);
-                if (t < nvalid) {
-                    dcg[t * bstr + r * kN + i] = (bf16)(cs * re - sn * im);
-                    dcg[t * bstr + r * kN + i + kNH] = (bf16)(sn * re + cs * im);
-                }
-            }
-        }
-    }
-    }
-    // <x, dy> over the chunk (the skip term's gradient), one value per
-    // column-block wave
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) xdy += __shfl_xor(xdy, o, kWave);
-    if (lane == 0 && wave < 4) s_red[0][wave] = xdy;
-    __syncthreads();
-
-    // ============ per-token scalars ============
-    const float *pst = a.pst + slot * (2 * kNH);
-    if (tid < kRows) {   // rows -> tokens
-        const int row = tid;
-        const float rc = s_rc[0][row] + s_rc[1][row] + s_rc[2][row] + s_rc[3][row];
-        const float rg = s_rg[0][row] + s_rg[1][row] + s_rg[2][row] + s_rg[3][row];
-        const int t = row / R;
-        const float vt = sp.v[t];
-        const float et = t < nvalid ? __expf(sp.cum[nvalid - 1] - sp.cum[t]) : 0.f;   // v_t / sigma_t
-        const float dcum = rc - s_cc[row] - s_dv[row] * vt + s_dcy[row];
-        const float dsig = s_cs[row] + s_dv[row] * et;
-        // rank rows of a token are R consecutive lanes: sum them
-        float sc = dcum, ss = dsig, sg = rg;
-#pragma unroll
-        for (int o = 1; o < R; o <<= 1) {
-            sc += __shfl_xor(sc, o, kWave);
-            ss += __shfl_xor(ss, o, kWave);
-            sg += __shfl_xor(sg, o, kWave);
-        }
-        if (row % R == 0) {
-            s_tok[0][t] = sc;
-            s_tok[1][t] = ss;
-            s_tok[2][t] = sg;
-        }
-        // dcum_e: the v_j terms and the state decay (per pair, from the pass)
-        float ce = s_dv[row] * vt + pst[kNH + row];
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) ce += __shfl_xor(ce, o, kWave);
-        if (row == 0) s_red[1][0] = ce;
-    }
-    __syncthreads();
-    if (tid < kWave) {   // one lane per token (Q <= 64)
-        const int t = tid;
-        float dcum = t < Q ? s_tok[0][t] : 0.f;
-        if (t == nvalid - 1) dcum += s_red[1][0];
-        // d(dt_u A_u) = sum_{t >= u} dcum_t: an inclusive scan in reverse token
-        // order (lane m holds token Q - 1 - m; lanes past the chunk hold zero)
-        const int rev = max(Q - 1 - t, 0);
-        const float rv = __shfl(dcum, rev, kWave);
-        const float rsc = wave_incl_scan(t < Q ? rv : 0.f, t);
-        const float da = __shfl(rsc, rev, kWave);
-        const float dsig = t < Q ? s_tok[1][t] : 0.f;
-        const float dsig_prev = __shfl(dsig, t > 0 ? t - 1 : 0, kWave);
-        const float dgam = (t < Q ? s_tok[2][t] : 0.f) + dsig;   // sigma_t = gamma_t + ...
-        float dAt = 0.f;
-        if (t < nvalid) {
-            const int64_t tg = t0 + t, k = (b * a.L + tg) * a.H + h;
-            const float dtv = a.dt[k], lamv = a.lam[k];
-            const float Av = a.A[b * a.a_sb + tg * a.a_st + h * a.a_sh];
-            float ddt = Av * da + lamv * dgam;
-            float dl = dtv * dgam;
-            if (t > 0) {   // the previous token's sigma reads this token's lambda and dt
-                ddt += (1.f - lamv) * dsig_prev;
-                dl -= dtv * dsig_prev;
-            }
-            a.ddt[k] = ddt;
-            a.dlam[k] = dl;
-            dAt = dtv * da;
-            if (a.dA_per_token) a.dA[k] = dAt;
-            if (t == nvalid - 1) a.dsig[slot] = dsig;
-        }
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) dAt += __shfl_xor(dAt, o, kWave);
-        if (t == 0) {
-            a.dApart[slot] = dAt;
-            a.dDpart[slot] = s_red[0][0] + s_red[0][1] + s_red[0][2] + s_red[0][3];
-        }
-    }
-    // dtheta: suffix sums over the chunk's tokens of dpsi per pair (lane i),
-    // by waves 1 .. 7, one segment of TSD consecutive tokens each: the
-    // segment's own suffix sums, then the totals of the later segments
-    // through LDS
-    constexpr int NSD = kThrC / kWave - 1, TSD = (Q + NSD - 1) / NSD;
-    const int sd = wave - 1, i = lane;
-    float dl[TSD];
-    if (wave >= 1) {
-        float acc = 0.f;
-#pragma unroll
-        for (int k = TSD - 1; k >= 0; --k) {
-            const int t = sd * TSD + k;
-            float d = 0.f;
-            if (t < nvalid) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    d += s_dpsi[0][(t * R + r) * kNH + i] + s_dpsi[1][(t * R + r) * kNH + i];
-                if (t == nvalid - 1) d += pst[i];
-            }
-            acc += d;
-            dl[k] = acc;
-        }
-        s_segd[sd][i] = acc;
-    }
-    __syncthreads();
-    if (wave >= 1) {
-        float off = 0.f;
-        for (int s2 = sd + 1; s2 < NSD; ++s2) off += s_segd[s2][i];
-        float *dth = a.dtheta + tok0 * kNH + i;
-#pragma unroll
-        for (int k = 0; k < TSD; ++k) {
-            const int t = sd * TSD + k;
-            if (t < nvalid) dth[(int64_t)t * a.H * kNH] = dl[k] + off;
-        }
-    }
-}
-
-// The sigma term of each chunk's last token reaching the next chunk's first
-// token: sigma_e = gamma_e + (1 - lambda_{e+1}) dt_{e+1}.
-__global__ __launch_bounds__(kThr) void k_bwd_finish(BwdArgs a, int Q) {
-    const int64_t s = (int64_t)blockIdx.x * kThr + threadIdx.x;
-    if (s >= a.batch * a.H * a.nchunks) return;
-    const int64_t bh = s / a.nchunks, c = s % a.nchunks;
-    if (c == 0) return;
-    const int64_t b = bh / a.H, h = bh % a.H;
-    const int64_t k = (b * a.L + c * Q) * a.H + h;
-    const float d = a.dsig[s - 1];
-    a.ddt[k] += (1.f - a.lam[k]) * d;
-    a.dlam[k] -= a.dt[k] * d;
-}
-
-// Per-head sums of the chunk partials (dD; dA when A is per head), in a fixed
-// order: one workgroup per head.
-__global__ __launch_bounds__(kThr) void k_bwd_reduce(BwdArgs a) {
-    __shared__ float s_a[kThr], s_d[kThr];
-    const int64_t h = blockIdx.x;
-    const int64_t n = a.batch * a.nchunks;
-    float sa = 0.f, sd = 0.f;
-    for (int64_t q = threadIdx.x; q < n; q += kThr) {
-        const int64_t b = q / a.nchunks, c = q % a.nchunks;
-        const int64_t s = (b * a.H + h) * a.nchunks + c;
-        sa += a.dApart[s];
-        sd += a.dDpart[s];
-    }
-    s_a[threadIdx.x] = sa;
-    s_d[threadIdx.x] = sd;
-    __syncthreads();
-    for (int w = kThr / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            s_a[threadIdx.x] += s_a[threadIdx.x + w];
-            s_d[threadIdx.x] += s_d[threadIdx.x + w];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (Sst) store_sbf(Sst + chunk(n) * kMap, to_bf(st), w);
+}
+
+__device__ __forceinline__ Slice slice_of(const BwdArgs &a, int64_t bh) {
+    Slice s;
+    s.b = bh / a.H;
+    s.h = bh % a.H;
+    s.tok = s.b * a.L * a.H + s.h;
+    return s;
+}
+
+// ---------------------------------------------------------------------------
+// k_bwd_aggr: grid (slices, segments - 1, 2): the forward map of segment y,
+// or the gradient map of segment y + 1.
+// ---------------------------------------------------------------------------
+template <int R>
+__global__ __launch_bounds__(kThr, 4) void k_bwd_aggr(BwdArgs a) {
+    __shared__ __attribute__((aligned(16))) SweepLds<R> L;
+    const Lane w;
+    const int64_t bh = blockIdx.x;
+    const Slice s = slice_of(a, bh);
+    const bool fwd = blockIdx.z == 0;
+    const int64_t seg = blockIdx.y + (fwd ? 0 : 1);
+    const int64_t c0 = seg * a.G, n = min(a.G, a.nchunks - c0);
+    State st;
+    zero(st);
+    float sc, sp;
+    if (fwd) sweep<R, true>(a, s, w, L, c0, n, st, nullptr, &sc, &sp);
+    else sweep<R, false>(a, s, w, L, c0 + n - 1, n, st, nullptr, &sc, &sp);
+    const int64_t slot = bh * a.nseg + seg;
+    store_map(st, (fwd ? a.Af : a.Ar) + slot * kMap, w);
+    float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
+    if (w.ph == 0 && w.g == 0) tot[1 + 16 * w.it + w.l16] = sp;
+    if (w.tid == 0) tot[0] = sc;
+}
+
+// ---------------------------------------------------------------------------
+// k_bwd_pass: grid (slices, 2, 2): the fold over a slice's segments, forward
+// or reverse (z), of the tile columns u = y; the folded maps replace the
+// segments' own (Af[s]: the state after segment s, from init_state; Ar[s]:
+// the gradient of the state entering segment s, from dfinal).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
+    const Lane w;
+    const int64_t bh = blockIdx.x;
+    const int u = blockIdx.y;
+    const bool fwd = blockIdx.z == 0;
+    const float *src = fwd ? a.init_state : a.dfinal;
+    f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
+    if (src) {
+        const float *m = src + bh * kMap + 16 * (2 * w.ph + u) + 4 * w.g;
+        re = *reinterpret_cast<const f32x4 *>(&m[(16 * w.it + w.l16) * kP]);
+        im = *reinterpret_cast<const f32x4 *>(&m[(64 + 16 * w.it + w.l16) * kP]);
+    }
+    float *M = fwd ? a.Af : a.Ar;
+    const int n = (int)a.nseg - 1;
+    constexpr int DEPTH = 4;   // segments whose loads are issued together
+    for (int k0 = 0; k0 < n; k0 += DEPTH) {
+        f32x4 mr[DEPTH], mi[DEPTH];
+        float c2[DEPTH], ps[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int k = min(k0 + d, n - 1);
+            const int64_t slot = bh * a.nseg + (fwd ? k : a.nseg - 1 - k);
+            const float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
+            c2[d] = tot[0];
+            ps[d] = tot[1 + 16 * w.it + w.l16];
+            const float *m = M + slot * kMap + 4 * w.tid;
+            mr[d] = *reinterpret_cast<const f32x4 *>(&m[u * 4 * kThr]);
+            mi[d] = *reinterpret_cast<const f32x4 *>(&m[(2 + u) * 4 * kThr]);
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (k0 + d >= n) break;
+            const int64_t slot = bh * a.nseg + (fwd ? k0 + d : a.nseg - 1 - (k0 + d));
+            const float e = exp2_fast(c2[d]);
+            float sn, cn;
+            sincos_fast(ps[d], &sn, &cn);
+            if (!fwd) sn = -sn;
+            f32x4 nr, ni;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                nr[v] = e * (cn * re[v] - sn * im[v]) + mr[d][v];
+                ni[v] = e * (sn * re[v] + cn * im[v]) + mi[d][v];
+            }
+            re = nr;
+            im = ni;
+            float *m = M + slot * kMap + 4 * w.tid;
+            *reinterpret_cast<f32x4 *>(&m[u * 4 * kThr]) = re;
+            *reinterpret_cast<f32x4 *>(&m[(2 + u) * 4 * kThr]) = im;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_bwd_main: one workgroup a segment (grid: slices x segments).  After the
+// forward sweep, the chunks last to first.  Wave (J, hf) owns row tile J of
+// the chunk as columns j (dx, dB^) and as rows t (dC^), for the half hf of
+// the columns p and of the rotation pairs.  Every output tile is formed
+// transposed, from operands whose rows are permuted (perm_*), so a lane holds
+// eight consecutive channels of one row: 16-byte stores, the row's weights
+// are per-lane scalars, and the sums over a row are in-lane.
+// ---------------------------------------------------------------------------
+template <int R> struct MainLds {
+    bf16 B[kRows * LDN], C[kRows * LDN];
+    bf16 X[kRows * LDP], Y[kRows * LDP], EY[kRows * LDP];   // x, dy, e^{cum} dy
+    bf16 S[kN * LDP], U[kN * LDP];                          // S_{c-1}, U_c  [n][p]
+    h2 cs[2][Shp<R>::Q * kNH];
+    Tok tok[2];
+    float seg[kNW][kNH];
+    float rc[4][kRows], rg[kRows];     // sums of the mask terms by token row group
+    float cc[kRows], csg[kRows];       // by column: cum, sigma
+    float dv[2][kRows], dcy[2][kRows]; // dJ/dv_j and the y state term of cum_t, by half
+    float dps[2][kNH], dcm[kNW];       // state terms of psi_e (by column half) and cum_e
+    float dth[4][kNH];                 // dpsi totals of the row tiles
+    float red[kNW];
+};
+
+template <int R>
+__global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
+    constexpr int Q = Shp<R>::Q;
+    constexpr int TT = 4 / R;   // tokens among a lane's four accumulator rows
+    __shared__ __attribute__((aligned(16))) char mem[std::max(sizeof(SweepLds<R>), sizeof(MainLds<R>))];
+    SweepLds<R> &SW = *reinterpret_cast<SweepLds<R> *>(mem);
+    MainLds<R> &M = *reinterpret_cast<MainLds<R> *>(mem);
+    Lane w;
+    const int64_t bh = blockIdx.x, seg = blockIdx.y;
+    const Slice s = slice_of(a, bh);
+    const int64_t cb = seg * a.G, n = min(a.G, a.nchunks - cb), slot = bh * a.nseg + seg;
+    const bool last = seg == a.nseg - 1;
+    bf16 *Sst = static_cast<bf16 *>(a.Sst) + bh * a.nchunks * kMap;
+    auto valid = [&](int64_t c) { return (int)min((int64_t)Q, a.L - c * Q); };
+
+    // ---- forward sweep: the state entering every chunk; Sp = S after the last
+    State G, Sp;
+    zero(Sp);
+    if (n > 0) {
+        State st;
+        if (seg > 0) load_map(st, a.Af + (slot - 1) * kMap, w);
+        else if (a.init_state) load_np(st, a.init_state + bh * kMap, w);
+        else zero(st);
+        float x0, x1;
+        sweep<R, true>(a, s, w, SW, cb, n - 1, st, Sst, &x0, &x1);
+        if (last && a.dfinal) {   // (else the end state meets a zero gradient, or is the next segment's)
+            sweep<R, true>(a, s, w, SW, cb + n - 1, 1, st, nullptr, &x0, &x1);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) Sp[q][u] = st[q][u];
+        }
+    }
+    if (!last) {
+        load_map(Sp, a.Af + slot * kMap, w);
+        load_map(G, a.Ar + (slot + 1) * kMap, w);
+    } else if (a.dfinal) {
+        load_np(G, a.dfinal + bh * kMap, w);
+    } else {
+        zero(G);
+    }
+
+    // ---- reverse
+    const float Dh = a.D[s.h];
+    float xdy = 0.f, dAsum = 0.f;
+    float pend_dt = 0.f, pend_lam = 0.f, first_dt = 0.f, first_lam = 0.f;   // (wave 0: chunk c + 1's first token)
+    RawTok<R> raw;
+    float sc_dt = 0.f, sc_lam = 0.f, sc_A = 0.f;   // (wave 0: the current chunk's)
+    Pair pB, pC;
+    bf16x8 pX, pY;
+    SBf sb;
+    auto load_rows = [&](int64_t c) {
+        const RowAt ra = row_at<R>(w);
+        const int nv = valid(c);
+        pB = load_pair<R>(a, s, ra, a.B, c * Q, nv);
+        pC = load_pair<R>(a, s, ra, a.C, c * Q, nv);
+        pX = load_row<R>(a, s, ra, a.x, c * Q, nv);
+        pY = load_row<R>(a, s, ra, a.dy, c * Q, nv);
+    };
+    auto stage = [&](int nv, const h2 *cs, const Tok &o) {
+        const RowAt ra = row_at<R>(w);
+        const bool in = ra.t < nv;
+        float c[8], sn[8];
+        cs_getn<8>(&cs[ra.t * kNH + ra.cp * 8], c, sn);
+        put_rot(M.B, ra, pB, c, sn, in);
+        put_rot(M.C, ra, pC, c, sn, in);
+        put_row(M.X, ra, pX, in);
+        put_row(M.Y, ra, pY, in);
+        put_row_scaled(M.EY, ra, pY, o.ec[ra.row], in);
+    };
+    const int64_t ce = cb + n - 1;
+    if (n > 0) {
+        const int nv = valid(ce);
+        load_tok<R>(a, s, w, ce, nv, raw);
+        load_rows(ce);
+        sb = load_sbf(Sst + ce * kMap, w);
+        __syncthreads();   // (the sweep's LDS)
+        tok_scan<R>(a, w, ce, nv, raw, M.seg, M.tok[0]);
+        __syncthreads();
+        tok_table<R>(w, nv, raw, M.seg, M.cs[0], M.tok[0]);
+        sc_dt = raw.dt; sc_lam = raw.lam; sc_A = raw.A;
+        if (n > 1) load_tok<R>(a, s, w, ce - 1, valid(ce - 1), raw);
+        __syncthreads();
+        stage(nv, M.cs[0], M.tok[0]);
+        if (n > 1) load_rows(ce - 1);
+        __syncthreads();
+    }
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t c = ce - k, t0 = c * Q;
+        const int nvalid = valid(c), par = (int)(k & 1);
+        const bool more = k + 1 < n;
+        const Tok &o = M.tok[par];
+        const h2 *cs = M.cs[par];
+        // (the thread index is opaque from here, so that no address of the
+        // chunk's work is held in registers across the loop)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        w = Lane(tid);
+        const int J = w.it, hf = w.ph;
+        const int row = 16 * J + w.l16, tl = row / R;   // this lane's chunk row and token
+
+        // ======== region 0: state step, masked scores ========
+        {
+            const float psi = o.psie[16 * w.it + w.l16], e = exp2_fast(o.c2e);
+            float sn, cn;
+            sincos_fast(psi, &sn, &cn);
+            float dps = 0.f, dcm = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                bf16x4 ur4, ui4, sr4, si4;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float gr = G[0][u][v], gi = G[1][u][v];
+                    dps += gi * Sp[0][u][v] - gr * Sp[1][u][v];       // rotation of S_c by psi_e
+                    const float ur = cn * gr + sn * gi, ui = cn * gi - sn * gr;
+                    sr4[v] = sb.q[0][4 * u + v];
+                    si4[v] = sb.q[1][4 * u + v];
+                    const float sr = (float)sr4[v], si = (float)si4[v];
+                    dcm += ur * sr + ui * si;                         // decay e^{cum_e} of S_{c-1}
+                    ur4[v] = (bf16)ur;
+                    ui4[v] = (bf16)ui;
+                    G[0][u][v] = e * ur;
+                    G[1][u][v] = e * ui;
+                    Sp[0][u][v] = sr;
+                    Sp[1][u][v] = si;
+                }
+                const int at = (16 * w.it + w.l16) * LDP + 16 * (2 * w.ph + u) + 4 * w.g;
+                *reinterpret_cast<bf16x4 *>(&M.U[at]) = ur4;
+                *reinterpret_cast<bf16x4 *>(&M.U[at + 64 * LDP]) = ui4;
+                *reinterpret_cast<bf16x4 *>(&M.S[at]) = sr4;
+                *reinterpret_cast<bf16x4 *>(&M.S[at + 64 * LDP]) = si4;
+            }
+            if (more) sb = load_sbf(Sst + (c - 1) * kMap, w);
+            dps = sum_g(dps);
+            if (w.g == 0) M.dps[w.ph][16 * w.it + w.l16] = dps;
+            dcm = sum_wave(e * dcm);
+            if (w.lane == 0) M.dcm[w.wave] = dcm;
+            add_outer(G, M.C, M.EY, w);
+        }
+        // fragments of the own rows (second operands below)
+        bf16x8 fB[4], fX[2], fY[2];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) fB[kk] = MM::load(&M.B[row * LDN + kk * 32 + 8 * w.g]);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            fX[kk] = MM::load(&M.X[row * LDP + kk * 32 + 8 * w.g]);
+            fY[kk] = MM::load(&M.Y[row * LDP + kk * 32 + 8 * w.g]);
+        }
+        // column tiles (T, J), T >= J: lane element (t = 16 T + 4 g + v, j = row)
+        bf16x8 wG[2], wD[2], wT[2];   // weighted scores as second operands, by pairs of tiles
+        {
+            const float c2j = o.c2[row], sgj = o.sig[row], gmj = o.gam[row];
+            float colc = 0.f, cols = 0.f;
+#pragma unroll
+            for (int kp = 0; kp < 2; ++kp)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int T = 2 * kp + h;
+                    f32x4 gt = {0.f, 0.f, 0.f, 0.f}, dg = gt;
+                    if (T >= J) {
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk)
+                            gt = MM::mma(MM::load(&M.C[(16 * T + w.l16) * LDN + kk * 32 + 8 * w.g]), fB[kk], gt);
+#pragma unroll
+                        for (int kk = 0; kk < 2; ++kk)
+                            dg = MM::mma(MM::load(&M.Y[(16 * T + w.l16) * LDP + kk * 32 + 8 * w.g]), fX[kk], dg);
+#pragma unroll
+                        for (int q = 0; q < TT; ++q) {
+                            const int r0 = 16 * T + 4 * w.g + q * R, tt = r0 / R;   // a token's rows
+                            const bool off = tl < tt, on = tl == tt;
+                            const float ex = off ? exp2_fast(o.c2[r0] - c2j) : 0.f;
+                            const float wt = off ? ex * sgj : on ? gmj : 0.f;
+                            float dW = 0.f;   // dJ/dw summed over the token's rows
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                const int v = q * R + r;
+                                dW += dg[v] * gt[v];
+                                gt[v] *= wt;
+                                dg[v] *= wt;
+                            }
+                            const float od = off ? dW : 0.f;
+                            if (hf == 0) {   // (the halves share the sums)
+                                const float val = od * wt;
+                                colc += val;
+                                const float rs = sum16(val);
+                                if (w.l16 == 0) M.rc[J][r0] = rs;
+                            } else {
+                                cols += od * ex;
+                                if (T == J) {
+                                    const float rs = sum16(on ? dW : 0.f);
+                                    if (w.l16 == 0) M.rg[r0] = rs;
+                                }
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        wG[kp][4 * h + v] = (bf16)gt[v];
+                        wD[kp][4 * h + v] = (bf16)dg[v];
+                    }
+                }
+            if (hf == 0) {
+                colc = sum_g(colc);
+                if (w.g == 0) M.cc[row] = colc;
+            } else {
+                cols = sum_g(cols);
+                if (w.g == 0) M.csg[row] = cols;
+            }
+        }
+        // row tiles (Jt, J), Jt <= J, of dG^T: lane element (j = 16 Jt + 4 g + v, t = row)
+        {
+            const float c2t = o.c2[row], gmt = o.gam[row];
+#pragma unroll
+            for (int jp = 0; jp < 2; ++jp)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int Jt = 2 * jp + h;
+                    f32x4 gT = {0.f, 0.f, 0.f, 0.f};
+                    if (Jt <= J) {
+#pragma unroll
+                        for (int kk = 0; kk < 2; ++kk)
+                            gT = MM::mma(MM::load(&M.X[(16 * Jt + w.l16) * LDP + kk * 32 + 8 * w.g]), fY[kk], gT);
+#pragma unroll
+                        for (int q = 0; q < TT; ++q) {
+                            const int r0 = 16 * Jt + 4 * w.g + q * R, tj = r0 / R;
+                            const float wt = tj < tl ? exp2_fast(c2t - o.c2[r0]) * o.sig[r0] : tj == tl ? gmt : 0.f;
+#pragma unroll
+                            for (int r = 0; r < R; ++r) gT[q * R + r] *= wt;
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) wT[jp][4 * h + v] = (bf16)gT[v];
+                }
+        }
+        if (more) tok_scan<R>(a, w, c - 1, valid(c - 1), raw, M.seg, M.tok[par ^ 1]);
+        __syncthreads();
+
+        // ======== region 1: the chunk's gradients ========
+        const float vj = o.v[row], ec = o.ec[row];
+        const int64_t trow = s.tok + (t0 + tl) * a.H;   // (this lane's token; stored when tl < nvalid)
+        const int rk = row % R;
+        {
+            // dx: columns 32 hf + 8 g + e
+            f32x4 d[2], bu[2];
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab) {
+                d[ab] = bu[ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kp = 0; kp < 2; ++kp)
+                    if (2 * kp + 1 >= J) d[ab] = MM::mma(perm_kt2(M.Y, LDP, 32 * kp, 32 * hf, ab, w), wG[kp], d[ab]);
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    bu[ab] = MM::mma(perm_kt(M.U, LDP, 32 * kk, 32 * hf, ab, w), fB[kk], bu[ab]);
+            }
+            const bf16x8 xv = MM::load(&M.X[row * LDP + 32 * hf + 8 * w.g]);
+            const bf16x8 yv = MM::load(&M.Y[row * LDP + 32 * hf + 8 * w.g]);
+            float dvp = 0.f;
+            bf16x8 out;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float xe = (float)xv[e], ye = (float)yv[e], be = bu[e / 4][e % 4];
+                dvp += xe * be;
+                xdy += xe * ye;
+                out[e] = (bf16)(d[e / 4][e % 4] + vj * be + Dh * ye);
+            }
+            if (tl < nvalid)
+                *reinterpret_cast<bf16x8 *>(static_cast<bf16 *>(a.dx) + (trow * R + rk) * kP + 32 * hf + 8 * w.g) = out;
+            dvp = sum_g(dvp);
+            if (w.g == 0) M.dv[hf][row] = dvp;
+        }
+        float cn[8], sn[8], dpsi[8];
+        cs_getn<8>(&cs[tl * kNH + 32 * hf + 8 * w.g], cn, sn);
+        {
+            // dB: pairs i = 32 hf + 8 g + e
+            f32x4 d[2][2], xu[2][2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab) {
+                    d[q][ab] = xu[q][ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kp = 0; kp < 2; ++kp)
+                        if (2 * kp + 1 >= J)
+                            d[q][ab] = MM::mma(perm_kt2(M.C, LDN, 32 * kp, 64 * q + 32 * hf, ab, w), wD[kp], d[q][ab]);
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+                        xu[q][ab] = MM::mma(perm_rows(M.U, LDP, 64 * q + 32 * hf, 32 * kk, ab, w), fX[kk], xu[q][ab]);
+                }
+            const bf16x8 br = MM::load(&M.B[row * LDN + 32 * hf + 8 * w.g]);
+            const bf16x8 bi = MM::load(&M.B[row * LDN + 64 + 32 * hf + 8 * w.g]);
+            bf16x8 o0, o1;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float re = d[0][e / 4][e % 4] + vj * xu[0][e / 4][e % 4];
+                const float im = d[1][e / 4][e % 4] + vj * xu[1][e / 4][e % 4];
+                dpsi[e] = re * (float)bi[e] - im * (float)br[e];
+                o0[e] = (bf16)(cn[e] * re - sn[e] * im);
+                o1[e] = (bf16)(sn[e] * re + cn[e] * im);
+            }
+            if (tl < nvalid) {
+                bf16 *p = static_cast<bf16 *>(a.dB) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
+                *reinterpret_cast<bf16x8 *>(p) = o0;
+                *reinterpret_cast<bf16x8 *>(p + kNH) = o1;
+            }
+        }
+        {
+            // dC
+            f32x4 d[2][2], t2[2][2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab) {
+                    d[q][ab] = t2[q][ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int jp = 0; jp < 2; ++jp)
+                        if (2 * jp <= J)
+                            d[q][ab] = MM::mma(perm_kt2(M.B, LDN, 32 * jp, 64 * q + 32 * hf, ab, w), wT[jp], d[q][ab]);
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+                        t2[q][ab] = MM::mma(perm_rows(M.S, LDP, 64 * q + 32 * hf, 32 * kk, ab, w), fY[kk], t2[q][ab]);
+                }
+            const bf16x8 cr = MM::load(&M.C[row * LDN + 32 * hf + 8 * w.g]);
+            const bf16x8 ci = MM::load(&M.C[row * LDN + 64 + 32 * hf + 8 * w.g]);
+            float dcy = 0.f;
+            bf16x8 o0, o1;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float tr = t2[0][e / 4][e % 4], ti = t2[1][e / 4][e % 4];
+                const float re = d[0][e / 4][e % 4] + ec * tr, im = d[1][e / 4][e % 4] + ec * ti;
+                dcy += (float)cr[e] * tr + (float)ci[e] * ti;
+                dpsi[e] += re * (float)ci[e] - im * (float)cr[e];
+                o0[e] = (bf16)(cn[e] * re - sn[e] * im);
+                o1[e] = (bf16)(sn[e] * re + cn[e] * im);
+            }
+            if (tl < nvalid) {
+                bf16 *p = static_cast<bf16 *>(a.dC) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
+                *reinterpret_cast<bf16x8 *>(p) = o0;
+                *reinterpret_cast<bf16x8 *>(p + kNH) = o1;
+            }
+            dcy = sum_g(dcy);
+            if (w.g == 0) M.dcy[hf][row] = ec * dcy;
+        }
+        // angle gradients: suffix sums over the tile's tokens, tile totals to LDS
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dpsi[e] = suffix16<R>(sum_rank<R>(dpsi[e]));
+        if (w.l16 == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; e += 4)
+                *reinterpret_cast<f32x4 *>(&M.dth[J][32 * hf + 8 * w.g + e]) =
+                    f32x4{dpsi[e], dpsi[e + 1], dpsi[e + 2], dpsi[e + 3]};
+        }
+        float nx_dt = 0.f, nx_lam = 0.f, nx_A = 0.f;
+        if (more) {
+            tok_table<R>(w, valid(c - 1), raw, M.seg, M.cs[par ^ 1], M.tok[par ^ 1]);
+            nx_dt = raw.dt; nx_lam = raw.lam; nx_A = raw.A;
+            if (k + 2 < n) load_tok<R>(a, s, w, c - 2, valid(c - 2), raw);
+        }
+        __syncthreads();
+
+        // ======== region 2: next rows, dtheta, per-token scalars ========
+        if (more) {
+            stage(valid(c - 1), M.cs[par ^ 1], M.tok[par ^ 1]);
+            if (k + 2 < n) load_rows(c - 2);
+        }
+        if (w.l16 % R == 0 && tl < nvalid) {
+            // (dps: the state's rotation by psi_e, which every token's angle enters)
+#pragma unroll
+            for (int e = 0; e < 8; e += 4) {
+                const int i = 32 * hf + 8 * w.g + e;
+                f32x4 off = *reinterpret_cast<const f32x4 *>(&M.dps[0][i]) +
+                            *reinterpret_cast<const f32x4 *>(&M.dps[1][i]);
+                for (int q = J + 1; q < 4; ++q) off += *reinterpret_cast<const f32x4 *>(&M.dth[q][i]);
+                f32x4u out;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[v] = dpsi[e + v] + off[v];
+                *reinterpret_cast<f32x4u *>(a.dtheta + trow * kNH + i) = out;
+            }
+        }
+        if (w.wave == 0) {
+            const int rw = w.lane, t = rw / R;   // lane: a row; a token's R lanes agree after the sums
+            const bool lead = rw % R == 0, in = t < nvalid;
+            const float dvr = M.dv[0][rw] + M.dv[1][rw], vt = o.v[rw];
+            const float et = in ? exp2_fast(o.c2e - o.c2[rw]) : 0.f;   // v_t / sigma_t
+            float dcum = M.dcy[0][rw] + M.dcy[1][rw] - M.cc[rw] - dvr * vt;
+            float dsig = M.csg[rw] + dvr * et;
+            dcum = sum_rank<R>(dcum);
+            dsig = sum_rank<R>(dsig);
+            for (int q = 0; q <= rw / 16; ++q) dcum += M.rc[q][t * R];
+            // dcum_e: the v_j terms and the state's decay
+            float cend = sum_wave(dvr * vt + (rw < kNW ? M.dcm[rw] : 0.f));
+            if (t == nvalid - 1) dcum += cend;
+            // d(dt_u A_u) = sum_{t >= u} dcum_t: a scan in reverse lane order
+            const float rv = __shfl(lead && in ? dcum : 0.f, kWave - 1 - rw, kWave);
+            const float da = __shfl(lane_scan(rv), kWave - 1 - rw, kWave);
+            const float dsig_prev = __shfl(dsig, max(rw - R, 0), kWave);
+            const float dgam = M.rg[t * R] + dsig;   // sigma_t = gamma_t + ...
+            float ddt = sc_A * da + sc_lam * dgam, dl = sc_dt * dgam;
+            if (t > 0) {   // the previous token's sigma reads this token's lambda and dt
+                ddt += (1.f - sc_lam) * dsig_prev;
+                dl -= sc_dt * dsig_prev;
+            }
+            const int64_t at = s.tok + (t0 + t) * a.H;
+            if (lead && in) {
+                if (t > 0) {   // (token 0 waits for the chunk before it)
+                    a.ddt[at] = ddt;
+                    a.dlam[at] = dl;
+                }
+                const float dAt = sc_dt * da;
+                dAsum += dAt;
+                if (a.dA_per_token) a.dA[at] = dAt;
+            }
+            // the sigma of this chunk's last token reaches the first token of
+            // the chunk worked on before
+            const float dse = lane_bcast(dsig, nvalid * R - 1);
+            if (w.lane == 0) {
+                if (k > 0) {
+                    a.ddt[at + Q * a.H] = pend_dt + (1.f - first_lam) * dse;
+                    a.dlam[at + Q * a.H] = pend_lam - first_dt * dse;
+                } else {
+                    a.dsig[slot] = dse;
+                }
+                if (!more) {   // (k_bwd_finish adds the segment before's)
+                    a.ddt[at] = ddt;
+                    a.dlam[at] = dl;
+                }
+            }
+            pend_dt = ddt;
+            pend_lam = dl;
+            first_dt = sc_dt;
+            first_lam = sc_lam;
+            sc_dt = nx_dt;
+            sc_lam = nx_lam;
+            sc_A = nx_A;
+        }
+        __syncthreads();
+    }
+    if (seg == 0 && a.dinit) store_np(G, a.dinit + bh * kMap, w);
+    // per-segment partials of dD and dA
+    xdy = sum_wave(xdy);
+    if (w.lane == 0) M.red[w.wave] = xdy;
+    dAsum = sum_wave(dAsum);
+    __syncthreads();
+    if (w.tid == 0) {
+        float d = 0.f;
+        for (int q = 0; q < kNW; ++q) d += M.red[q];
+        a.dDpart[slot] = d;
+        a.dApart[slot] = dAsum;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_bwd_finish: blocks 0 .. H - 1 the per-head sums of the segments' partials
+// in a fixed order; the rest the sigma term of each segment's last token in
+// the next segment's first token (sigma_e = gamma_e + (1 - lambda_{e+1}) dt_{e+1}).
+// ---------------------------------------------------------------------------
+constexpr int kThrF = 256;
+__global__ __launch_bounds__(kThrF) void k_bwd_finish(BwdArgs a, int Q) {
+    __shared__ float s_a[kThrF], s_d[kThrF];
+    const int tid = threadIdx.x;
+    if (blockIdx.x >= a.H) {
+        const int64_t q = ((int64_t)blockIdx.x - a.H) * kThrF + tid;
+        if (q >= a.batch * a.H * (a.nseg - 1)) return;
+        const int64_t bh = q / (a.nseg - 1), seg = q % (a.nseg - 1) + 1;
+        const int64_t k = slice_of(a, bh).tok + seg * a.G * Q * a.H;
+        const float d = a.dsig[bh * a.nseg + seg - 1];
+        a.ddt[k] += (1.f - a.lam[k]) * d;
+        a.dlam[k] -= a.dt[k] * d;
+        return;
+    }
+    const int64_t h = blockIdx.x, n = a.batch * a.nseg;
+    float sa = 0.f, sd = 0.f;
+    for (int64_t q = tid; q < n; q += kThrF) {
+        const int64_t s = (q / a.nseg * a.H + h) * a.nseg + q % a.nseg;
+        sa += a.dApart[s];
+        sd += a.dDpart[s];
+    }
+    s_a[tid] = sa;
+    s_d[tid] = sd;
+    __syncthreads();
+    for (int w = kThrF / 2; w > 0; w >>= 1) {
+        if (tid < w) {
+            s_a[tid] += s_a[tid + w];
+            s_d[tid] += s_d[tid + w];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
         a.dD[h] = s_d[0];
         if (!a.dA_per_token) a.dA[h] = s_a[0];
     }
 }
 
-template <int R>
-hipError_t launch_bwd(const BwdArgs &a, hipStream_t stream) {
-    constexpr int Q = kRows / R;
-    const int64_t BH = a.batch * a.H, nslot = BH * a.nchunks;
-    if (a.nchunks > 0)
-        hipLaunchKernelGGL((k_bwd_aggr<R>), dim3((unsigned)nslot), dim3(kThr), 0, stream, a);
-    constexpr int per = kNH * kP / kThr;
-    hipLaunchKernelGGL(k_bwd_pass, dim3((unsigned)(BH * per)), dim3(kThr), 0, stream, a, per);
-    if (a.nchunks > 0) {
-        hipLaunchKernelGGL((k_bwd_chunk<R>), dim3((unsigned)nslot), dim3(kThrC), 0, stream, a);
-        hipLaunchKernelGGL(k_bwd_finish, dim3((unsigned)((nslot + kThr - 1) / kThr)), dim3(kThr), 0,
-                           stream, a, Q);
+// Most segments a slice may be split into: the workspace holds their maps, so
+// the bound does not depend on the device.
+constexpr int64_t kMaxGroups = 1024;
+int64_t max_segments(int64_t BH, int64_t nchunks) {
+    return std::max<int64_t>(1, std::min(nchunks, kMaxGroups / BH));
+}
+
+// Chunks per segment: the least estimated time over the segment counts.  A
+// workgroup of k_bwd_main takes a CU and about kMain a chunk; several
+// segments a slice add two aggregate sweeps (kAggr a chunk, two workgroups a
+// CU) and the fold over the segments.
+int64_t choose_chunks(int64_t BH, int64_t nchunks, int ncu) {
+    constexpr double kMain = 10.0, kAggr = 3.0, kPass = 8.0, kFold = 0.25;   // us
+    const int64_t most = max_segments(BH, nchunks);
+    double best = 0.0;
+    int64_t bestG = nchunks;
+    for (int64_t ns = 1; ns <= most; ++ns) {
+        const int64_t G = (nchunks + ns - 1) / ns, m = (nchunks + G - 1) / G;
+        double t = (double)((BH * m + ncu - 1) / ncu) * G * kMain;
+        if (m > 1) t += (double)((BH * (m - 1) * 2 + 2 * ncu - 1) / (2 * ncu)) * G * kAggr + kPass + kFold * m;
+        if (ns == 1 || t < best) {
+            best = t;
+            bestG = G;
+        }
     }
-    hipLaunchKernelGGL(k_bwd_reduce, dim3((unsigned)a.H), dim3(kThr), 0, stream, a);
+    return bestG;
+}
+
+template <int R>
+hipError_t launch_bwd(const BwdArgs &args, hipStream_t stream) {
+    constexpr int Q = Shp<R>::Q;
+    static int cus[64];
+    BwdArgs a = args;
+    const int64_t BH = a.batch * a.H;
+    a.G = 1;
+    a.nseg = 1;
+    if (a.nchunks > 0) {
+        const int ncu = cu_count(cus);
+        if (ncu <= 0) return hipErrorInvalidDevice;
+        a.G = choose_chunks(BH, a.nchunks, ncu);
+        a.nseg = (a.nchunks + a.G - 1) / a.G;
+    }
+    const unsigned ns = (unsigned)a.nseg, nsl = (unsigned)BH;
+    if (a.nseg > 1) {
+        hipLaunchKernelGGL((k_bwd_aggr<R>), dim3(nsl, ns - 1, 2), dim3(kThr), 0, stream, a);
+        hipLaunchKernelGGL(k_bwd_pass, dim3(nsl, 2, 2), dim3(kThr), 0, stream, a);
+    }
+    hipLaunchKernelGGL((k_bwd_main<R>), dim3(nsl, ns), dim3(kThr), 0, stream, a);
+    const int64_t edges = (BH * (a.nseg - 1) + kThrF - 1) / kThrF;
+    hipLaunchKernelGGL(k_bwd_finish, dim3((unsigned)(a.H + edges)), dim3(kThrF), 0, stream, a, Q);
     return hipGetLastError();
 }
 
@@ -825,19 +1137,18 @@ hipError_t launch_bwd(const BwdArgs &a, hipStream_t stream) {
 
 BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, int64_t P) {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t per = (size_t)BH * (size_t)nchunks;
-    const size_t st = per * (size_t)(N * P) * sizeof(float);
+    const size_t np = (size_t)(N * P), segs = (size_t)BH * (size_t)max_segments(BH, nchunks);
     BwdWorkspaceLayout w = {};
     w.off_Af = kCtlBytes;   // (the scans' control block, left untouched in a shared workspace)
-    w.off_Mb = up(w.off_Af + st);
-    w.off_Sst = up(w.off_Mb + st);
-    w.off_Ust = up(w.off_Sst + st / 2);   // (bf16 maps)
-    w.off_tot = up(w.off_Ust + st / 2);
-    w.off_pst = up(w.off_tot + per * (size_t)(1 + N / 2) * sizeof(float));
-    w.off_dsig = up(w.off_pst + per * (size_t)N * sizeof(float));
-    w.off_dA = up(w.off_dsig + per * sizeof(float));
-    w.off_dD = up(w.off_dA + per * sizeof(float));
-    w.total = up(w.off_dD + per * sizeof(float));
+    w.off_Ar = up(w.off_Af + segs * np * sizeof(float));
+    w.off_Sst = up(w.off_Ar + segs * np * sizeof(float));
+    w.off_tot = up(w.off_Sst + (size_t)BH * (size_t)nchunks * np * 2);
+    w.off_dsig = up(w.off_tot + segs * 2 * (size_t)(1 + N / 2) * sizeof(float));
+    w.off_dA = up(w.off_dsig + segs * sizeof(float));
+    w.off_dD = up(w.off_dA + segs * sizeof(float));
+    // (at least the documented three fp32 maps a chunk)
+    w.total = up(std::max(w.off_dD + segs * sizeof(float),
+                          kCtlBytes + (size_t)BH * (size_t)nchunks * 3 * np * sizeof(float)));
     return w;
 }
 

@@ -91,16 +91,15 @@ struct BwdArgs {
     void *dx, *dB, *dC;
     float *ddt, *dA, *dlam, *dtheta, *dD, *dinit;
     int dA_per_token;                   // dA [B][L][H] (else [H], summed)
-    // workspace regions (bwd_workspace_layout), per (slice, chunk)
-    float *Af;      // [N][P] chunk aggregate R(psi_e) sum_j v_j B^_j x_j^T
-    float *Mb;      // [N][P] sum_t e^{cum_t} C^_t dy_t^T
-    float *tot;     // [1 + N/2] cum_e, psi_e
-    float *Sst;     // [N][P] state entering the chunk, stored as bf16 (an MFMA operand; the decay term)
-    float *Ust;     // [N][P] R(-psi_e) dJ/dS_out, stored as bf16 (an MFMA operand only)
-    float *pst;     // [2][N/2] state terms of dpsi_e and dcum_e (per pair)
-    float *dsig;    // [1] dJ/dsigma of the chunk's last token
-    float *dApart;  // [1] sum over the chunk of dt dJ/d(dt A)
-    float *dDpart;  // [1] sum over the chunk of <x, dy>
+    // workspace regions (bwd_workspace_layout)
+    float *Af;      // per segment, [N][P] in thread order: its forward state map, then the state after it
+    float *Ar;      // per segment: its reverse gradient map, then the gradient of the state entering it
+    void *Sst;      // per chunk: the state entering it, bf16 in thread order (an MFMA operand; the decay term)
+    float *tot;     // per segment and direction: [1 + N/2] sums of cum_e (base 2) and psi_e
+    float *dsig;    // per segment: dJ/dsigma of its last token
+    float *dApart;  // per segment: sum of dt dJ/d(dt A)
+    float *dDpart;  // per segment: sum of <x, dy>
+    int64_t G, nseg;                    // chunks per segment, segments per slice (the launcher's choice)
     int64_t batch, L, H, nchunks;
     int64_t a_sb, a_st, a_sh;
 };
@@ -108,7 +107,7 @@ typedef hipError_t (*bwd_launch_fn)(const BwdArgs &, hipStream_t);
 // backward kernels for the shape (null: none built)
 bwd_launch_fn find_bwd_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
 struct BwdWorkspaceLayout {
-    size_t off_Af, off_Mb, off_tot, off_Sst, off_Ust, off_pst, off_dsig, off_dA, off_dD, total;
+    size_t off_Af, off_Ar, off_Sst, off_tot, off_dsig, off_dA, off_dD, total;
 };
 BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, int64_t P);
 

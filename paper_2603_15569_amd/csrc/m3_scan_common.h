@@ -456,6 +456,18 @@ __device__ __forceinline__ bool is_janitor(int64_t u, int64_t sl, int64_t nsl, i
 constexpr uint32_t kFlagInit = 3;   // probe result for "before the first chunk"
 constexpr int kProbe = 16;          // predecessors probed per look-back round
 
+// Compute units of the current device (cached per device in `cache`; 0 on
+// error).
+inline int cu_count(int *cache) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    int v = __atomic_load_n(&cache[dev], __ATOMIC_RELAXED);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    __atomic_store_n(&cache[dev], v, __ATOMIC_RELAXED);
+    return v;
+}
+
 // Workgroups of one kernel resident on the whole device at once (cached per
 // device in `cache`; 0 on error).
 inline int resident_capacity(const void *fn, int nthr, int *cache) {

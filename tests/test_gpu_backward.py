@@ -154,3 +154,54 @@ def test_backward_deterministic():
     o2, *_ = grads_case(inp, 64, seed=5)
     for k in o1:
         assert torch.equal(o1[k], o2[k]), k
+
+
+# Slices, length and rank for each way the launch splits a slice's chunks into
+# segments: one segment of several chunks (more slices than compute units),
+# one chunk a segment, several segments of several chunks with a shorter last
+# one and a ragged last chunk, and exactly full chunks.
+@pytest.mark.parametrize("B_,H,R,L", [(20, 16, 4, 37), (20, 16, 1, 64), (1, 1, 2, 32), (1, 2, 1, 640),
+                                      (8, 16, 4, 133), (8, 10, 2, 224), (5, 8, 1, 1093)])
+def test_backward_segments(B_, H, R, L):
+    Q = 64 // R
+    say(f"backward segments B={B_} H={H} R={R} L={L}")
+    inp = make_scan_inputs(B_, L, H, 64, 128, R, io="bf16", seed=1300 + B_ + L, device=DEV, chunk=Q)
+    out, dy, dfin, h0, A = grads_case(inp, Q, seed=R + L)
+    slices = [(b, h) for b in range(B_) for h in range(H)]
+    ref = oracle_grads(inp, A, dy, dfin, h0, slices)
+    compare(out, ref, slices, f"bwd B={B_} H={H} R={R} L={L}", A, H)
+    check_head_sums(out, ref, slices, H, f"bwd B={B_} H={H} R={R} L={L}")
+
+
+def test_backward_arrays_at_four_byte_alignment():
+    """dt, lambda, theta and the gradients other than dx, dB, dC need only
+    4-byte alignment: the same bits from arrays that start 4 bytes off."""
+    B_, H, R, L, Q = 2, 3, 1, 150, 64
+    inp = make_scan_inputs(B_, L, H, 64, 128, R, io="bf16", seed=77, device=DEV, chunk=Q)
+    dy = torch.randn(inp.x.shape, device=DEV, generator=torch.Generator(DEV).manual_seed(1)).to(inp.x.dtype)
+    args = (inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, inp.theta, inp.D)
+    want = m3.scan_bwd(*args, dy, Q)
+
+    def off4(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
+        v = buf[1:].view(t.shape)
+        v.copy_(t)
+        return v
+    moved = [off4(t) if t.dtype == torch.float32 else t for t in args]
+    got = {k: (off4(v) if v.dtype == torch.float32 else torch.empty_like(v)) for k, v in want.items()}
+    for v in got.values():
+        v.zero_()
+    d = m3.scan_dims(inp.x, inp.Bm, Q, inp.A)
+    import ctypes
+    n = int(m3.lib().m3_scan_bwd_workspace_bytes(ctypes.byref(d)))
+    ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+    p = [t.data_ptr() for t in moved]
+    status = m3.lib().m3_scan_bwd(
+        ctypes.byref(d), *p, None, dy.data_ptr(), None, got["dx"].data_ptr(), got["dB"].data_ptr(),
+        got["dC"].data_ptr(), got["ddt"].data_ptr(), got["dA"].data_ptr(), got["dlam"].data_ptr(),
+        got["dtheta"].data_ptr(), got["dD"].data_ptr(), None, ws.data_ptr(), n,
+        torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert status == m3.M3_OK
+    for k in want:
+        assert torch.equal(got[k], want[k]), k
