@@ -101,6 +101,9 @@ typedef enum { M3_F32 = 0, M3_BF16 = 1 } m3_dtype;
  * faster there.  When a slice is one segment and io is bf16
  * with rank 4 and chunk 64, a warp-specialised variant runs (half of its
  * waves form the outputs, half stage the inputs and carry the state).
+ * bf16 states of 64 and 32: each workgroup walks a segment of a slice's chunks
+ * with the state in registers, after a pass over the segments' maps when a
+ * slice needs several; every flag selects it, and its own chunk is 64 rows.
  * M3_SCAN_SPLIT: three kernels (chunk states, a state pass over chunks,
  * chunk outputs); the only path for other shapes, and for tokens wider than
  * the single-pass kernels' 32-bit row offsets allow (nheads * rank *
@@ -165,7 +168,7 @@ size_t m3_scan_workspace_bytes(const m3_dims *dims);
  * Supported shapes (else M3_ERR_UNSUPPORTED): io bf16 with dstate 128,
  * headdim 64, rank 1/2/4 and chunk*rank a multiple of 64 with chunk in
  * {32, 64, 128}; io bf16 with headdim 64 and the smaller states of the
- * paper's state-size sweep on the three-kernel path: dstate 64 with (rank,
+ * paper's state-size sweep (kernels of their own, below): dstate 64 with (rank,
  * chunk) in {(1, 64), (1, 128), (2, 32), (2, 64), (4, 16), (4, 32)}, dstate 32
  * with (1, 64), (2, 32), (4, 16); io fp32 with (dstate, headdim) = (16, 16) or
  * (128, 64), rank 1/2/4, chunk in {16, 32, 64} and chunk*rank a multiple of

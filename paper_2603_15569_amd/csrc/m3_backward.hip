@@ -100,15 +100,6 @@ struct Tok {
     float c2e;
 };
 
-// Sum over the 16 lanes of a row group (every lane receives it): four DPP
-// rotations on the VALU.
-__device__ __forceinline__ float sum16(float v) {
-    v += dpp_src<0x128, 0xf>(v);
-    v += dpp_src<0x124, 0xf>(v);
-    v += dpp_src<0x122, 0xf>(v);
-    v += dpp_src<0x121, 0xf>(v);
-    return v;
-}
 // Sum over the R lanes of a token's rank rows.
 template <int R> __device__ __forceinline__ float sum_rank(float v) {
     if constexpr (R >= 2) v += dpp_src<0xB1, 0xf>(v);   // quad_perm: lane ^ 1
@@ -124,35 +115,6 @@ template <int R> __device__ __forceinline__ float suffix16(float v) {
     v += dpp_src<0x108, 0xf>(v);
     return v;
 }
-__device__ __forceinline__ float sum_g(float v) {   // over the four 16-lane groups
-    v += __shfl_xor(v, 16, kWave);
-    v += __shfl_xor(v, 32, kWave);
-    return v;
-}
-__device__ __forceinline__ float sum_wave(float v) { return sum_g(sum16(v)); }
-
-// MFMA operand with its rows (the output's rows) taken from 32 columns of a
-// row-major LDS block so that a lane of the output tiles ab = 0 and 1 holds
-// the columns c0 + 8 g + 4 ab + v: eight consecutive ones.  K elements: rows
-// r0 + 8 g .. + 7 (kt), or rows r0 + 4 g .. + 3 and r0 + 16 + 4 g .. + 3
-// (kt2: the order in which two 16-row accumulator tiles hold them).
-__device__ __forceinline__ bf16x8 cat4(bf16x4 lo, bf16x4 hi) {
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-__device__ __forceinline__ bf16x8 perm_kt(const bf16 *M, int ld, int r0, int c0, int ab, const Lane &w) {
-    const bf16 *p = M + (r0 + 8 * w.g + w.l16 / 4) * ld + c0 + 8 * (w.l16 % 4) + 4 * ab;
-    return cat4(lds_tr4(p), lds_tr4(p + 4 * ld));
-}
-__device__ __forceinline__ bf16x8 perm_kt2(const bf16 *M, int ld, int r0, int c0, int ab, const Lane &w) {
-    const bf16 *p = M + (r0 + 4 * w.g + w.l16 / 4) * ld + c0 + 8 * (w.l16 % 4) + 4 * ab;
-    return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
-}
-// The same with rows r0 .. r0 + 31 of the block as the operand's rows, K
-// along the columns.
-__device__ __forceinline__ bf16x8 perm_rows(const bf16 *M, int ld, int r0, int k0, int ab, const Lane &w) {
-    return MM::load(&M[(r0 + 8 * (w.l16 / 4) + 4 * ab + w.l16 % 4) * ld + k0 + 8 * w.g]);
-}
-
 // ---------------------------------------------------------------------------
 // Chunk prologue, in two steps with a barrier between them, each on values
 // loaded a chunk earlier.
@@ -837,10 +799,10 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 d[ab] = bu[ab] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kp = 0; kp < 2; ++kp)
-                    if (2 * kp + 1 >= J) d[ab] = MM::mma(perm_kt2(M.Y, LDP, 32 * kp, 32 * hf, ab, w), wG[kp], d[ab]);
+                    if (2 * kp + 1 >= J) d[ab] = MM::mma(perm_kt2(M.Y, LDP, 32 * kp, 32 * hf, ab, w.g, w.l16), wG[kp], d[ab]);
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk)
-                    bu[ab] = MM::mma(perm_kt(M.U, LDP, 32 * kk, 32 * hf, ab, w), fB[kk], bu[ab]);
+                    bu[ab] = MM::mma(perm_kt(M.U, LDP, 32 * kk, 32 * hf, ab, w.g, w.l16), fB[kk], bu[ab]);
             }
             const bf16x8 xv = MM::load(&M.X[row * LDP + 32 * hf + 8 * w.g]);
             const bf16x8 yv = MM::load(&M.Y[row * LDP + 32 * hf + 8 * w.g]);
@@ -871,10 +833,10 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                     for (int kp = 0; kp < 2; ++kp)
                         if (2 * kp + 1 >= J)
-                            d[q][ab] = MM::mma(perm_kt2(M.C, LDN, 32 * kp, 64 * q + 32 * hf, ab, w), wD[kp], d[q][ab]);
+                            d[q][ab] = MM::mma(perm_kt2(M.C, LDN, 32 * kp, 64 * q + 32 * hf, ab, w.g, w.l16), wD[kp], d[q][ab]);
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk)
-                        xu[q][ab] = MM::mma(perm_rows(M.U, LDP, 64 * q + 32 * hf, 32 * kk, ab, w), fX[kk], xu[q][ab]);
+                        xu[q][ab] = MM::mma(perm_rows(M.U, LDP, 64 * q + 32 * hf, 32 * kk, ab, w.g, w.l16), fX[kk], xu[q][ab]);
                 }
             const bf16x8 br = MM::load(&M.B[row * LDN + 32 * hf + 8 * w.g]);
             const bf16x8 bi = MM::load(&M.B[row * LDN + 64 + 32 * hf + 8 * w.g]);
@@ -904,10 +866,10 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                     for (int jp = 0; jp < 2; ++jp)
                         if (2 * jp <= J)
-                            d[q][ab] = MM::mma(perm_kt2(M.B, LDN, 32 * jp, 64 * q + 32 * hf, ab, w), wT[jp], d[q][ab]);
+                            d[q][ab] = MM::mma(perm_kt2(M.B, LDN, 32 * jp, 64 * q + 32 * hf, ab, w.g, w.l16), wT[jp], d[q][ab]);
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk)
-                        t2[q][ab] = MM::mma(perm_rows(M.S, LDP, 64 * q + 32 * hf, 32 * kk, ab, w), fY[kk], t2[q][ab]);
+                        t2[q][ab] = MM::mma(perm_rows(M.S, LDP, 64 * q + 32 * hf, 32 * kk, ab, w.g, w.l16), fY[kk], t2[q][ab]);
                 }
             const bf16x8 cr = MM::load(&M.C[row * LDN + 32 * hf + 8 * w.g]);
             const bf16x8 ci = MM::load(&M.C[row * LDN + 64 + 32 * hf + 8 * w.g]);

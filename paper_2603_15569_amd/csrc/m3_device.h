@@ -71,6 +71,13 @@ __device__ __forceinline__ float reduce_angle(float x) {
 __device__ __forceinline__ void sincos_fast(float x, float *s, float *c) {
     __sincosf(reduce_angle(x), s, c);
 }
+// The same with the reduction in revolutions, the units of v_sin and v_cos
+// (four operations): x / 2 pi, less its whole part.
+__device__ __forceinline__ void sincos_rev(float x, float *s, float *c) {
+    const float r = __builtin_amdgcn_fractf(x * 0.15915494309189533577f);
+    *s = __builtin_amdgcn_sinf(r);
+    *c = __builtin_amdgcn_cosf(r);
+}
 __device__ __forceinline__ void sincos_fast(double x, double *s, double *c) { sincos(x, s, c); }
 __device__ __forceinline__ float exp_fast(float x) { return __expf(x); }
 // 2^x on the hardware exp unit (v_exp_f32)

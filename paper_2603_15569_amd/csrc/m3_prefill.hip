@@ -516,15 +516,6 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t stream) {
     X(0, float, 128, 64, 2, 32)    \
     X(0, float, 128, 64, 4, 16)    \
     X(0, float, 128, 64, 4, 32)    \
-    X(1, bf16, 32, 64, 1, 64)      \
-    X(1, bf16, 32, 64, 2, 32)      \
-    X(1, bf16, 32, 64, 4, 16)      \
-    X(1, bf16, 64, 64, 1, 64)      \
-    X(1, bf16, 64, 64, 1, 128)     \
-    X(1, bf16, 64, 64, 2, 32)      \
-    X(1, bf16, 64, 64, 2, 64)      \
-    X(1, bf16, 64, 64, 4, 16)      \
-    X(1, bf16, 64, 64, 4, 32)      \
     X(1, bf16, 128, 64, 1, 64)     \
     X(1, bf16, 128, 64, 1, 128)    \
     X(1, bf16, 128, 64, 2, 32)     \
@@ -540,7 +531,7 @@ ScanImpl find_scan_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q) {
         return ScanImpl{&launch_scan<T, N_, P_, R_, Q_>, (int)sizeof(typename AccOf<T>::type), false, nullptr};
     M3_SCAN_SHAPES(M3_CASE)
 #undef M3_CASE
-    return ScanImpl{nullptr, 0, false, nullptr};
+    return find_walk_impl(io, N, P, R, Q);   // bf16 with the smaller states
 }
 
 }  // namespace m3

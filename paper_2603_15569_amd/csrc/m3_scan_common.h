@@ -188,6 +188,67 @@ __device__ __forceinline__ float load_kt(const float *M, int ld, int r0, int c0,
     return M[(r0 + g) * ld + c0 + l16];
 }
 
+// Sum over the 16 lanes of a row group (every lane receives it): four DPP
+// rotations on the VALU.
+__device__ __forceinline__ float sum16(float v) {
+    v += dpp_src<0x128, 0xf>(v);
+    v += dpp_src<0x124, 0xf>(v);
+    v += dpp_src<0x122, 0xf>(v);
+    v += dpp_src<0x121, 0xf>(v);
+    return v;
+}
+__device__ __forceinline__ float sum_g(float v) {   // over the four 16-lane groups
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
+    return v;
+}
+__device__ __forceinline__ float sum_wave(float v) { return sum_g(sum16(v)); }
+
+// Tile order of a channel axis (within each group of 32): LDS position 16 ab +
+// 4 g + v holds channel 8 g + 4 ab + v, so that the lane (g, .) of the 16-row
+// output tiles ab = 0 and 1 holds the eight consecutive channels 8 g .. 8 g + 7
+// of its column: 16-byte global stores, while every tile operand is read from
+// 16 consecutive positions (a permuted read puts its lanes on half the banks).
+__device__ __forceinline__ int chan_of(int pos) { return (pos & ~31) + 8 * (pos / 4 % 4) + 4 * (pos / 16 % 2) + pos % 4; }
+// Piece cp (channels 8 cp .. 8 cp + 7) of a row in tile order.
+__device__ __forceinline__ bf16x8 cat4(bf16x4 lo, bf16x4 hi) {
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ void put_tile_order(bf16 *row, int cp, const bf16x8 &v) {
+    bf16 *p = row + cp / 4 * 32 + cp % 4 * 4;
+    *reinterpret_cast<bf16x4 *>(p) = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+    *reinterpret_cast<bf16x4 *>(p + 16) = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+}
+__device__ __forceinline__ bf16x8 get_tile_order(const bf16 *row, int cp) {
+    const bf16 *p = row + cp / 4 * 32 + cp % 4 * 4;
+    return cat4(*reinterpret_cast<const bf16x4 *>(p), *reinterpret_cast<const bf16x4 *>(p + 16));
+}
+// load_kt with K elements in the order in which two 16-row accumulator tiles
+// hold them: rows r0 + 4 g .. + 3 and r0 + 16 + 4 g .. + 3.
+__device__ __forceinline__ bf16x8 load_kt2(const bf16 *M, int ld, int r0, int c0, int g, int l16) {
+    const bf16 *p = M + (r0 + 4 * g + l16 / 4) * ld + c0 + 4 * (l16 % 4);
+    return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
+}
+
+// MFMA operand with its rows (the output's rows) taken from 32 columns of a
+// row-major LDS block so that a lane of the output tiles ab = 0 and 1 holds
+// the columns c0 + 8 g + 4 ab + v: eight consecutive ones.  K elements: rows
+// r0 + 8 g .. + 7 (kt), or rows r0 + 4 g .. + 3 and r0 + 16 + 4 g .. + 3
+// (kt2: the order in which two 16-row accumulator tiles hold them).
+__device__ __forceinline__ bf16x8 perm_kt(const bf16 *M, int ld, int r0, int c0, int ab, int g, int l16) {
+    const bf16 *p = M + (r0 + 8 * g + l16 / 4) * ld + c0 + 8 * (l16 % 4) + 4 * ab;
+    return cat4(lds_tr4(p), lds_tr4(p + 4 * ld));
+}
+__device__ __forceinline__ bf16x8 perm_kt2(const bf16 *M, int ld, int r0, int c0, int ab, int g, int l16) {
+    const bf16 *p = M + (r0 + 4 * g + l16 / 4) * ld + c0 + 8 * (l16 % 4) + 4 * ab;
+    return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
+}
+// The same with rows r0 .. r0 + 31 of the block as the operand's rows, K
+// along the columns.
+__device__ __forceinline__ bf16x8 perm_rows(const bf16 *M, int ld, int r0, int k0, int ab, int g, int l16) {
+    return Mma<bf16>::load(&M[(r0 + 8 * (l16 / 4) + 4 * ab + l16 % 4) * ld + k0 + 8 * g]);
+}
+
 // Four consecutive output columns of one row, held by one lane of a
 // transposed MFMA tile (the lane's four accumulator rows are y columns).
 __device__ __forceinline__ void store4(bf16 *dst, const f32x4 &v) {

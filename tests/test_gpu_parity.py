@@ -992,3 +992,43 @@ def test_workspace_shared_across_calls():
                         dy, 64, workspace=ws)
             torch.cuda.synchronize()
             assert np.array_equal(ctl_words(ws), before)
+
+
+# The smaller states' kernels walk segments of 64-row chunks: one segment of
+# several chunks (more slices than compute units), one chunk a segment, few
+# and many segments a slice (the fold in the kernel and as its own launch), a
+# ragged and an exact last chunk; with the gate, the per-head frequencies and
+# an initial state and carry.
+@pytest.mark.parametrize("N,R,Q,B_,H,L,gate,ph,init", [
+    (64, 1, 64, 40, 10, 129, True, False, True), (64, 4, 32, 33, 8, 48, False, True, True),
+    (32, 2, 32, 40, 8, 65, True, True, False), (64, 1, 128, 1, 1, 64 * 9, False, False, True),
+    (64, 2, 64, 1, 2, 32 * 40 + 5, True, True, True), (32, 1, 64, 2, 3, 64 * 30 + 1, True, False, True),
+    (32, 4, 16, 1, 2, 16 * 70 + 7, False, True, False), (64, 4, 16, 1, 1, 3, True, False, True)])
+def test_small_state_segments(N, R, Q, B_, H, L, gate, ph, init):
+    P = 64
+    say(f"small-state segments N={N} R={R} Q={Q} B={B_} H={H} L={L} gate={gate} ph={ph} init={init}")
+    inp = make_scan_inputs(B_, L, H, P, N, R, io="bf16", seed=2100 + L, device=DEV, chunk=Q)
+    g = torch.Generator(DEV).manual_seed(L)
+    kw, okw = {}, {}
+    slices = [(b, h) for b in sorted({0, B_ - 1}) for h in range(H)]
+    if init:
+        h0 = torch.randn((B_, H, N, P), device=DEV, generator=g) * 0.3
+        cB = torch.randn((B_, H, R, N), device=DEV, generator=g).to(torch.bfloat16)
+        cX = torch.randn((B_, H, R, P), device=DEV, generator=g).to(torch.bfloat16)
+        kw = dict(init_state=h0, init_carry=(cB, cX))
+        okw = dict(init_state=oracle.slices_of_state(h0, slices), init_B=oracle.slices_of_state(cB, slices),
+                   init_X=oracle.slices_of_state(cX, slices))
+    z = torch.randn(inp.x.shape, device=DEV, generator=g).to(torch.bfloat16) if gate else None
+    theta = inp.omega if ph else inp.theta
+    y, fs, (oB, oX) = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, theta, inp.D, chunk=Q, z=z, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.slices_of_scan(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, inp.theta, inp.D, slices)
+    ry, rs, rb, rx = oracle.scan(**ref, **okw)
+    for k, (b, h) in enumerate(slices):
+        want = ry[k]
+        if gate:
+            want = oracle.gate(want, z[b, :, h].double().cpu().numpy())
+        assert oracle.rel_err(y[b, :, h].double().cpu().numpy(), want) <= 2e-2, (b, h)
+        assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 2e-2, (b, h)
+        assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
+        assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
