@@ -635,6 +635,7 @@ extern "C" m3_status m3_scan_bwd(const m3_dims *d, const void *x, const void *B,
     a.Ar = reinterpret_cast<float *>(ws + wl.off_Ar);
     a.Sst = ws + wl.off_Sst;
     a.tot = reinterpret_cast<float *>(ws + wl.off_tot);
+    a.dump = ws + wl.off_dump;
     a.dsig = reinterpret_cast<float *>(ws + wl.off_dsig);
     a.dApart = reinterpret_cast<float *>(ws + wl.off_dA);
     a.dDpart = reinterpret_cast<float *>(ws + wl.off_dD);

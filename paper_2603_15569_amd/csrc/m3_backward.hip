@@ -65,8 +65,9 @@ using namespace scan;
 
 constexpr int kN = 128, kP = 64, kNH = 64, kRows = 64;
 constexpr int kNW = 8, kThr = kNW * kWave;
-constexpr int LDN = kN + 8;   // bf16 row strides (16-byte padding)
-constexpr int LDP = kP + 8;
+constexpr int LDN = kN + 16;  // bf16 row strides (32-byte padding: FShape::PAD)
+constexpr int LDP = kP + 16;
+constexpr int LDC = kNH + 4;  // cos / sin rows (as many dwords apart)
 constexpr int kMap = kN * kP;
 constexpr float kLog2e = 1.44269504088896340736f;
 typedef Mma<bf16> MM;
@@ -74,11 +75,13 @@ typedef Mma<bf16> MM;
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Lane and wave coordinates of a 512-thread workgroup.  The carried N x P
-// state is held transposed in MFMA tiles: wave (it, ph) owns the pair tiles
-// n = 16 it + l16 (q = 0) and 64 + 16 it + l16 (q = 1) and the columns
-// p = 16 (2 ph + u) + 4 g + v, element st[q][u][v].
+// state is held transposed in MFMA tiles: wave (it, ph) owns the positions
+// 16 it + l16 (q = 0) and 64 + 16 it + l16 (q = 1) of N and the positions
+// 16 (2 ph + u) + 4 g + v of P, element st[q][u][v].  Positions are in tile
+// order (chan_of) everywhere in LDS and registers: pair `i` of the lane is
+// chan_of(16 it + l16).
 struct Lane {
-    int tid, lane, wave, g, l16, it, ph;
+    int tid, lane, wave, g, l16, it, ph, i;
     __device__ __forceinline__ Lane() : Lane((int)threadIdx.x) {}
     __device__ __forceinline__ explicit Lane(int tid_) {
         tid = tid_;
@@ -88,6 +91,7 @@ struct Lane {
         l16 = lane & 15;
         it = wave & 3;
         ph = wave >> 2;
+        i = chan_of(16 * it + l16);
     }
 };
 typedef f32x4 State[2][2];
@@ -96,7 +100,7 @@ typedef f32x4 State[2][2];
 // sigma, v, e^{cum}; its total log-decay and the pairs' total angles.
 struct Tok {
     float c2[kRows], gam[kRows], sig[kRows], v[kRows], ec[kRows];
-    float psie[kNH];
+    float psie[kNH], ce[kNH], se[kNH];   // psi_e, its cosine and sine
     float c2e;
 };
 
@@ -128,49 +132,64 @@ struct Slice {   // the slice's offsets
     int64_t b, h, tok;   // tok: (b L) H + h, the slice's first scalar
 };
 
+// Where a thread's loads stand in the chunk to be loaded next, as token indices
+// (b L + t) H + h advanced a chunk at a time, so that no load needs a 64-bit
+// product: `th` its first angle token, `row` its staged row's token.
+struct Cur {
+    int64_t th, row, t0;   // t0: the chunk's first token
+};
+// Steps back to the last valid token for a token t past the end (only the
+// sequence's last chunk is ragged: a branch rarely taken).
+__device__ __forceinline__ int64_t past_end(int t, int nvalid, int q, int64_t stride) {
+    int64_t o = 0;
+    if (nvalid < q) {
+        asm volatile("");   // (a branch, not selects on every load)
+        o = t >= nvalid ? (nvalid - 1 - t) * stride : 0;
+    }
+    return o;
+}
+
 // Raw values of a chunk's prologue: wave w's tokens w TPS .. of the angles
 // (pair = lane), and, by wave 0 with one lane a row, the token's scalars.
-template <int R> struct RawTok {
+template <int R>
+struct RawTok {
     float th[Shp<R>::TPS];
     float dt, lam, A, dtn, lamn;
 };
 
 template <int R>
-__device__ __forceinline__ void load_tok(const BwdArgs &a, const Slice &s, const Lane &w, int64_t c, int nvalid,
+__device__ __forceinline__ void load_tok(const BwdArgs &a, const Slice &s, const Lane &w, const Cur &u, int nvalid,
                                          RawTok<R> &r) {
     constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
-    const int64_t t0 = c * Q;
-    const float *th = a.theta + (s.tok + t0 * a.H) * kNH + w.lane;
 #pragma unroll
-    for (int k = 0; k < TPS; ++k) {
-        const int t = min(w.wave * TPS + k, nvalid - 1);
-        r.th[k] = th[(int64_t)t * a.H * kNH];
-    }
+    for (int k = 0; k < TPS; ++k)
+        r.th[k] = a.theta[(u.th + k * a.H + past_end(w.wave * TPS + k, nvalid, Q, a.H)) * kNH + w.lane];
     if (w.wave == 0) {
-        const int t = min(w.lane / R, nvalid - 1);
-        const int64_t tg = t0 + t, tn = min(tg + 1, a.L - 1);
-        r.dt = a.dt[s.tok + tg * a.H];
-        r.lam = a.lam[s.tok + tg * a.H];
-        r.A = a.A[s.b * a.a_sb + tg * a.a_st + s.h * a.a_sh];
+        const int64_t t = u.t0 + min(w.lane / R, nvalid - 1), tn = min(t + 1, a.L - 1);
+        r.dt = a.dt[s.tok + t * a.H];
+        r.lam = a.lam[s.tok + t * a.H];
+        r.A = a.A[s.b * a.a_sb + t * a.a_st + s.h * a.a_sh];
         r.dtn = a.dt[s.tok + tn * a.H];
         r.lamn = a.lam[s.tok + tn * a.H];
     }
 }
 
-// Step 1: each wave's angle prefix sums (in place, its total to `seg`), and
-// wave 0 the scalar tables.  Tokens past the end of the sequence get zero
-// angles and weights.
+// Step 1: each wave's angle prefix sums (its total to `seg`), and wave 0 the
+// scalar tables.  Tokens past the end of the sequence get zero angles and
+// weights.
 template <int R>
-__device__ __forceinline__ void tok_scan(const BwdArgs &a, const Lane &w, int64_t c, int nvalid, RawTok<R> &r,
-                                         float (*seg)[kNH], Tok &o) {
+__device__ __forceinline__ void tok_scan(const BwdArgs &a, const Lane &w, int64_t c, int nvalid, const RawTok<R> &r,
+                                         float (&ps)[Shp<R>::TPS], float (*seg)[kNH], Tok &o) {
     constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
-    float run = 0.f;
 #pragma unroll
-    for (int k = 0; k < TPS; ++k) {
-        run += w.wave * TPS + k < nvalid ? r.th[k] : 0.f;
-        r.th[k] = run;
+    for (int k = 0; k < TPS; ++k) ps[k] = r.th[k];
+    if (nvalid < Q) {
+#pragma unroll
+        for (int k = 0; k < TPS; ++k) ps[k] = w.wave * TPS + k < nvalid ? ps[k] : 0.f;
     }
-    seg[w.wave][w.lane] = run;
+#pragma unroll
+    for (int k = 1; k < TPS; ++k) ps[k] += ps[k - 1];
+    seg[w.wave][w.lane] = ps[TPS - 1];
     if (w.wave == 0) {
         const int t = w.lane / R;
         const bool in = t < nvalid;
@@ -188,21 +207,30 @@ __device__ __forceinline__ void tok_scan(const BwdArgs &a, const Lane &w, int64_
     }
 }
 
-// Step 2: the cos / sin table of psi_t and psi_e.
+// Step 2: the cos / sin table of psi_t, and psi_e with its own in fp32.
 template <int R>
-__device__ __forceinline__ void tok_table(const Lane &w, int nvalid, const RawTok<R> &r, const float (*seg)[kNH],
-                                          h2 *cs, Tok &o) {
+__device__ __forceinline__ void tok_table(const Lane &w, int nvalid, const float (&ps)[Shp<R>::TPS],
+                                          const float (*seg)[kNH], h2 *cs, Tok &o) {
     constexpr int TPS = Shp<R>::TPS;
     float off = 0.f;
     for (int s = 0; s < w.wave; ++s) off += seg[s][w.lane];
+    float pe = 0.f, se = 0.f, ce = 0.f;
 #pragma unroll
     for (int k = 0; k < TPS; ++k) {
-        const int t = w.wave * TPS + k;
-        const float psi = r.th[k] + off;
+        const float psi = ps[k] + off;
         float sn, cn;
-        sincos_fast(psi, &sn, &cn);
-        cs_put(&cs[t * kNH + w.lane], cn, sn);
-        if (t == nvalid - 1) o.psie[w.lane] = psi;
+        sincos_rev(psi, &sn, &cn);
+        cs_put(&cs[(w.wave * TPS + k) * LDC + w.lane], cn, sn);
+        if (k == (nvalid - 1) % TPS) {
+            pe = psi;
+            se = sn;
+            ce = cn;
+        }
+    }
+    if (w.wave == (nvalid - 1) / TPS) {
+        o.psie[w.lane] = pe;
+        o.ce[w.lane] = ce;
+        o.se[w.lane] = se;
     }
 }
 
@@ -220,44 +248,34 @@ template <int R> __device__ __forceinline__ RowAt row_at(const Lane &w) {
     k.r = k.row % R;
     return k;
 }
-// B or C piece pair (channels i and i + N/2) of the thread's row.
+// B or C piece pair (channels i and i + N/2) of the thread's row at token `at`.
 struct Pair { bf16x8 lo, hi; };
 template <int R>
-__device__ __forceinline__ Pair load_pair(const BwdArgs &a, const Slice &s, const RowAt &k, const void *src,
-                                          int64_t t0, int nvalid) {
-    const int64_t t = t0 + min(k.t, nvalid - 1);
-    const bf16 *p = static_cast<const bf16 *>(src) + ((s.tok + t * a.H) * R + k.r) * kN + k.cp * 8;
+__device__ __forceinline__ Pair load_pair(const RowAt &k, const void *src, int64_t at) {
+    const bf16 *p = static_cast<const bf16 *>(src) + (at * R + k.r) * kN + k.cp * 8;
     return Pair{*reinterpret_cast<const bf16x8 *>(p), *reinterpret_cast<const bf16x8 *>(p + kNH)};
 }
 template <int R>
-__device__ __forceinline__ bf16x8 load_row(const BwdArgs &a, const Slice &s, const RowAt &k, const void *src,
-                                           int64_t t0, int nvalid) {
-    const int64_t t = t0 + min(k.t, nvalid - 1);
-    return *reinterpret_cast<const bf16x8 *>(static_cast<const bf16 *>(src) +
-                                             ((s.tok + t * a.H) * R + k.r) * kP + k.cp * 8);
+__device__ __forceinline__ bf16x8 load_row(const RowAt &k, const void *src, int64_t at) {
+    return *reinterpret_cast<const bf16x8 *>(static_cast<const bf16 *>(src) + (at * R + k.r) * kP + k.cp * 8);
 }
 // Rotated by -psi_t (cos c, sin s of the thread's eight pairs) into [row][LDN].
-__device__ __forceinline__ void put_rot(bf16 *dst, const RowAt &k, Pair v, const float (&c)[8], const float (&s)[8],
-                                        bool in) {
+__device__ __forceinline__ void put_rot(bf16 *dst, const RowAt &k, const Pair &v, const float (&c)[8],
+                                        const float (&s)[8]) {
     Pair o;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const float u = in ? (float)v.lo[e] : 0.f, x = in ? (float)v.hi[e] : 0.f;
+        const float u = (float)v.lo[e], x = (float)v.hi[e];
         o.lo[e] = (bf16)(c[e] * u + s[e] * x);
         o.hi[e] = (bf16)(c[e] * x - s[e] * u);
     }
-    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDN + k.cp * 8]) = o.lo;
-    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDN + kNH + k.cp * 8]) = o.hi;
+    put_tile_order(&dst[k.row * LDN], k.cp, o.lo);
+    put_tile_order(&dst[k.row * LDN + kNH], k.cp, o.hi);
 }
-__device__ __forceinline__ void put_row(bf16 *dst, const RowAt &k, bf16x8 v, bool in) {
+__device__ __forceinline__ void put_scaled(bf16 *dst, const RowAt &k, bf16x8 v, float sc) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = in ? v[e] : (bf16)0.f;
-    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDP + k.cp * 8]) = v;
-}
-__device__ __forceinline__ void put_row_scaled(bf16 *dst, const RowAt &k, bf16x8 v, float sc, bool in) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = in ? (bf16)(sc * (float)v[e]) : (bf16)0.f;
-    *reinterpret_cast<bf16x8 *>(&dst[k.row * LDP + k.cp * 8]) = v;
+    for (int e = 0; e < 8; ++e) v[e] = (bf16)(sc * (float)v[e]);
+    put_tile_order(&dst[k.row * LDP], k.cp, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -308,7 +326,7 @@ __device__ __forceinline__ void load_np(State &st, const float *m, const Lane &w
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             st[q][u] = *reinterpret_cast<const f32x4 *>(
-                &m[(64 * q + 16 * w.it + w.l16) * kP + 16 * (2 * w.ph + u) + 4 * w.g]);
+                &m[(64 * q + w.i) * kP + 32 * w.ph + 8 * w.g + 4 * u]);
 }
 __device__ __forceinline__ void store_np(const State &st, float *m, const Lane &w) {
 #pragma unroll
@@ -316,7 +334,7 @@ __device__ __forceinline__ void store_np(const State &st, float *m, const Lane &
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             *reinterpret_cast<f32x4 *>(
-                &m[(64 * q + 16 * w.it + w.l16) * kP + 16 * (2 * w.ph + u) + 4 * w.g]) = st[q][u];
+                &m[(64 * q + w.i) * kP + 32 * w.ph + 8 * w.g + 4 * u]) = st[q][u];
 }
 __device__ __forceinline__ void load_map(State &st, const float *m, const Lane &w) {
 #pragma unroll
@@ -362,77 +380,104 @@ __device__ __forceinline__ SBf load_sbf(const bf16 *m, const Lane &w) {
 // With Sst, the state entering each chunk is stored (and one more after the
 // last: n + 1 stores when n covers all but the segment's last chunk).
 // Returns the sums of cum_e (base 2) and of the lane's psi_e.  Two barriers a
-// chunk; the next chunk's rows and the angles of the one after are in flight
-// while a chunk is worked on.
+// chunk; the next chunk's rows and the prologue values of the one after are in
+// flight while a chunk is worked on.
 // ---------------------------------------------------------------------------
 template <int R> struct SweepLds {
     bf16 rows[kRows * LDN], cols[kRows * LDP];
-    h2 cs[Shp<R>::Q * kNH];
+    h2 cs[Shp<R>::Q * LDC];
     float seg[kNW][kNH];
-    Tok tok[4];
+    Tok tok[3];
 };
 
 template <int R, bool kFwd>
 __device__ __forceinline__ void sweep(const BwdArgs &a, const Slice &s, const Lane &w, SweepLds<R> &L, int64_t c0,
                                       int64_t n, State &st, bf16 *Sst, float *sum_c2, float *sum_psi) {
-    constexpr int Q = Shp<R>::Q;
+    constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
+    constexpr int kDir = kFwd ? 1 : -1;
     const void *rsrc = kFwd ? a.B : a.C, *csrc = kFwd ? a.x : a.dy;
     const RowAt ra = row_at<R>(w);
-    auto chunk = [&](int64_t k) { return kFwd ? c0 + k : c0 - k; };
+    const int64_t ce = c0 + kDir * (n - 1);   // the last chunk
     auto valid = [&](int64_t c) { return (int)min((int64_t)Q, a.L - c * Q); };
+    auto next = [&](int64_t c) { return c == ce ? c : c + kDir; };   // (past the last: loaded unused)
+    Cur u;
+    u.t0 = c0 * Q;
+    u.th = s.tok + (u.t0 + w.wave * TPS) * a.H;
+    u.row = s.tok + (u.t0 + ra.t) * a.H;
     RawTok<R> raw;
+    float ps[TPS];
     Pair pr;
     bf16x8 px;
+    auto fetch = [&](int64_t c) {
+        const int64_t at = u.row + past_end(ra.t, valid(c), Q, a.H);
+        pr = load_pair<R>(ra, rsrc, at);
+        px = load_row<R>(ra, csrc, at);
+        u.row += c == ce ? 0 : kDir * Q * a.H;
+    };
+    auto fetch_tok = [&](int64_t c) {
+        load_tok<R>(a, s, w, u, valid(c), raw);
+        u.th += c == ce ? 0 : kDir * Q * a.H;
+        u.t0 += c == ce ? 0 : kDir * Q;
+    };
+    auto stage = [&](int nv, const Tok &o) {
+        const bool in = ra.t < nv;
+        float c[8], sn[8];
+        cs_getn<8>(&L.cs[ra.t * LDC + ra.cp * 8], c, sn);
+        if (nv < Q) {   // rows past the end are zero
+            const bf16x8 z = {};
+            if (!in) pr.lo = pr.hi = px = z;
+        }
+        put_rot(L.rows, ra, pr, c, sn);
+        put_scaled(L.cols, ra, px, kFwd ? o.v[ra.row] : o.ec[ra.row]);
+    };
     *sum_c2 = 0.f;
     *sum_psi = 0.f;
+    int p0 = 0, p1 = 1, p2 = 2;   // scalar tables of this chunk, the next, the one after
     if (n > 0) {
-        load_tok<R>(a, s, w, chunk(0), valid(chunk(0)), raw);
-        pr = load_pair<R>(a, s, ra, rsrc, chunk(0) * Q, valid(chunk(0)));
-        px = load_row<R>(a, s, ra, csrc, chunk(0) * Q, valid(chunk(0)));
-        tok_scan<R>(a, w, chunk(0), valid(chunk(0)), raw, L.seg, L.tok[0]);
+        const int64_t c1 = next(c0), c2 = next(c1);
+        fetch_tok(c0);
+        fetch(c0);
+        tok_scan<R>(a, w, c0, valid(c0), raw, ps, L.seg, L.tok[p0]);
+        fetch_tok(c1);
+        __syncthreads();
+        tok_table<R>(w, valid(c0), ps, L.seg, L.cs, L.tok[p0]);
+        __syncthreads();
+        stage(valid(c0), L.tok[p0]);
+        fetch(c1);
+        tok_scan<R>(a, w, c1, valid(c1), raw, ps, L.seg, L.tok[p1]);
+        fetch_tok(c2);
         __syncthreads();
     }
-    for (int64_t k = -1; k < n; ++k) {
-        // (a) chunk k's state update; the table of chunk k + 1
-        if (k >= 0) {
-            const Tok &o = L.tok[k & 3];
-            if (Sst) store_sbf(Sst + chunk(k) * kMap, to_bf(st), w);
-            const float psi = o.psie[16 * w.it + w.l16], e = exp2_fast(o.c2e);
-            float sn, cn;
-            sincos_fast(psi, &sn, &cn);
+    int64_t c = c0;
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t c1 = next(c), c2 = next(c1), c3 = next(c2);
+        // (a) this chunk's state update; the next one's table
+        {
+            const Tok &o = L.tok[p0];
+            if (Sst) store_sbf(Sst + c * kMap, to_bf(st), w);
+            const float e = exp2_fast(o.c2e), cn = o.ce[w.i], sn = o.se[w.i];
             *sum_c2 += o.c2e;
-            *sum_psi += psi;
+            *sum_psi += o.psie[w.i];
             if constexpr (!kFwd) rotate(st, cn, -sn);
             scale(st, e);
             add_outer(st, L.rows, L.cols, w);
             if constexpr (kFwd) rotate(st, cn, sn);
         }
-        const int64_t c1 = chunk(k + 1);
-        const bool more = k + 1 < n;
-        const int nv1 = more ? valid(c1) : 0;
-        if (more) {
-            tok_table<R>(w, nv1, raw, L.seg, L.cs, L.tok[(k + 1) & 3]);
-            if (k + 2 < n) load_tok<R>(a, s, w, chunk(k + 2), valid(chunk(k + 2)), raw);
-        }
+        tok_table<R>(w, valid(c1), ps, L.seg, L.cs, L.tok[p1]);
         __syncthreads();
-        // (b) chunk k + 1's rows staged; the scans of chunk k + 2
-        if (more) {
-            const Tok &o = L.tok[(k + 1) & 3];
-            float c[8], sn[8];
-            cs_getn<8>(&L.cs[ra.t * kNH + ra.cp * 8], c, sn);
-            put_rot(L.rows, ra, pr, c, sn, ra.t < nv1);
-            put_row_scaled(L.cols, ra, px, kFwd ? o.v[ra.row] : o.ec[ra.row], ra.t < nv1);
-            if (k + 2 < n) {
-                const int64_t c2 = chunk(k + 2);
-                const int nv2 = valid(c2);
-                pr = load_pair<R>(a, s, ra, rsrc, c2 * Q, nv2);
-                px = load_row<R>(a, s, ra, csrc, c2 * Q, nv2);
-                tok_scan<R>(a, w, c2, nv2, raw, L.seg, L.tok[(k + 2) & 3]);
-            }
-        }
+        // (b) the next chunk's rows; the scans of the one after
+        stage(valid(c1), L.tok[p1]);
+        fetch(c2);
+        tok_scan<R>(a, w, c2, valid(c2), raw, ps, L.seg, L.tok[p2]);
+        fetch_tok(c3);
+        const int p = p0;
+        p0 = p1;
+        p1 = p2;
+        p2 = p;
+        c += kDir;
         __syncthreads();
     }
-    if (Sst) store_sbf(Sst + chunk(n) * kMap, to_bf(st), w);
+    if (Sst) store_sbf(Sst + c * kMap, to_bf(st), w);
 }
 
 __device__ __forceinline__ Slice slice_of(const BwdArgs &a, int64_t bh) {
@@ -464,7 +509,7 @@ __global__ __launch_bounds__(kThr, 4) void k_bwd_aggr(BwdArgs a) {
     const int64_t slot = bh * a.nseg + seg;
     store_map(st, (fwd ? a.Af : a.Ar) + slot * kMap, w);
     float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
-    if (w.ph == 0 && w.g == 0) tot[1 + 16 * w.it + w.l16] = sp;
+    if (w.ph == 0 && w.g == 0) tot[1 + w.i] = sp;
     if (w.tid == 0) tot[0] = sc;
 }
 
@@ -482,9 +527,9 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
     const float *src = fwd ? a.init_state : a.dfinal;
     f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
     if (src) {
-        const float *m = src + bh * kMap + 16 * (2 * w.ph + u) + 4 * w.g;
-        re = *reinterpret_cast<const f32x4 *>(&m[(16 * w.it + w.l16) * kP]);
-        im = *reinterpret_cast<const f32x4 *>(&m[(64 + 16 * w.it + w.l16) * kP]);
+        const float *m = src + bh * kMap + 32 * w.ph + 8 * w.g + 4 * u;
+        re = *reinterpret_cast<const f32x4 *>(&m[w.i * kP]);
+        im = *reinterpret_cast<const f32x4 *>(&m[(64 + w.i) * kP]);
     }
     float *M = fwd ? a.Af : a.Ar;
     const int n = (int)a.nseg - 1;
@@ -498,7 +543,7 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
             const int64_t slot = bh * a.nseg + (fwd ? k : a.nseg - 1 - k);
             const float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
             c2[d] = tot[0];
-            ps[d] = tot[1 + 16 * w.it + w.l16];
+            ps[d] = tot[1 + w.i];
             const float *m = M + slot * kMap + 4 * w.tid;
             mr[d] = *reinterpret_cast<const f32x4 *>(&m[u * 4 * kThr]);
             mi[d] = *reinterpret_cast<const f32x4 *>(&m[(2 + u) * 4 * kThr]);
@@ -509,7 +554,7 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
             const int64_t slot = bh * a.nseg + (fwd ? k0 + d : a.nseg - 1 - (k0 + d));
             const float e = exp2_fast(c2[d]);
             float sn, cn;
-            sincos_fast(ps[d], &sn, &cn);
+            sincos_rev(ps[d], &sn, &cn);
             if (!fwd) sn = -sn;
             f32x4 nr, ni;
 #pragma unroll
@@ -531,15 +576,15 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
 // forward sweep, the chunks last to first.  Wave (J, hf) owns row tile J of
 // the chunk as columns j (dx, dB^) and as rows t (dC^), for the half hf of
 // the columns p and of the rotation pairs.  Every output tile is formed
-// transposed, from operands whose rows are permuted (perm_*), so a lane holds
-// eight consecutive channels of one row: 16-byte stores, the row's weights
-// are per-lane scalars, and the sums over a row are in-lane.
+// transposed, from operands in tile order, so a lane holds eight consecutive
+// channels of one row: 16-byte stores, the row's weights are per-lane scalars,
+// and the sums over a row are in-lane.
 // ---------------------------------------------------------------------------
 template <int R> struct MainLds {
     bf16 B[kRows * LDN], C[kRows * LDN];
     bf16 X[kRows * LDP], Y[kRows * LDP], EY[kRows * LDP];   // x, dy, e^{cum} dy
     bf16 S[kN * LDP], U[kN * LDP];                          // S_{c-1}, U_c  [n][p]
-    h2 cs[2][Shp<R>::Q * kNH];
+    h2 cs[2][Shp<R>::Q * LDC];
     Tok tok[2];
     float seg[kNW][kNH];
     float rc[4][kRows], rg[kRows];     // sums of the mask terms by token row group
@@ -597,49 +642,70 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
     float xdy = 0.f, dAsum = 0.f;
     float pend_dt = 0.f, pend_lam = 0.f, first_dt = 0.f, first_lam = 0.f;   // (wave 0: chunk c + 1's first token)
     RawTok<R> raw;
+    float ps[Shp<R>::TPS];
     float sc_dt = 0.f, sc_lam = 0.f, sc_A = 0.f;   // (wave 0: the current chunk's)
     Pair pB, pC;
     bf16x8 pX, pY;
     SBf sb;
-    auto load_rows = [&](int64_t c) {
+    const int64_t ce = cb + n - 1, QH = Q * a.H;
+    Cur u;
+    u.t0 = ce * Q;
+    u.th = s.tok + (u.t0 + w.wave * Shp<R>::TPS) * a.H;
+    u.row = s.tok + (u.t0 + row_at<R>(w).t) * a.H;
+    int64_t trow = s.tok + (u.t0 + (16 * w.it + w.l16) / R) * a.H;   // the output lane's token
+    bf16 *dump = static_cast<bf16 *>(a.dump) + 8 * w.lane;   // (lanes past the end store here)
+    // loads of chunk c, where the cursors stand; then to chunk c - 1 (kept at
+    // the segment's first)
+    auto fetch = [&](int64_t c) {
         const RowAt ra = row_at<R>(w);
-        const int nv = valid(c);
-        pB = load_pair<R>(a, s, ra, a.B, c * Q, nv);
-        pC = load_pair<R>(a, s, ra, a.C, c * Q, nv);
-        pX = load_row<R>(a, s, ra, a.x, c * Q, nv);
-        pY = load_row<R>(a, s, ra, a.dy, c * Q, nv);
+        const int64_t at = u.row + past_end(ra.t, valid(c), Q, a.H);
+        pB = load_pair<R>(ra, a.B, at);
+        pC = load_pair<R>(ra, a.C, at);
+        pX = load_row<R>(ra, a.x, at);
+        pY = load_row<R>(ra, a.dy, at);
+        u.row -= c == cb ? 0 : QH;
+    };
+    auto fetch_tok = [&](int64_t c) {
+        load_tok<R>(a, s, w, u, valid(c), raw);
+        u.th -= c == cb ? 0 : QH;
+        u.t0 -= c == cb ? 0 : Q;
     };
     auto stage = [&](int nv, const h2 *cs, const Tok &o) {
         const RowAt ra = row_at<R>(w);
-        const bool in = ra.t < nv;
         float c[8], sn[8];
-        cs_getn<8>(&cs[ra.t * kNH + ra.cp * 8], c, sn);
-        put_rot(M.B, ra, pB, c, sn, in);
-        put_rot(M.C, ra, pC, c, sn, in);
-        put_row(M.X, ra, pX, in);
-        put_row(M.Y, ra, pY, in);
-        put_row_scaled(M.EY, ra, pY, o.ec[ra.row], in);
+        cs_getn<8>(&cs[ra.t * LDC + ra.cp * 8], c, sn);
+        if (nv < Q) {   // rows past the end are zero
+            const bf16x8 z = {};
+            if (ra.t >= nv) pB.lo = pB.hi = pC.lo = pC.hi = pX = pY = z;
+        }
+        put_rot(M.B, ra, pB, c, sn);
+        put_rot(M.C, ra, pC, c, sn);
+        put_tile_order(&M.X[ra.row * LDP], ra.cp, pX);
+        put_tile_order(&M.Y[ra.row * LDP], ra.cp, pY);
+        put_scaled(M.EY, ra, pY, o.ec[ra.row]);
     };
-    const int64_t ce = cb + n - 1;
     if (n > 0) {
         const int nv = valid(ce);
-        load_tok<R>(a, s, w, ce, nv, raw);
-        load_rows(ce);
+        const int64_t c1 = max(ce - 1, cb);
+        fetch_tok(ce);
+        fetch(ce);
         sb = load_sbf(Sst + ce * kMap, w);
         __syncthreads();   // (the sweep's LDS)
-        tok_scan<R>(a, w, ce, nv, raw, M.seg, M.tok[0]);
-        __syncthreads();
-        tok_table<R>(w, nv, raw, M.seg, M.cs[0], M.tok[0]);
+        tok_scan<R>(a, w, ce, nv, raw, ps, M.seg, M.tok[0]);
         sc_dt = raw.dt; sc_lam = raw.lam; sc_A = raw.A;
-        if (n > 1) load_tok<R>(a, s, w, ce - 1, valid(ce - 1), raw);
+        fetch_tok(c1);
+        __syncthreads();
+        tok_table<R>(w, nv, ps, M.seg, M.cs[0], M.tok[0]);
         __syncthreads();
         stage(nv, M.cs[0], M.tok[0]);
-        if (n > 1) load_rows(ce - 1);
+        fetch(c1);
         __syncthreads();
     }
     for (int64_t k = 0; k < n; ++k) {
         const int64_t c = ce - k, t0 = c * Q;
         const int nvalid = valid(c), par = (int)(k & 1);
+        const int64_t c1 = max(c - 1, cb), c2 = max(c - 2, cb);   // (below the first: loaded unused)
+        const int nv1 = valid(c1);
         const bool more = k + 1 < n;
         const Tok &o = M.tok[par];
         const h2 *cs = M.cs[par];
@@ -653,9 +719,7 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 
         // ======== region 0: state step, masked scores ========
         {
-            const float psi = o.psie[16 * w.it + w.l16], e = exp2_fast(o.c2e);
-            float sn, cn;
-            sincos_fast(psi, &sn, &cn);
+            const float e = exp2_fast(o.c2e), cn = o.ce[w.i], sn = o.se[w.i];
             float dps = 0.f, dcm = 0.f;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -682,9 +746,9 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 *reinterpret_cast<bf16x4 *>(&M.S[at]) = sr4;
                 *reinterpret_cast<bf16x4 *>(&M.S[at + 64 * LDP]) = si4;
             }
-            if (more) sb = load_sbf(Sst + (c - 1) * kMap, w);
+            sb = load_sbf(Sst + c1 * kMap, w);
             dps = sum_g(dps);
-            if (w.g == 0) M.dps[w.ph][16 * w.it + w.l16] = dps;
+            if (w.g == 0) M.dps[w.ph][w.i] = dps;
             dcm = sum_wave(e * dcm);
             if (w.lane == 0) M.dcm[w.wave] = dcm;
             add_outer(G, M.C, M.EY, w);
@@ -716,11 +780,12 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                         for (int kk = 0; kk < 2; ++kk)
                             dg = MM::mma(MM::load(&M.Y[(16 * T + w.l16) * LDP + kk * 32 + 8 * w.g]), fX[kk], dg);
+                        const f32x4 c4 = *reinterpret_cast<const f32x4 *>(&o.c2[16 * T + 4 * w.g]);
 #pragma unroll
                         for (int q = 0; q < TT; ++q) {
                             const int r0 = 16 * T + 4 * w.g + q * R, tt = r0 / R;   // a token's rows
                             const bool off = tl < tt, on = tl == tt;
-                            const float ex = off ? exp2_fast(o.c2[r0] - c2j) : 0.f;
+                            const float ex = off ? exp2_fast(c4[q * R] - c2j) : 0.f;
                             const float wt = off ? ex * sgj : on ? gmj : 0.f;
                             float dW = 0.f;   // dJ/dw summed over the token's rows
 #pragma unroll
@@ -772,10 +837,13 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                         for (int kk = 0; kk < 2; ++kk)
                             gT = MM::mma(MM::load(&M.X[(16 * Jt + w.l16) * LDP + kk * 32 + 8 * w.g]), fY[kk], gT);
+                        const f32x4 c4 = *reinterpret_cast<const f32x4 *>(&o.c2[16 * Jt + 4 * w.g]);
+                        const f32x4 s4 = *reinterpret_cast<const f32x4 *>(&o.sig[16 * Jt + 4 * w.g]);
 #pragma unroll
                         for (int q = 0; q < TT; ++q) {
-                            const int r0 = 16 * Jt + 4 * w.g + q * R, tj = r0 / R;
-                            const float wt = tj < tl ? exp2_fast(c2t - o.c2[r0]) * o.sig[r0] : tj == tl ? gmt : 0.f;
+                            const int tj = (16 * Jt + 4 * w.g) / R + q;
+                            float wt = tj < tl ? exp2_fast(c2t - c4[q * R]) * s4[q * R] : 0.f;
+                            wt = tj == tl ? gmt : wt;
 #pragma unroll
                             for (int r = 0; r < R; ++r) gT[q * R + r] *= wt;
                         }
@@ -784,13 +852,22 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                     for (int v = 0; v < 4; ++v) wT[jp][4 * h + v] = (bf16)gT[v];
                 }
         }
-        if (more) tok_scan<R>(a, w, c - 1, valid(c - 1), raw, M.seg, M.tok[par ^ 1]);
+        tok_scan<R>(a, w, c1, nv1, raw, ps, M.seg, M.tok[par ^ 1]);
+        const float nx_dt = raw.dt, nx_lam = raw.lam, nx_A = raw.A;
+        fetch_tok(c2);
         __syncthreads();
 
         // ======== region 1: the chunk's gradients ========
         const float vj = o.v[row], ec = o.ec[row];
-        const int64_t trow = s.tok + (t0 + tl) * a.H;   // (this lane's token; stored when tl < nvalid)
         const int rk = row % R;
+        // (every lane stores, so that a wait for the loads before never waits for these stores)
+        bf16 *gx = static_cast<bf16 *>(a.dx) + (trow * R + rk) * kP + 32 * hf + 8 * w.g;
+        bf16 *gB = static_cast<bf16 *>(a.dB) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
+        bf16 *gC = static_cast<bf16 *>(a.dC) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
+        if (nvalid < Q) {
+            asm volatile("");
+            if (tl >= nvalid) gx = gB = gC = dump;
+        }
         {
             // dx: columns 32 hf + 8 g + e
             f32x4 d[2], bu[2];
@@ -799,13 +876,13 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 d[ab] = bu[ab] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kp = 0; kp < 2; ++kp)
-                    if (2 * kp + 1 >= J) d[ab] = MM::mma(perm_kt2(M.Y, LDP, 32 * kp, 32 * hf, ab, w.g, w.l16), wG[kp], d[ab]);
+                    if (2 * kp + 1 >= J) d[ab] = MM::mma(load_kt2(M.Y, LDP, 32 * kp, 32 * hf + 16 * ab, w.g, w.l16), wG[kp], d[ab]);
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk)
-                    bu[ab] = MM::mma(perm_kt(M.U, LDP, 32 * kk, 32 * hf, ab, w.g, w.l16), fB[kk], bu[ab]);
+                    bu[ab] = MM::mma(load_kt(M.U, LDP, 32 * kk, 32 * hf + 16 * ab, w.g, w.l16), fB[kk], bu[ab]);
             }
-            const bf16x8 xv = MM::load(&M.X[row * LDP + 32 * hf + 8 * w.g]);
-            const bf16x8 yv = MM::load(&M.Y[row * LDP + 32 * hf + 8 * w.g]);
+            const bf16x8 xv = get_tile_order(&M.X[row * LDP], 4 * hf + w.g);
+            const bf16x8 yv = get_tile_order(&M.Y[row * LDP], 4 * hf + w.g);
             float dvp = 0.f;
             bf16x8 out;
 #pragma unroll
@@ -815,13 +892,12 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 xdy += xe * ye;
                 out[e] = (bf16)(d[e / 4][e % 4] + vj * be + Dh * ye);
             }
-            if (tl < nvalid)
-                *reinterpret_cast<bf16x8 *>(static_cast<bf16 *>(a.dx) + (trow * R + rk) * kP + 32 * hf + 8 * w.g) = out;
+            *reinterpret_cast<bf16x8 *>(gx) = out;
             dvp = sum_g(dvp);
             if (w.g == 0) M.dv[hf][row] = dvp;
         }
         float cn[8], sn[8], dpsi[8];
-        cs_getn<8>(&cs[tl * kNH + 32 * hf + 8 * w.g], cn, sn);
+        cs_getn<8>(&cs[tl * LDC + 32 * hf + 8 * w.g], cn, sn);
         {
             // dB: pairs i = 32 hf + 8 g + e
             f32x4 d[2][2], xu[2][2];
@@ -833,13 +909,13 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                     for (int kp = 0; kp < 2; ++kp)
                         if (2 * kp + 1 >= J)
-                            d[q][ab] = MM::mma(perm_kt2(M.C, LDN, 32 * kp, 64 * q + 32 * hf, ab, w.g, w.l16), wD[kp], d[q][ab]);
+                            d[q][ab] = MM::mma(load_kt2(M.C, LDN, 32 * kp, 64 * q + 32 * hf + 16 * ab, w.g, w.l16), wD[kp], d[q][ab]);
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk)
-                        xu[q][ab] = MM::mma(perm_rows(M.U, LDP, 64 * q + 32 * hf, 32 * kk, ab, w.g, w.l16), fX[kk], xu[q][ab]);
+                        xu[q][ab] = MM::mma(MM::load(&M.U[(64 * q + 32 * hf + 16 * ab + w.l16) * LDP + 32 * kk + 8 * w.g]), fX[kk], xu[q][ab]);
                 }
-            const bf16x8 br = MM::load(&M.B[row * LDN + 32 * hf + 8 * w.g]);
-            const bf16x8 bi = MM::load(&M.B[row * LDN + 64 + 32 * hf + 8 * w.g]);
+            const bf16x8 br = get_tile_order(&M.B[row * LDN], 4 * hf + w.g);
+            const bf16x8 bi = get_tile_order(&M.B[row * LDN + kNH], 4 * hf + w.g);
             bf16x8 o0, o1;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -849,11 +925,8 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 o0[e] = (bf16)(cn[e] * re - sn[e] * im);
                 o1[e] = (bf16)(sn[e] * re + cn[e] * im);
             }
-            if (tl < nvalid) {
-                bf16 *p = static_cast<bf16 *>(a.dB) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
-                *reinterpret_cast<bf16x8 *>(p) = o0;
-                *reinterpret_cast<bf16x8 *>(p + kNH) = o1;
-            }
+            *reinterpret_cast<bf16x8 *>(gB) = o0;
+            *reinterpret_cast<bf16x8 *>(gB + kNH) = o1;
         }
         {
             // dC
@@ -866,13 +939,13 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 #pragma unroll
                     for (int jp = 0; jp < 2; ++jp)
                         if (2 * jp <= J)
-                            d[q][ab] = MM::mma(perm_kt2(M.B, LDN, 32 * jp, 64 * q + 32 * hf, ab, w.g, w.l16), wT[jp], d[q][ab]);
+                            d[q][ab] = MM::mma(load_kt2(M.B, LDN, 32 * jp, 64 * q + 32 * hf + 16 * ab, w.g, w.l16), wT[jp], d[q][ab]);
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk)
-                        t2[q][ab] = MM::mma(perm_rows(M.S, LDP, 64 * q + 32 * hf, 32 * kk, ab, w.g, w.l16), fY[kk], t2[q][ab]);
+                        t2[q][ab] = MM::mma(MM::load(&M.S[(64 * q + 32 * hf + 16 * ab + w.l16) * LDP + 32 * kk + 8 * w.g]), fY[kk], t2[q][ab]);
                 }
-            const bf16x8 cr = MM::load(&M.C[row * LDN + 32 * hf + 8 * w.g]);
-            const bf16x8 ci = MM::load(&M.C[row * LDN + 64 + 32 * hf + 8 * w.g]);
+            const bf16x8 cr = get_tile_order(&M.C[row * LDN], 4 * hf + w.g);
+            const bf16x8 ci = get_tile_order(&M.C[row * LDN + kNH], 4 * hf + w.g);
             float dcy = 0.f;
             bf16x8 o0, o1;
 #pragma unroll
@@ -884,11 +957,8 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 o0[e] = (bf16)(cn[e] * re - sn[e] * im);
                 o1[e] = (bf16)(sn[e] * re + cn[e] * im);
             }
-            if (tl < nvalid) {
-                bf16 *p = static_cast<bf16 *>(a.dC) + (trow * R + rk) * kN + 32 * hf + 8 * w.g;
-                *reinterpret_cast<bf16x8 *>(p) = o0;
-                *reinterpret_cast<bf16x8 *>(p + kNH) = o1;
-            }
+            *reinterpret_cast<bf16x8 *>(gC) = o0;
+            *reinterpret_cast<bf16x8 *>(gC + kNH) = o1;
             dcy = sum_g(dcy);
             if (w.g == 0) M.dcy[hf][row] = ec * dcy;
         }
@@ -901,19 +971,12 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                 *reinterpret_cast<f32x4 *>(&M.dth[J][32 * hf + 8 * w.g + e]) =
                     f32x4{dpsi[e], dpsi[e + 1], dpsi[e + 2], dpsi[e + 3]};
         }
-        float nx_dt = 0.f, nx_lam = 0.f, nx_A = 0.f;
-        if (more) {
-            tok_table<R>(w, valid(c - 1), raw, M.seg, M.cs[par ^ 1], M.tok[par ^ 1]);
-            nx_dt = raw.dt; nx_lam = raw.lam; nx_A = raw.A;
-            if (k + 2 < n) load_tok<R>(a, s, w, c - 2, valid(c - 2), raw);
-        }
+        tok_table<R>(w, nv1, ps, M.seg, M.cs[par ^ 1], M.tok[par ^ 1]);
         __syncthreads();
 
         // ======== region 2: next rows, dtheta, per-token scalars ========
-        if (more) {
-            stage(valid(c - 1), M.cs[par ^ 1], M.tok[par ^ 1]);
-            if (k + 2 < n) load_rows(c - 2);
-        }
+        stage(nv1, M.cs[par ^ 1], M.tok[par ^ 1]);
+        fetch(c2);
         if (w.l16 % R == 0 && tl < nvalid) {
             // (dps: the state's rotation by psi_e, which every token's angle enters)
 #pragma unroll
@@ -984,6 +1047,7 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
             sc_lam = nx_lam;
             sc_A = nx_A;
         }
+        trow -= QH;
         __syncthreads();
     }
     if (seg == 0 && a.dinit) store_np(G, a.dinit + bh * kMap, w);
@@ -1041,6 +1105,9 @@ __global__ __launch_bounds__(kThrF) void k_bwd_finish(BwdArgs a, int Q) {
         if (!a.dA_per_token) a.dA[h] = s_a[0];
     }
 }
+
+// Store target of the lanes past the end: 16 bytes a lane, twice kNH apart.
+constexpr size_t kDumpBytes = 2 * kNH + 16 * kWave;
 
 // Most segments a slice may be split into: the workspace holds their maps, so
 // the bound does not depend on the device.
@@ -1105,7 +1172,8 @@ BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, 
     w.off_Ar = up(w.off_Af + segs * np * sizeof(float));
     w.off_Sst = up(w.off_Ar + segs * np * sizeof(float));
     w.off_tot = up(w.off_Sst + (size_t)BH * (size_t)nchunks * np * 2);
-    w.off_dsig = up(w.off_tot + segs * 2 * (size_t)(1 + N / 2) * sizeof(float));
+    w.off_dump = up(w.off_tot + segs * 2 * (size_t)(1 + N / 2) * sizeof(float));
+    w.off_dsig = up(w.off_dump + kDumpBytes);
     w.off_dA = up(w.off_dsig + segs * sizeof(float));
     w.off_dD = up(w.off_dA + segs * sizeof(float));
     // (at least the documented three fp32 maps a chunk)

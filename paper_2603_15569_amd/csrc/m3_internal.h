@@ -96,6 +96,7 @@ struct BwdArgs {
     float *Ar;      // per segment: its reverse gradient map, then the gradient of the state entering it
     void *Sst;      // per chunk: the state entering it, bf16 in thread order (an MFMA operand; the decay term)
     float *tot;     // per segment and direction: [1 + N/2] sums of cum_e (base 2) and psi_e
+    void *dump;     // store target of lanes past the end (never read)
     float *dsig;    // per segment: dJ/dsigma of its last token
     float *dApart;  // per segment: sum of dt dJ/d(dt A)
     float *dDpart;  // per segment: sum of <x, dy>
@@ -107,7 +108,7 @@ typedef hipError_t (*bwd_launch_fn)(const BwdArgs &, hipStream_t);
 // backward kernels for the shape (null: none built)
 bwd_launch_fn find_bwd_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
 struct BwdWorkspaceLayout {
-    size_t off_Af, off_Ar, off_Sst, off_tot, off_dsig, off_dA, off_dD, total;
+    size_t off_Af, off_Ar, off_Sst, off_tot, off_dump, off_dsig, off_dA, off_dD, total;
 };
 BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, int64_t P);
 

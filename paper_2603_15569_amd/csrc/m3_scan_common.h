@@ -230,25 +230,6 @@ __device__ __forceinline__ bf16x8 load_kt2(const bf16 *M, int ld, int r0, int c0
     return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
 }
 
-// MFMA operand with its rows (the output's rows) taken from 32 columns of a
-// row-major LDS block so that a lane of the output tiles ab = 0 and 1 holds
-// the columns c0 + 8 g + 4 ab + v: eight consecutive ones.  K elements: rows
-// r0 + 8 g .. + 7 (kt), or rows r0 + 4 g .. + 3 and r0 + 16 + 4 g .. + 3
-// (kt2: the order in which two 16-row accumulator tiles hold them).
-__device__ __forceinline__ bf16x8 perm_kt(const bf16 *M, int ld, int r0, int c0, int ab, int g, int l16) {
-    const bf16 *p = M + (r0 + 8 * g + l16 / 4) * ld + c0 + 8 * (l16 % 4) + 4 * ab;
-    return cat4(lds_tr4(p), lds_tr4(p + 4 * ld));
-}
-__device__ __forceinline__ bf16x8 perm_kt2(const bf16 *M, int ld, int r0, int c0, int ab, int g, int l16) {
-    const bf16 *p = M + (r0 + 4 * g + l16 / 4) * ld + c0 + 8 * (l16 % 4) + 4 * ab;
-    return cat4(lds_tr4(p), lds_tr4(p + 16 * ld));
-}
-// The same with rows r0 .. r0 + 31 of the block as the operand's rows, K
-// along the columns.
-__device__ __forceinline__ bf16x8 perm_rows(const bf16 *M, int ld, int r0, int k0, int ab, int g, int l16) {
-    return Mma<bf16>::load(&M[(r0 + 8 * (l16 / 4) + 4 * ab + l16 % 4) * ld + k0 + 8 * g]);
-}
-
 // Four consecutive output columns of one row, held by one lane of a
 // transposed MFMA tile (the lane's four accumulator rows are y columns).
 __device__ __forceinline__ void store4(bf16 *dst, const f32x4 &v) {
@@ -323,7 +304,11 @@ struct FShape {
     static constexpr int TPW = RT / NWO;                  // row tiles per output wave
     static constexpr int PTW = 16 / NW;                   // state pair-tiles per wave
     static constexpr int JB = 64, NJB = QR / JB;          // staged row blocks
-    static constexpr int PAD = 16 / (int)sizeof(T);
+    // Row padding of the LDS tiles.  bf16: 32 bytes, so that the 16 rows of an
+    // MFMA operand read start 32 bytes apart modulo the banks (a 16-byte read
+    // of 16 rows takes 3.4 cycles of the LDS against 6.0 with 16 bytes of
+    // padding, the transposing one 2.9-3.6 against 3.6).
+    static constexpr int PAD = sizeof(T) == 2 ? 16 : 4;
     static constexpr int LDN = N + PAD;                   // [rows][N] and [P][N] tiles
     static constexpr int LDJ = JB + PAD;                  // [N or P][rows] tiles
     static constexpr int NSEG = NTHR / NH;                // angle-scan segments

@@ -98,6 +98,7 @@ void k_scan_fused(ScanArgs a) {
     // W x [row][p]; MFMA operands whose K axis runs along the rows (B^T and
     // (W x)^T for M, x^T for y) are read with the LDS transposing reads.
     constexpr int LDP = P + S::PAD;
+    constexpr int LDY = P + 16 / (int)sizeof(T);   // y staging (8-byte writes down 16 rows)
     constexpr int kSB = S::JB * S::LDN, kSXr = S::JB * LDP;
     __shared__ __attribute__((aligned(16))) T s_B[NBUF * kSB];        // B^ blocks [row][n]
     __shared__ __attribute__((aligned(16))) T s_XW[2 * NBUF * kSXr];  // x blocks, then W x blocks [row][p]
@@ -1093,19 +1094,19 @@ void k_scan_fused(ScanArgs a) {
     // execute in order: no further barrier) and writes whole 16-byte pieces
     // of the y rows
     __syncthreads();
-    T *s_y = s_XW + wave * (16 * LDP);
+    T *s_y = s_XW + wave * (16 * LDY);
     T *Yg = static_cast<T *>(a.y) + tok0 * (R * P);
 #pragma unroll
     for (int m = 0; m < TPW; ++m) {
         const int TT = owned_tile<S>(wave, m);
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt) store4(&s_y[l16 * LDP + pt * 16 + 4 * g], acc[m][pt]);
+        for (int pt = 0; pt < PT; ++pt) store4(&s_y[l16 * LDY + pt * 16 + 4 * g], acc[m][pt]);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int i = 0; i < NPC; ++i) {
             const int k = lane + i * kWave, rl = k / RP, col = (k % RP) * S::CE;
             const int row = TT * 16 + rl, t = row / R, r = row % R;
-            V16 yv = *reinterpret_cast<const V16 *>(&s_y[rl * LDP + col]);
+            V16 yv = *reinterpret_cast<const V16 *>(&s_y[rl * LDY + col]);
             if constexpr (kPro) {
                 // gate factor SiLU(W_Z o Z') in fp32, then (optionally) the
                 // output norm: the group's pieces sit in consecutive lanes

@@ -93,6 +93,7 @@ void k_scan_seg(ScanArgs a) {
     // W x [row][p].  MFMA operands whose K axis runs along the rows (x^T for
     // y, B^T and (W x)^T for M) are read with the LDS transposing reads.
     constexpr int LDP = P + S::PAD;
+    constexpr int LDY = P + 16 / (int)sizeof(T);   // y staging (8-byte writes down 16 rows)
     constexpr int kSB = S::JB * S::LDN, kSXr = S::JB * LDP;
     __shared__ __attribute__((aligned(16))) T s_B[NBUF * kSB];        // B^ blocks [row][n]; S^T [p][n]
     __shared__ __attribute__((aligned(16))) T s_XW[2 * NBUF * kSXr];  // x blocks, then W x blocks [row][p]
@@ -946,21 +947,21 @@ void k_scan_seg(ScanArgs a) {
         // buffers, free after the last block's barrier (a wave's LDS accesses
         // execute in order: no barrier), and writes whole 16-byte pieces of
         // its columns of the y rows
-        T *s_y = s_XW + wave * (16 * LDP);
+        T *s_y = s_XW + wave * (16 * LDY);
         T *Yg = static_cast<T *>(a.y) + tk * (R * P);
 #pragma unroll
         for (int m = 0; m < TPW; ++m) {
             if (!ow) break;
             const int TT = owned_tile<S>(wt, m);
 #pragma unroll
-            for (int pt = 0; pt < PTS; ++pt) store4(&s_y[l16 * LDP + pt * 16 + 4 * g], acc[m][pt]);
+            for (int pt = 0; pt < PTS; ++pt) store4(&s_y[l16 * LDY + pt * 16 + 4 * g], acc[m][pt]);
             asm volatile("" ::: "memory");
 #pragma unroll
             for (int i = 0; i < NPC; ++i) {
                 const int k = lane + i * kWave, rl = k / RP, col = (k % RP) * S::CE;
                 const int row = TT * 16 + rl, t = row / R, r = row % R;
                 if (k < 16 * RP && t < nv) {
-                    V16 yv = *reinterpret_cast<const V16 *>(&s_y[rl * LDP + col]);
+                    V16 yv = *reinterpret_cast<const V16 *>(&s_y[rl * LDY + col]);
                     if constexpr (kGate) yv = gate_piece<T>(yv, zp[m][i]);
                     *reinterpret_cast<V16 *>(Yg + t * xstr + r * P + pofs * 16 + col) = yv;
                 }

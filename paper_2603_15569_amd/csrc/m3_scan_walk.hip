@@ -53,7 +53,7 @@ template <int N_, int R_> struct Walk {
     static constexpr int NIT = N / 32;           // 16-row tiles of rotation pairs
     static constexpr int U = NIT * (kP / 16) / NW;   // (pair tile, column tile) units a wave
     static constexpr int KC = N / 32;            // K steps along the state
-    static constexpr int LDN = N + 8, LDP = kP + 8, LDC = NH + 4;   // padded LDS rows
+    static constexpr int LDN = N + 16, LDP = kP + 16, LDC = NH + 4;   // padded LDS rows
     static constexpr int BT = kRows * NH / 8;    // tasks of the B rows (a piece pair each)
     static constexpr int XT = kRows * kP / 8 / NTHR;   // x pieces a thread
     static constexpr int kMap = N * kP;

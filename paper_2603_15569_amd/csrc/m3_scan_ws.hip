@@ -49,8 +49,9 @@ struct WsShape {
     static constexpr int NST = NSW * kWave;            // state threads
     static constexpr int TPW = RT / NWO;               // row tiles per output wave
     static constexpr int JB = 64, NJB = QR / JB;       // staged row blocks
-    static constexpr int PAD = 8;                      // bf16 elements (16 bytes)
+    static constexpr int PAD = 16;                     // bf16 elements (32 bytes: FShape::PAD)
     static constexpr int LDN = N + PAD, LDP = P + PAD;
+    static constexpr int LDY = P + 8;                  // y staging (8-byte writes down 16 rows)
     static constexpr int CE = 8;                       // bf16 per 16-byte vector
     static constexpr int PPW = NH / NSW;               // angle pairs per state wave
     static_assert(Q == kWave, "prologue: one token per lane");
@@ -90,7 +91,7 @@ void k_scan_ws(ScanArgs a) {
     // State entering the chunk, transposed [p][n], in bf16 (operand of y).
     __shared__ __attribute__((aligned(16))) T s_S[P * LDN];
     // y staging, one 16-row tile per output wave.
-    __shared__ __attribute__((aligned(16))) T s_Y[S::NWO][16 * LDP];
+    __shared__ __attribute__((aligned(16))) T s_Y[S::NWO][16 * S::LDY];
     // Block prologue tables of the head (fp32): B gain and bias as 16-byte
     // entries at bgb(r, i) (gain and bias of element i, then of element
     // i + N/2, of rank row r: one read serves a rotation pair; ordered so that
@@ -394,7 +395,7 @@ void k_scan_ws(ScanArgs a) {
 #pragma unroll
                     for (int m = 0; m < TPW; ++m) {
 #pragma unroll
-                        for (int pt = 0; pt < PT; ++pt) store4(&sy[l16 * LDP + pt * 16 + 4 * g], acc[m][pt]);
+                        for (int pt = 0; pt < PT; ++pt) store4(&sy[l16 * S::LDY + pt * 16 + 4 * g], acc[m][pt]);
                         asm volatile("" ::: "memory");
 #pragma unroll
                         for (int i = 0; i < NPC; ++i) {
@@ -406,7 +407,7 @@ void k_scan_ws(ScanArgs a) {
                                 // pieces are RP consecutive lanes, so a group's
                                 // sum of squares is a lane sum (all lanes take
                                 // part; rows past the end are not stored)
-                                V16 yv = *reinterpret_cast<const V16 *>(&sy[rl * LDP + col]);
+                                V16 yv = *reinterpret_cast<const V16 *>(&sy[rl * S::LDY + col]);
                                 float yf[CE], gz[CE], wz[CE];
                                 if constexpr (kGate) tab(kPWZ + r * P + col, wz, CE);
 #pragma unroll
@@ -445,7 +446,7 @@ void k_scan_ws(ScanArgs a) {
                                 for (int e = 0; e < CE; ++e) fset(yv, e, yf[e]);
                                 if (t < nv) *reinterpret_cast<V16 *>(Yg + t * xstr + r * P + col) = yv;
                             } else if (t < nv) {
-                                V16 yv = *reinterpret_cast<const V16 *>(&sy[rl * LDP + col]);
+                                V16 yv = *reinterpret_cast<const V16 *>(&sy[rl * S::LDY + col]);
                                 if constexpr (kGate) yv = gate_piece<T>(yv, zp[m][i]);
                                 *reinterpret_cast<V16 *>(Yg + t * xstr + r * P + col) = yv;
                             }
