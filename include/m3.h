@@ -90,17 +90,17 @@ typedef enum {
 typedef enum { M3_F32 = 0, M3_BF16 = 1 } m3_dtype;
 
 /* m3_dims.flags select the prefill kernels (same results up to rounding).
- * Default (0), wherever built (dstate 128, headdim 64): the segmented
- * single-pass kernel: each workgroup scans a segment of consecutive chunks of
- * one (batch, head) slice and carries the state across them; segments of a
- * slice are linked by a decoupled look-back over their state maps.  When
- * seg_chunks is 0 and several segments per slice would be needed, the
- * one-chunk-per-workgroup kernel runs instead for chunks of fewer than 128
- * rows (chunk * rank), and for chunks of 64 or more tokens when the scan has
- * at least 16384 chunks in all (batch * nheads * chunks per slice): it is
- * faster there.  When a slice is one segment and io is bf16
- * with rank 4 and chunk 64, a warp-specialised variant runs (half of its
- * waves form the outputs, half stage the inputs and carry the state).
+ * Default (0), wherever built (dstate 128, headdim 64): one of the single-pass
+ * kernels.  One chunk per workgroup, with a decoupled look-back across every
+ * chunk; or segmented: each workgroup scans a segment of consecutive chunks of
+ * one (batch, head) slice and carries the state across them, the segments of
+ * a slice linked by a look-back over their state maps (a segment per slice:
+ * no look-back; then with rank 4 a warp-specialised variant, half of whose
+ * waves form the outputs while half stage the inputs and carry the state).
+ * With seg_chunks 0, bf16 scans run whichever is estimated to be fastest for
+ * the batch, and may run on a longer chunk than dims->chunk (the results do
+ * not depend on it).  seg_chunks > 0 asks for the segmented kernel on
+ * dims->chunk.
  * bf16 states of 64 and 32: each workgroup walks a segment of a slice's chunks
  * with the state in registers, after a pass over the segments' maps when a
  * slice needs several; every flag selects it, and its own chunk is 64 rows.
@@ -109,8 +109,8 @@ typedef enum { M3_F32 = 0, M3_BF16 = 1 } m3_dtype;
  * the single-pass kernels' 32-bit row offsets allow (nheads * rank *
  * max(dstate, headdim) elements of at least 16 MiB, or a chunk of such
  * tokens of at least 2 GiB).
- * M3_SCAN_PER_CHUNK: the single-pass kernel with one chunk per workgroup
- * (a look-back across every chunk).  Ignored together with M3_SCAN_SPLIT.
+ * M3_SCAN_PER_CHUNK: the single-pass kernel with one chunk (of dims->chunk
+ * tokens) per workgroup.  Ignored together with M3_SCAN_SPLIT.
  * M3_THETA_PER_HEAD (m3_scan_fwd and m3_step, gated or not): theta / theta_t
  * are the per-head frequencies omega [nheads][dstate/2] and every angle is
  * dt * omega (Sec. 3.2: the rotation angle is Delta_t times theta, here with
@@ -127,12 +127,13 @@ typedef struct {
     int64_t headdim;   /* P                                                  */
     int64_t dstate;    /* N, even                                            */
     int64_t rank;      /* R >= 1 (MIMO rank)                                 */
-    int64_t chunk;     /* Q: tokens per chunk of the prefill scan            */
+    int64_t chunk;     /* Q: tokens per chunk of the prefill scan (at least, by
+                          default: above)                                  */
     int32_t io;        /* m3_dtype of x, B, C, y and the carry               */
     int32_t flags;     /* M3_SCAN_* bits; other bits must be 0               */
     int64_t a_stride_b, a_stride_t, a_stride_h; /* strides of A, in floats   */
     int64_t seg_chunks; /* chunks per workgroup of the segmented kernel; 0 =
-                           enough that all workgroups are resident at once
+                           the library's choice of kernel, segments and chunk
                            (results then depend on the device's CU count in
                            the last bits); ignored by m3_step              */
 } m3_dims;
@@ -345,10 +346,9 @@ typedef struct {
  * prologue `pro` (not NULL) applied to B, C, x and z as they are read.  x
  * (and z with w_z) is [batch][seqlen][nheads][headdim] when w_x (w_z) is
  * given, else as in m3_scan_fwd.  Runs the one-chunk-per-workgroup
- * single-pass kernel, except where the default choice (flags without
- * M3_SCAN_PER_CHUNK, seg_chunks as for m3_scan_fwd) gives one segment per
- * slice at rank 4 and chunk 64: then the warp-specialised kernel runs with
- * the prologue (the workspace is sized by m3_scan_workspace_bytes(dims) as
+ * single-pass kernel, except where the choice (by default, or a seg_chunks of
+ * at least the chunk count) is one segment per slice at rank 4 and 64-token
+ * chunks: then the warp-specialised kernel runs with the prologue (the workspace is sized by m3_scan_workspace_bytes(dims) as
  * usual).  Supported shapes: io bf16,
  * dstate 128, headdim 64, rank 1/2/4 and chunk 32/64/128 with chunk*rank a
  * multiple of 64 and at most 512 (else M3_ERR_UNSUPPORTED, also with

@@ -4,10 +4,12 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <vector>
 
 #include "m3.h"
 #include "m3_internal.h"
+#include "m3_scan_common.h"
 
 namespace m3 {
 
@@ -149,6 +151,79 @@ extern "C" size_t m3_scan_workspace_bytes(const m3_dims *d) {
         .total;
 }
 
+// ---------------------------------------------------------------------------
+// Kernel choice of the default bf16 scan (no M3_SCAN_* flag, seg_chunks 0).
+// The result does not depend on the chunk, so a scan may run on a longer chunk
+// than the caller's (never a shorter one: the workspace is sized for the
+// caller's, and holds what a longer one needs).  The estimates below are
+// fitted to MI355X times at N = 128, P = 64 over 1 to 512 slices and 1 to 256
+// chunks a slice, within about 10%:
+//   per chunk   the larger of all items at `item` each and a slice's chain of
+//               chunks at kLink a link, and `base`, one item's lifetime
+//   one segment `single` a chunk, once per batch of resident slices
+//   segments    `two` a chunk (two passes over each), a link per segment
+// Longer chunks have fewer links and maps but grow the quadratic part: B=1
+// L=2048 H=16 rank 1, chunk 64: 49 us per chunk of 64, 35 of 128; B=4 L=2048
+// H=16 rank 2, chunk 32: 156, 133 and 99 us of 32, 64 and 128 tokens; B=1
+// L=16384 H=8 rank 1, chunk 64: 305 and 147 us per chunk, 109 us in segments.
+// ---------------------------------------------------------------------------
+namespace m3 {
+namespace {
+
+struct ScanCost {   // microseconds
+    int rank, rows;
+    double item, item_pro, base, single, two;   // (single, two: 0 where no such kernel is built)
+};
+constexpr ScanCost kScanCosts[] = {
+    {1, 64, .036, .039, 11.5, 6.6, 10.0},  {1, 128, .066, .082, 15.5, 13.4, 20.0},
+    {2, 64, .033, .038, 11.6, 6.1, 9.0},   {2, 128, .057, .071, 14.4, 9.2, 13.6},
+    {2, 256, .084, .105, 18.3, 20.0, 30.0}, {4, 128, .051, .064, 13.7, 8.4, 12.6},
+    {4, 256, .075, .093, 17.8, 13.2, 22.5}, {4, 512, .133, .182, 29.6, 0.0, 0.0},
+};
+constexpr double kLink = 1.06, kSingleBase = 8.0, kTwoBase = 10.0;
+
+struct ScanChoice {
+    int64_t chunk, G;   // G: chunks per segment (0: one chunk per workgroup)
+};
+
+ScanChoice choose_scan(const m3_dims *d, bool pro, int ncu) {
+    ScanChoice best{d->chunk, 0};
+    double tbest = -1.0;
+    const double nsl = (double)(d->batch * d->nheads);
+    auto rounds = [&](double wgs) { return std::ceil(wgs / ncu); };
+    auto offer = [&](double t, int64_t chunk, int64_t G) {
+        if (tbest < 0.0 || t < tbest) {
+            tbest = t;
+            best = ScanChoice{chunk, G};
+        }
+    };
+    for (const ScanCost &c : kScanCosts) {
+        const int64_t chunk = c.rows / c.rank;
+        if (c.rank != d->rank || chunk < d->chunk) continue;
+        if (!(pro ? find_fused_pro_impl(d->io, d->dstate, d->headdim, d->rank, chunk)
+                  : find_fused_impl(d->io, d->dstate, d->headdim, d->rank, chunk)))
+            continue;
+        const int64_t n = (d->seqlen + chunk - 1) / chunk;
+        offer(std::max(nsl * n * (pro ? c.item_pro : c.item), n * kLink) + c.base, chunk, 0);
+        // (with the prologue only the warp-specialised one-segment kernel)
+        const bool seg = pro ? find_ws_pro_impl(d->io, d->dstate, d->headdim, d->rank, chunk) != nullptr
+                             : find_seg_impl(d->io, d->dstate, d->headdim, d->rank, chunk) != nullptr;
+        if (!seg) continue;
+        offer(rounds(nsl) * n * c.single * (pro ? 1.2 : 1.0) + kSingleBase, chunk, n);
+        if (pro) continue;
+        for_segment_counts(std::min<int64_t>(n, 256), d->batch * d->nheads, ncu, [&](int64_t m) {
+            const int64_t G = (n + m - 1) / m, segs = (n + G - 1) / G;
+            if (G == n) return;
+            offer(rounds(nsl * segs) * G * c.two * (nsl * segs < 0.75 * ncu ? 0.8 : 1.0) + segs * kLink + kTwoBase,
+                  chunk, G);
+        });
+    }
+    return best;
+}
+
+}  // namespace
+}  // namespace m3
+
 // Both scan entry points; `gated` requires z (a token array like x).  With
 // `dry_run` only the checks run (nothing is launched).
 static m3_status scan_fwd(const m3_dims *d, const void *x, const void *B, const void *C,
@@ -195,11 +270,28 @@ static m3_status scan_fwd(const m3_dims *d, const void *x, const void *B, const 
     const void *scal[] = {dt, A, lambda, D};
     for (const void *p : scal)
         if (!aligned4(p)) return M3_ERR_ALIGN;
-    const ScanWorkspaceLayout wl = scan_workspace_layout(d->batch * d->nheads, nc, d->dstate,
-                                                         d->headdim, io_bytes_of(d->io),
-                                                         impl.acc_bytes, impl.fused);
+    ScanWorkspaceLayout wl = scan_workspace_layout(d->batch * d->nheads, nc, d->dstate, d->headdim,
+                                                   io_bytes_of(d->io), impl.acc_bytes, impl.fused);
     if (nc > 0 && (workspace == nullptr || workspace_bytes < wl.total)) return M3_ERR_WORKSPACE;
     if (dry_run) return M3_OK;
+    int64_t seg_chunks = d->seg_chunks;
+    if (nc > 0 && impl.fused && d->io == M3_BF16 && seg_chunks == 0 &&
+        !(d->flags & (M3_SCAN_SPLIT | M3_SCAN_PER_CHUNK))) {
+        static int cus[64];
+        const int ncu = scan::cu_count(cus);
+        const ScanChoice ch = ncu > 0 ? choose_scan(d, pr.on, ncu) : ScanChoice{d->chunk, 0};
+        const scan_launch_fn pc = pr.on ? find_fused_pro_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk)
+                                        : find_fused_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk);
+        const int64_t tok_bytes = d->nheads * d->rank * d->dstate * 2;   // (rows within 32-bit offsets)
+        if (pc && ch.chunk * tok_bytes < (INT64_C(1) << 31)) {
+            impl.per_chunk = pc;
+            impl.launch = ch.G > 0 ? find_seg_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk) : pc;
+            seg_chunks = ch.G;
+            nc = (d->seqlen + ch.chunk - 1) / ch.chunk;
+            wl = scan_workspace_layout(d->batch * d->nheads, nc, d->dstate, d->headdim, io_bytes_of(d->io),
+                                       impl.acc_bytes, impl.fused);
+        }
+    }
 
     ScanArgs a;
     a.x = x; a.B = B; a.C = C;
@@ -223,7 +315,7 @@ static m3_status scan_fwd(const m3_dims *d, const void *x, const void *B, const 
     }
     a.batch = d->batch; a.L = d->seqlen; a.H = d->nheads; a.nchunks = nc;
     a.a_sb = d->a_stride_b; a.a_st = d->a_stride_t; a.a_sh = d->a_stride_h;
-    a.G = d->seg_chunks; a.nseg = 0; a.per_chunk = impl.per_chunk;
+    a.G = seg_chunks; a.nseg = 0; a.per_chunk = impl.per_chunk;
     a.spin_max = g_spin_max.load(std::memory_order_relaxed);
     a.pro = pr;
     const hipError_t e = impl.launch(a, static_cast<hipStream_t>(stream));

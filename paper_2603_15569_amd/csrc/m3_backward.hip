@@ -1125,7 +1125,7 @@ int64_t choose_chunks(int64_t BH, int64_t nchunks, int ncu) {
     const int64_t most = max_segments(BH, nchunks);
     double best = 0.0;
     int64_t bestG = nchunks;
-    for (int64_t ns = 1; ns <= most; ++ns) {
+    for_segment_counts(most, BH, ncu, [&](int64_t ns) {
         const int64_t G = (nchunks + ns - 1) / ns, m = (nchunks + G - 1) / G;
         double t = (double)((BH * m + ncu - 1) / ncu) * G * kMain;
         if (m > 1) t += (double)((BH * (m - 1) * 2 + 2 * ncu - 1) / (2 * ncu)) * G * kAggr + kPass + kFold * m;
@@ -1133,7 +1133,7 @@ int64_t choose_chunks(int64_t BH, int64_t nchunks, int ncu) {
             best = t;
             bestG = G;
         }
-    }
+    });
     return bestG;
 }
 

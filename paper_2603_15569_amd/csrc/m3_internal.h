@@ -112,6 +112,18 @@ struct BwdWorkspaceLayout {
 };
 BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, int64_t P);
 
+// Segment counts worth an estimate when a slice's work is split (up to
+// `most`): 1, 2, 3, 4, 6, 8, 12, ... and the counts that fill the device once,
+// twice and three times over (a handful instead of every count: the choice is
+// made on each call).
+template <class F> inline void for_segment_counts(int64_t most, int64_t slices, int64_t ncu, F f) {
+    for (int64_t m = 1; m <= most; m = (m & (m - 1)) == 0 && m > 1 ? m + m / 2 : m < 3 ? m + 1 : m / 3 * 4) f(m);
+    for (int64_t k = 1; k <= 3; ++k) {
+        const int64_t m = k * ncu / slices;
+        if (m > 1 && m <= most) f(m);
+    }
+}
+
 // default bound of a look-back wait (polls; ~seconds), then an error count
 constexpr uint32_t kSpinMaxDefault = 1u << 22;
 

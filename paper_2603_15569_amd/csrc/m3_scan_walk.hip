@@ -659,7 +659,7 @@ int64_t walk_chunks(int64_t BH, int64_t n64, int64_t most, int64_t ncu) {
     constexpr double kChunk = 4.1, kMapChunk = 2.5, kStart = 5.0, kFoldStep = 0.3;   // us
     double best = 0.0;
     int64_t bestG = n64;
-    for (int64_t ns = 1; ns <= std::min<int64_t>(most, 256); ++ns) {
+    for_segment_counts(std::min<int64_t>(most, 256), BH, ncu, [&](int64_t ns) {
         const int64_t G = (n64 + ns - 1) / ns, m = (n64 + G - 1) / G;
         auto load = [&](int64_t wgs) { return std::max(1.0, 0.87 * (double)((wgs + ncu - 1) / ncu)); };
         double t = G * kChunk * load(BH * m) + kStart;
@@ -668,7 +668,7 @@ int64_t walk_chunks(int64_t BH, int64_t n64, int64_t most, int64_t ncu) {
             best = t;
             bestG = G;
         }
-    }
+    });
     return bestG;
 }
 

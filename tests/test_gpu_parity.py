@@ -1032,3 +1032,42 @@ def test_small_state_segments(N, R, Q, B_, H, L, gate, ph, init):
         assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 2e-2, (b, h)
         assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
         assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
+
+
+# The default scan's own choice of kernel, chunk and segments (longer chunks
+# than the caller's, segments of few slices, one segment a slice), in a
+# workspace of exactly the caller's size, against the oracle.
+@pytest.mark.parametrize("R,Q,B_,H,L,gate,ph,init", [
+    (2, 32, 1, 16, 1001, True, False, True), (4, 32, 1, 8, 707, False, True, True),
+    (1, 64, 1, 4, 64 * 150 + 9, False, False, True), (1, 64, 2, 8, 65, True, True, False),
+    (4, 32, 40, 8, 40, False, False, True), (4, 64, 2, 16, 900, True, False, False),
+    (2, 32, 1, 2, 3, True, False, True), (1, 64, 9, 32, 200, False, False, True)])
+def test_default_choice(R, Q, B_, H, L, gate, ph, init):
+    N, P = 128, 64
+    say(f"default choice R={R} Q={Q} B={B_} H={H} L={L} gate={gate} ph={ph} init={init}")
+    inp = make_scan_inputs(B_, L, H, P, N, R, io="bf16", seed=3100 + L, device=DEV, chunk=Q)
+    g = torch.Generator(DEV).manual_seed(L)
+    kw, okw = {}, {}
+    slices = [(b, h) for b in sorted({0, B_ - 1}) for h in sorted({0, H // 2, H - 1})]
+    if init:
+        h0 = torch.randn((B_, H, N, P), device=DEV, generator=g) * 0.3
+        cB = torch.randn((B_, H, R, N), device=DEV, generator=g).to(torch.bfloat16)
+        cX = torch.randn((B_, H, R, P), device=DEV, generator=g).to(torch.bfloat16)
+        kw = dict(init_state=h0, init_carry=(cB, cX))
+        okw = dict(init_state=oracle.slices_of_state(h0, slices), init_B=oracle.slices_of_state(cB, slices),
+                   init_X=oracle.slices_of_state(cX, slices))
+    z = torch.randn(inp.x.shape, device=DEV, generator=g).to(torch.bfloat16) if gate else None
+    d = m3.scan_dims(inp.x, inp.Bm, Q, inp.A, theta_per_head=ph)
+    ws = torch.zeros(m3.workspace_bytes(d), dtype=torch.uint8, device=DEV)
+    ref = oracle.slices_of_scan(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, inp.theta, inp.D, slices)
+    ry, rs, rb, rx = oracle.scan(**ref, **okw)
+    for _ in range(2):   # (the workspace's control block serves the next call)
+        y, fs, (oB, oX) = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam,
+                                      inp.omega if ph else inp.theta, inp.D, chunk=Q, z=z, workspace=ws,
+                                      check=True, **kw)
+        for k, (b, h) in enumerate(slices):
+            want = oracle.gate(ry[k], z[b, :, h].double().cpu().numpy()) if gate else ry[k]
+            assert oracle.rel_err(y[b, :, h].double().cpu().numpy(), want) <= 2e-2, (b, h)
+            assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 2e-2, (b, h)
+            assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
+            assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
