@@ -164,7 +164,7 @@ extern "C" size_t m3_scan_workspace_bytes(const m3_dims *d) {
 //   segments    `two` a chunk (two passes over each), a link per segment
 // Longer chunks have fewer links and maps but grow the quadratic part: B=1
 // L=2048 H=16 rank 1, chunk 64: 49 us per chunk of 64, 35 of 128; B=4 L=2048
-// H=16 rank 2, chunk 32: 156, 133 and 99 us of 32, 64 and 128 tokens; B=1
+// H=16 rank 2, chunk 32: 156, 103 and 99 us of 32, 64 and 128 tokens; B=1
 // L=16384 H=8 rank 1, chunk 64: 305 and 147 us per chunk, 109 us in segments.
 // ---------------------------------------------------------------------------
 namespace m3 {
@@ -175,12 +175,12 @@ struct ScanCost {   // microseconds
     double item, item_pro, base, single, two;   // (single, two: 0 where no such kernel is built)
 };
 constexpr ScanCost kScanCosts[] = {
-    {1, 64, .036, .039, 11.5, 6.6, 10.0},  {1, 128, .066, .082, 15.5, 13.4, 20.0},
-    {2, 64, .033, .038, 11.6, 6.1, 9.0},   {2, 128, .057, .071, 14.4, 9.2, 13.6},
-    {2, 256, .084, .105, 18.3, 20.0, 30.0}, {4, 128, .051, .064, 13.7, 8.4, 12.6},
-    {4, 256, .075, .093, 17.8, 13.2, 22.5}, {4, 512, .133, .182, 29.6, 0.0, 0.0},
+    {1, 64, .036, .039, 11.7, 6.6, 10.0},   {1, 128, .0515, .059, 14.0, 13.4, 20.0},
+    {2, 64, .033, .036, 11.0, 6.1, 9.0},    {2, 128, .0444, .0477, 12.7, 9.2, 13.6},
+    {2, 256, .084, .101, 18.3, 20.0, 30.0}, {4, 128, .0416, .0461, 12.0, 8.4, 12.6},
+    {4, 256, .076, .095, 17.8, 13.2, 22.5}, {4, 512, .135, .196, 29.6, 0.0, 0.0},
 };
-constexpr double kLink = 1.06, kSingleBase = 8.0, kTwoBase = 10.0;
+constexpr double kLink = 1.0, kSingleBase = 8.0, kTwoBase = 10.0;
 
 struct ScanChoice {
     int64_t chunk, G;   // G: chunks per segment (0: one chunk per workgroup)

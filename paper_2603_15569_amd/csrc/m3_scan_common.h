@@ -298,7 +298,7 @@ struct FShape {
     static constexpr int N = 128, P = 64, NH = 64, Q = Q_, R = R_;
     static constexpr int QR = Q * R;
     static constexpr int RT = QR / 16;                    // 16-row tiles in a chunk
-    static constexpr int NW = NW_ ? NW_ : (RT >= 16 ? 8 : 4);   // waves per workgroup
+    static constexpr int NW = NW_ ? NW_ : (RT >= 8 ? 8 : 4);    // waves per workgroup
     static constexpr int NWO = NW < RT ? NW : RT;         // waves owning output row tiles
     static constexpr int NTHR = NW * kWave;
     static constexpr int TPW = RT / NWO;                  // row tiles per output wave

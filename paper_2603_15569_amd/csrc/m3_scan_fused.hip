@@ -65,7 +65,14 @@ template <typename T, int Q, int R, bool kGate, bool kPro, bool kVar = false>
 // gain, bias; x and z: X = W_X o X', Z = W_Z o Z'), from per-head tables in
 // LDS.  kVar: sequences of different lengths packed along the token axis,
 // items and sequences from the varlen tables.
-__global__ __launch_bounds__((FShape<T, Q, R>::NTHR), 2)
+//
+// Bound: an item's latency times the workgroups a CU holds.  bf16 chunks of 128
+// rows run on eight waves with one row buffer and S_in in it (50-79 KB of LDS,
+// 128 VGPRs), so two workgroups share a CU: 51 / 44 / 42 ns an item at rank 1 /
+// 2 / 4 over the whole device (128 slices of 4096 tokens); one workgroup a CU
+// of four waves with two buffers took 69 / 58 / 52.  With the prologue 59 / 48 /
+// 46 against 73 / 65 / 61.
+__global__ __launch_bounds__((FShape<T, Q, R>::NTHR), (sizeof(T) == 2 && Q * R == 128 ? 4 : 2))
 void k_scan_fused(ScanArgs a) {
     typedef FShape<T, Q, R> S;
     typedef typename S::Acc Acc;
@@ -87,13 +94,16 @@ void k_scan_fused(ScanArgs a) {
     __shared__ Acc s_psie[NH];
     __shared__ float s_gam[Q], s_sig[Q], s_w[Q];
     __shared__ __attribute__((aligned(16))) CS s_cs[Q * LDT];
-    // Chunks of several row blocks double-buffer the staged blocks: block
-    // jb + 1 is committed while the MFMAs read block jb (one barrier a block).
-    constexpr int NBUF = (S::NJB > 1 && sizeof(T) == 2) ? 2 : 1;   // (fp32 blocks: LDS too small)
-    // With two buffers the intra-chunk outputs are formed in the aggregate
-    // pass itself, from the same staged blocks (B^, x and W x): one pass over
-    // the chunk's rows; only e^{cum_t} C^ S_in waits for the look-back.
-    constexpr bool kMerged = NBUF == 2;
+    // Chunks of several row blocks form the intra-chunk outputs in the
+    // aggregate pass itself, from the same staged blocks (B^, x and W x): one
+    // pass over the chunk's rows; only e^{cum_t} C^ S_in waits for the
+    // look-back.  (fp32 blocks: LDS too small.)
+    constexpr bool kMerged = S::NJB > 1 && sizeof(T) == 2;
+    // Chunks of more than two blocks double-buffer them: block jb + 1 is
+    // committed while the MFMAs read block jb (one barrier a block).  Two
+    // blocks keep one buffer, and with S_in in the dead block buffer two
+    // workgroups share a CU, which hides more than the second buffer does.
+    constexpr int NBUF = kMerged && S::NJB > 2 ? 2 : 1;
     // Row blocks are staged row-major (16-byte writes): B^ [row][n], x and
     // W x [row][p]; MFMA operands whose K axis runs along the rows (B^T and
     // (W x)^T for M, x^T for y) are read with the LDS transposing reads.
@@ -102,7 +112,13 @@ void k_scan_fused(ScanArgs a) {
     constexpr int kSB = S::JB * S::LDN, kSXr = S::JB * LDP;
     __shared__ __attribute__((aligned(16))) T s_B[NBUF * kSB];        // B^ blocks [row][n]
     __shared__ __attribute__((aligned(16))) T s_XW[2 * NBUF * kSXr];  // x blocks, then W x blocks [row][p]
-    __shared__ __attribute__((aligned(16))) T s_S[P * S::LDN];        // S_in^T [p][n] (io dtype)
+    // S_in^T [p][n] (io dtype): with one buffer, in it once the merged pass is over
+    constexpr bool kAliasS = kMerged && NBUF == 1;
+    __shared__ __attribute__((aligned(16))) T s_Sown[kAliasS ? 8 : P * S::LDN];
+    static_assert(P * S::LDN <= kSB, "S_in fits a block buffer");
+    T *s_S;
+    if constexpr (kAliasS) s_S = s_B;
+    else s_S = s_Sown;
     __shared__ int s_i[4];
     __shared__ uint32_t s_ctl[2];   // call epoch, whether this item is the janitor
     // block prologue tables of the head (fp32): B gain and bias as 16-byte
@@ -242,7 +258,7 @@ void k_scan_fused(ScanArgs a) {
     // (JB is a multiple of R): chunks of up to 256 rows hold their table
     // entries in registers for the whole chunk; the 512-row chunks need those
     // registers for their tiles and read the entries per block.
-    constexpr bool kHoldB = kPro && S::QR <= 256;
+    constexpr bool kHoldB = kPro && S::QR <= 256 && S::QR != 128;   // (128 rows: two workgroups a CU need the registers)
     static_assert(S::JB % R == 0, "rank row of a B task independent of the block");
     float4 bgr[kHoldB ? TB : 1][kHoldB ? S::CE : 1];
     // kAgg: stage W x too (operand of M); kOut: stage x too (operand of y)
@@ -679,7 +695,14 @@ void k_scan_fused(ScanArgs a) {
 #pragma unroll
     for (int sb = 0; sb < S::NJB; ++sb) {
         const int jb = blk(sb);
-        if constexpr (NBUF == 2) {
+        if constexpr (kMerged && NBUF == 1) {
+            if (sb > 0) {   // (the first block is staged above; the barrier below ended the reads of the last)
+                commit(jb, ring[0], True{}, True{});
+                __syncthreads();
+                if (sb + 1 < S::NJB) fetch(blk(sb + 1), ring[0]);
+            }
+            if constexpr (kRev) load_c(sb);
+        } else if constexpr (NBUF == 2) {
             if (sb + 1 < S::NJB) {   // stage the next block while this one feeds the MFMAs
                 commit(blk(sb + 1), ring[(sb + 1) % DA], True{}, True{});
                 if (sb + 1 + DA < S::NJB) fetch(blk(sb + 1 + DA), ring[(sb + 1) % DA]);
