@@ -141,6 +141,8 @@ struct ScanImpl {
 ScanImpl find_scan_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
 // segments walked with the state in registers (bf16, N = 64 and 32)
 ScanImpl find_walk_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
+// chunks side by side in a workgroup (fp32, N = P = 16)
+ScanImpl find_f32s_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
 step_launch_fn find_step_impl(int io, int64_t N, int64_t P, int64_t R);
 scan_launch_fn find_fused_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q);
 // the per-chunk kernel over varlen tables (null: not built for the shape)

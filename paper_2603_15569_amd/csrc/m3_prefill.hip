@@ -507,12 +507,6 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t stream) {
 
 // Instantiated shapes: (io, N, P, R, Q).  io 0 = fp32, 1 = bf16.
 #define M3_SCAN_SHAPES(X)          \
-    X(0, float, 16, 16, 1, 64)     \
-    X(0, float, 16, 16, 2, 32)     \
-    X(0, float, 16, 16, 2, 64)     \
-    X(0, float, 16, 16, 4, 16)     \
-    X(0, float, 16, 16, 4, 32)     \
-    X(0, float, 16, 16, 4, 64)     \
     X(0, float, 128, 64, 2, 32)    \
     X(0, float, 128, 64, 4, 16)    \
     X(0, float, 128, 64, 4, 32)    \
@@ -531,7 +525,8 @@ ScanImpl find_scan_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q) {
         return ScanImpl{&launch_scan<T, N_, P_, R_, Q_>, (int)sizeof(typename AccOf<T>::type), false, nullptr};
     M3_SCAN_SHAPES(M3_CASE)
 #undef M3_CASE
-    return find_walk_impl(io, N, P, R, Q);   // bf16 with the smaller states
+    const ScanImpl f = find_f32s_impl(io, N, P, R, Q);
+    return f.launch ? f : find_walk_impl(io, N, P, R, Q);   // (bf16 with the smaller states)
 }
 
 }  // namespace m3

@@ -1,0 +1,377 @@
+// Prefill scan of the small fp32 build (N = P = 16) in one launch, on gfx950.
+//
+// The decomposition is that of m3_prefill.hip on chunks of 64 rows (64 / R
+// tokens) whatever the caller's chunk.  A workgroup walks a segment of a
+// slice's chunks, kC chunks at a time side by side, four waves each: their
+// prologues, rotated rows and maps M, then the short chain of states through
+// the kC chunks, then their outputs.  Few and long slices are split into
+// segments: k_f32s<false> forms the segments' maps first, and each workgroup
+// folds those before its own.
+// Bound: the latency of a pass (a memory round trip, the fp64 scans, sines,
+// cosines and exponentials, six barriers).  Against three kernels with a
+// workgroup per chunk and a sine and cosine per element and use: B=1 L=256 H=2
+// rank 1 17.3 us (20.3), B=1 L=4096 H=8 31 (42), B=64 L=1000 H=16 234 (290),
+// B=1 L=16384 H=2 rank 4 chunk 32 77 (223), B=8 L=47 H=32 11.6 (20.3).
+// Precision as there: fp64 prefix sums, angles, decays and rotations, each
+// operand rounded once to fp32, fp32 MFMA.
+#include <algorithm>
+
+#include "m3_device.h"
+#include "m3_internal.h"
+#include "m3_scan_common.h"
+
+namespace m3 {
+namespace {
+
+using namespace scan;
+
+constexpr int kN = 16, kP = 16, kNH = 8, kRows = 64, kMap = kN * kP;
+constexpr int LD = 20;   // LDS row stride in floats (16-byte rows)
+typedef Mma<float> MF;
+
+// e^x for x <= 0 to better than fp32's half unit (relative error below 1e-11),
+// in fp64: 2^n times the Taylor polynomial of 2^f, |f| <= 1/2, whose terms are
+// (ln 2)^k / k!.  Half the operations of exp, which sixteen waves of a compute
+// unit take in turn here.
+__device__ __forceinline__ double exp_neg(double x) {
+    const double y = fmax(x, -700.0) * 1.4426950408889634074, n = rint(y), f = y - n;
+    double p = 1.01780860092396960e-07;
+    p = fma(p, f, 1.32154867901443053e-06);
+    p = fma(p, f, 1.52527338040598377e-05);
+    p = fma(p, f, 1.54035303933816061e-04);
+    p = fma(p, f, 1.33335581464284411e-03);
+    p = fma(p, f, 9.61812910762847688e-03);
+    p = fma(p, f, 5.55041086648215762e-02);
+    p = fma(p, f, 2.40226506959100694e-01);
+    p = fma(p, f, 6.93147180559945286e-01);
+    return ldexp(fma(p, f, 1.0), (int)n);
+}
+
+struct ChunkLds {   // one chunk's share
+    float B[kRows * LD], VB[kRows * LD], C[kRows * LD], X[kRows * LD];   // B^, v B^, C^, x
+    double psi[kRows][kNH];        // by row (a token's rank rows agree)
+    double cum[kRows];
+    float sig[kRows], gam[kRows];
+    double ce[kNH], se[kNH], e;    // cos and sin of psi_e, e^{cum_e}
+    float M[kMap];                 // [n][p]
+    float S[kP * LD];              // S_in^T [p][n]
+};
+
+struct Raw {   // a lane's loads for one chunk
+    float2 th;                     // pairs 2 wq, 2 wq + 1 of its row's token
+    float dts;                     // (per-head frequencies: the token's dt)
+    float dt, lam, A, dtn, lamn;
+    f32x4 B0, B1, C0, C1, X;       // its row's columns 4g.. and the rotation partners
+};
+
+template <int R, int kC, bool kOut>
+__global__ __launch_bounds__(256 * kC) void k_f32s(ScanArgs a) {
+    constexpr int Q = kRows / R;
+    __shared__ __attribute__((aligned(16))) ChunkLds L[kC];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), q = wave / 4, wq = wave % 4;
+    const int g = lane >> 4, l16 = lane & 15;
+    const int64_t bh = blockIdx.x, seg = blockIdx.y, b = bh / a.H, h = bh % a.H;
+    const int64_t tok = b * a.L * a.H + h;             // the slice's first (token, head)
+    const int64_t n64 = (a.L + Q - 1) / Q;
+    const int64_t c0 = seg * a.G, c1 = min(c0 + a.G, n64);   // (G: a multiple of kC but in the last segment)
+    ChunkLds &K = L[q];
+    auto valid = [&](int64_t c) { return (int)max((int64_t)0, min((int64_t)Q, a.L - c * Q)); };
+    const int srow = lane, st = srow / R;              // the scans' row and token
+    const int row = 16 * wq + l16, rt = row / R;       // the staged row and its token
+    const int pi = 4 * (g & 1);                        // its four rotation pairs
+
+    auto load = [&](int64_t c, Raw &r) {
+        const int64_t t0 = c * Q, last = max((int64_t)0, a.L - 1);
+        const int64_t ts = min(t0 + st, last), tn = min(ts + 1, last), tr = min(t0 + rt, last);
+        const float *th = a.theta_ph ? a.theta + h * kNH : a.theta + (tok + ts * a.H) * kNH;
+        r.th = *reinterpret_cast<const float2 *>(th + 2 * wq);
+        r.dt = a.dt[tok + ts * a.H];
+        r.dts = a.theta_ph ? r.dt : 1.f;
+        r.lam = a.lam[tok + ts * a.H];
+        r.A = a.A[b * a.a_sb + ts * a.a_st + h * a.a_sh];
+        r.dtn = a.dt[tok + tn * a.H];
+        r.lamn = a.lam[tok + tn * a.H];
+        const int64_t at = (tok + tr * a.H) * R + row % R;
+        const float *B = static_cast<const float *>(a.B) + at * kN, *C = static_cast<const float *>(a.C) + at * kN;
+        r.B0 = *reinterpret_cast<const f32x4 *>(B + 4 * g);
+        r.B1 = *reinterpret_cast<const f32x4 *>(B + 4 * (g ^ 2));
+        if constexpr (kOut) {
+            r.C0 = *reinterpret_cast<const f32x4 *>(C + 4 * g);
+            r.C1 = *reinterpret_cast<const f32x4 *>(C + 4 * (g ^ 2));
+        }
+        r.X = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.x) + at * kP + 4 * g);
+    };
+
+    // entering state: thread (pair, column) of the first 128
+    const int si = (tid / kP) % kNH, sp = tid % kP;
+    float sre = 0.f, sim = 0.f;
+    if (kOut && tid < kNH * kP) {
+        float re = 0.f, im = 0.f;
+        if (a.init_state) {
+            re = a.init_state[bh * kMap + si * kP + sp];
+            im = a.init_state[bh * kMap + (si + kNH) * kP + sp];
+        }
+        if (a.L > 0 && a.init_cB) {   // the previous-input term of token 0
+            const float wb = (1.f - a.lam[tok]) * a.dt[tok];
+            const float *iB = static_cast<const float *>(a.init_cB) + bh * (R * kN);
+            const float *iX = static_cast<const float *>(a.init_cX) + bh * (R * kP);
+            float ure = 0.f, uim = 0.f;
+            for (int r = 0; r < R; ++r) {
+                ure += iB[r * kN + si] * iX[r * kP + sp];
+                uim += iB[r * kN + si + kNH] * iX[r * kP + sp];
+            }
+            re += wb * ure;
+            im += wb * uim;
+        }
+        for (int64_t s = 0; s < seg; ++s) {   // S <- e^{..} R S + map, rounded to fp32 as every chunk's state
+            const double *t = static_cast<const double *>(a.tot) + (bh * a.nseg + s) * (2 * kNH);
+            const float *m = a.M + (bh * a.nseg + s) * kMap;
+            const double c = t[si], sn = t[kNH + si];
+            const float nr = (float)(c * re - sn * im + m[si * kP + sp]);
+            im = (float)(sn * re + c * im + m[(si + kNH) * kP + sp]);
+            re = nr;
+        }
+        sre = re;
+        sim = im;
+    }
+    const float Dh = a.D[h];
+    double tc = 1.0, ts = 0.0;   // (maps: e^{sum cum} (cos, sin) of the segment's angles)
+    // (four chunks side by side leave no registers to load a pass ahead)
+    constexpr bool kAhead = kC == 1;
+    Raw raw;
+    if (kAhead && c0 < c1) load(min(c0 + q, c1 - 1), raw);
+    for (int64_t cb = c0; cb < c1; cb += kC) {
+        const int64_t c = cb + q;
+        const bool on = c < c1;                       // (uniform per wave; an idle chunk slot repeats the last)
+        const int64_t cc = on ? c : c1 - 1;
+        const int nv = valid(cc);
+        if constexpr (!kAhead) load(cc, raw);
+        // 1. prefix sums over the tokens (a token's value on its first rank row)
+        {
+            const bool in = st < nv, lead = in && srow % R == 0;
+            const double lg = lead ? (double)raw.dt * (double)raw.A : 0.0;
+            const double p0 = wave_incl_scan(lead ? (double)(raw.th.x * raw.dts) : 0.0, lane);
+            const double p1 = wave_incl_scan(lead ? (double)(raw.th.y * raw.dts) : 0.0, lane);
+            K.psi[srow][2 * wq] = p0;
+            K.psi[srow][2 * wq + 1] = p1;
+            if (wq == 0) {
+                K.cum[srow] = wave_incl_scan(lg, lane);
+                const float gam = in ? raw.lam * raw.dt : 0.f;
+                float sig = gam;
+                if (in && cc * Q + st + 1 < a.L) sig += (1.f - raw.lamn) * raw.dtn;
+                K.gam[srow] = gam;
+                K.sig[srow] = sig;
+            }
+        }
+        __syncthreads();
+        // 2. rotated rows.  A lane's row has four pairs; it forms the sines and
+        // cosines of two, the lane of the partner columns the others.
+        const double cume = K.cum[nv * R - 1];
+        const f32x4 xr = raw.X;
+        {
+            const int mine = pi + (g < 2 ? 0 : 2);
+            double cs[4], sn[4];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                double s, c2;
+                sincospi(K.psi[row][mine + k] * 0.31830988618379067154, &s, &c2);   // (x / pi: no large-argument path)
+                const double so = __shfl_xor(s, 32, kWave), co = __shfl_xor(c2, 32, kWave);
+                cs[k] = g < 2 ? c2 : co;
+                sn[k] = g < 2 ? s : so;
+                cs[2 + k] = g < 2 ? co : c2;
+                sn[2 + k] = g < 2 ? so : s;
+            }
+            const bool in = rt < nv;
+            const double v = in ? exp_neg(cume - K.cum[row]) * (double)K.sig[row] : 0.0;
+            const double sg = g < 2 ? 1.0 : -1.0;   // re: c u + s v; im: c v - s u
+            f32x4 bo, vo, co;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double rb = in ? cs[k] * (double)raw.B0[k] + sg * sn[k] * (double)raw.B1[k] : 0.0;
+                bo[k] = (float)rb;
+                vo[k] = (float)(v * rb);
+                if constexpr (kOut) co[k] = in ? (float)(cs[k] * (double)raw.C0[k] + sg * sn[k] * (double)raw.C1[k]) : 0.f;
+            }
+            f32x4 x4 = xr;
+            if (!in) x4 = f32x4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4 *>(&K.VB[row * LD + 4 * g]) = vo;
+            *reinterpret_cast<f32x4 *>(&K.X[row * LD + 4 * g]) = x4;
+            if constexpr (kOut) {
+                *reinterpret_cast<f32x4 *>(&K.B[row * LD + 4 * g]) = bo;
+                *reinterpret_cast<f32x4 *>(&K.C[row * LD + 4 * g]) = co;
+            }
+            if (row == nv * R - 1 && g < 2) {   // the chunk's rotation and decay
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    K.ce[pi + k] = cs[k];
+                    K.se[pi + k] = sn[k];
+                }
+                if (g == 0) K.e = exp_neg(cume);
+            }
+        }
+        if (kAhead && cb + kC < c1) load(min(cb + kC + q, c1 - 1), raw);
+        __syncthreads();
+        // 3. M = sum_j v_j B^_j x_j^T (one wave a chunk)
+        if (wq == 0) {
+            f32x4 m = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < kRows / 4; ++ks)
+                m = MF::mma(K.VB[(4 * ks + g) * LD + l16], K.X[(4 * ks + g) * LD + l16], m);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) K.M[(4 * g + v) * kP + l16] = m[v];
+        }
+        __syncthreads();
+        // 4. the states through these chunks: S <- R(psi_e) (e^{cum_e} S + M)
+        if (tid < kNH * kP) {
+#pragma unroll
+            for (int k = 0; k < kC; ++k) {
+                if (cb + k >= c1) break;
+                ChunkLds &Z = L[k];
+                if constexpr (kOut) {
+                    Z.S[sp * LD + si] = sre;
+                    Z.S[sp * LD + si + kNH] = sim;
+                }
+                const double cn = Z.ce[si], sn = Z.se[si], e = Z.e;
+                const double ure = e * (double)sre + (double)Z.M[si * kP + sp];
+                const double uim = e * (double)sim + (double)Z.M[(si + kNH) * kP + sp];
+                sre = (float)(cn * ure - sn * uim);
+                sim = (float)(sn * ure + cn * uim);
+                if constexpr (!kOut) {
+                    const double nc = e * (cn * tc - sn * ts);
+                    ts = e * (sn * tc + cn * ts);
+                    tc = nc;
+                }
+            }
+        }
+        if constexpr (kOut) {
+            __syncthreads();
+            // 5. y of row tile wq, transposed: lane (row l16; columns 4g .. 4g + 3)
+            const int tl = rt;
+            f32x4 y = {0.f, 0.f, 0.f, 0.f};
+            float cf[4];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                cf[kk] = K.C[row * LD + 4 * kk + g];
+                y = MF::mma(K.S[l16 * LD + 4 * kk + g], cf[kk], y);
+            }
+            const double cumt = K.cum[row];
+            y *= (float)exp_neg(cumt);
+#pragma unroll
+            for (int J = 0; J < 4; ++J) {
+                if (J > wq) continue;
+                f32x4 gt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) gt = MF::mma(K.B[(16 * J + l16) * LD + 4 * kk + g], cf[kk], gt);
+#pragma unroll
+                for (int v = 0; v < 4; v += R) {
+                    const int j = 16 * J + 4 * g + v, tj = j / R;
+                    float w = 0.f;
+                    if (tj < tl) w = (float)exp_neg(cumt - K.cum[j]) * K.sig[j];
+                    else if (tj == tl) w = K.gam[row];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) gt[v + r] *= w;
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y = MF::mma(K.X[(16 * J + 4 * g + v) * LD + l16], gt[v], y);
+            }
+            if (on && rt < nv) {
+                const int64_t at = ((tok + (cc * Q + rt) * a.H) * R + row % R) * kP + 4 * g;
+                f32x4 zv = {0.f, 0.f, 0.f, 0.f};
+                if (a.z) zv = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.z) + at);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    y[v] += Dh * xr[v];
+                    if (a.z) y[v] *= silu(zv[v]);
+                }
+                *reinterpret_cast<f32x4 *>(static_cast<float *>(a.y) + at) = y;
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (!kOut) {
+        if (tid < kNH * kP) {
+            float *m = a.M + (bh * a.nseg + seg) * kMap;
+            m[si * kP + sp] = sre;
+            m[(si + kNH) * kP + sp] = sim;
+            double *t = static_cast<double *>(a.tot) + (bh * a.nseg + seg) * (2 * kNH);
+            if (sp == 0) {
+                t[si] = tc;
+                t[kNH + si] = ts;
+            }
+        }
+    } else if (seg == a.nseg - 1) {
+        if (tid < kNH * kP) {
+            a.final_state[bh * kMap + si * kP + sp] = sre;
+            a.final_state[bh * kMap + (si + kNH) * kP + sp] = sim;
+        }
+        // the carry: the last token's B and x (the initial carry of an empty sequence)
+        const int64_t lastt = tok + (a.L - 1) * a.H;
+        const float *sB = a.L > 0 ? static_cast<const float *>(a.B) + lastt * (R * kN)
+                                  : a.init_cB ? static_cast<const float *>(a.init_cB) + bh * (R * kN) : nullptr;
+        const float *sX = a.L > 0 ? static_cast<const float *>(a.x) + lastt * (R * kP)
+                                  : a.init_cX ? static_cast<const float *>(a.init_cX) + bh * (R * kP) : nullptr;
+        float *cB = static_cast<float *>(a.cB) + bh * (R * kN), *cX = static_cast<float *>(a.cX) + bh * (R * kP);
+        if (tid < R * kN) {
+            cB[tid] = sB ? sB[tid] : 0.f;
+            cX[tid] = sX ? sX[tid] : 0.f;
+        }
+    }
+}
+
+template <int R>
+hipError_t launch_f32s(const ScanArgs &args, hipStream_t stream) {
+    constexpr int Q = kRows / R;
+    static int cus[64];
+    ScanArgs a = args;
+    const int64_t BH = a.batch * a.H, n64 = (a.L + Q - 1) / Q;
+    const int ncu = cu_count(cus);
+    if (ncu <= 0) return hipErrorInvalidDevice;
+    // One chunk at a time in a small workgroup where the slices fill the
+    // device (six workgroups a CU) or have one chunk each, else four side by
+    // side.
+    const bool wide = n64 > 1 && BH < 4 * ncu;
+    a.G = std::max<int64_t>(n64, 1);
+    a.nseg = 1;
+    if (wide) {
+        // a pass of four chunks takes kPass, in a map pass kMapPass; a launch
+        // and a workgroup's start kStart (microseconds)
+        constexpr double kPass = 7.0, kMapPass = 5.0, kStart = 5.0, kFoldStep = 0.2;
+        double best = 0.0;
+        const int64_t passes = (n64 + 3) / 4;
+        // (the totals of a segment take 16 doubles of the 9 a caller's chunk has)
+        for_segment_counts(std::min(passes, std::max<int64_t>(a.nchunks / 2, 1)), BH, ncu, [&](int64_t m) {
+            const int64_t G = (passes + m - 1) / m, ns = (passes + G - 1) / G;
+            double t = (double)((BH * ns + ncu - 1) / ncu) * G * kPass + kStart;
+            if (ns > 1) t += (double)((BH * (ns - 1) + ncu - 1) / ncu) * G * kMapPass + kStart + kFoldStep * ns;
+            if (m == 1 || t < best) {
+                best = t;
+                a.G = 4 * G;
+                a.nseg = ns;
+            }
+        });
+    }
+    const unsigned nsl = (unsigned)BH, ns = (unsigned)a.nseg;
+    if (!wide) {
+        hipLaunchKernelGGL((k_f32s<R, 1, true>), dim3(nsl, 1), dim3(256), 0, stream, a);
+    } else {
+        if (ns > 1) hipLaunchKernelGGL((k_f32s<R, 4, false>), dim3(nsl, ns - 1), dim3(1024), 0, stream, a);
+        hipLaunchKernelGGL((k_f32s<R, 4, true>), dim3(nsl, ns), dim3(1024), 0, stream, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// fp32, N = P = 16: every (rank, chunk) the caller may ask for.
+ScanImpl find_f32s_impl(int io, int64_t N, int64_t P, int64_t R, int64_t Q) {
+    const ScanImpl none{nullptr, 0, false, nullptr};
+    if (io != 0 || N != kN || P != kP) return none;
+#define M3_CASE(R_, Q_) \
+    if (R == R_ && Q == Q_) return ScanImpl{&launch_f32s<R_>, (int)sizeof(double), false, nullptr};
+    M3_CASE(1, 64) M3_CASE(2, 32) M3_CASE(2, 64) M3_CASE(4, 16) M3_CASE(4, 32) M3_CASE(4, 64)
+#undef M3_CASE
+    return none;
+}
+
+}  // namespace m3

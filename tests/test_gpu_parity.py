@@ -1071,3 +1071,37 @@ def test_default_choice(R, Q, B_, H, L, gate, ph, init):
             assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 2e-2, (b, h)
             assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
             assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
+
+
+# The small fp32 scan: chunks side by side and one at a time (many slices, one
+# chunk a slice), a partial last pass, segments of several passes, ragged ends.
+@pytest.mark.parametrize("R,Q,B_,H,L,gate,ph,init", [
+    (1, 64, 1, 1, 64 * 40 + 3, True, False, True), (4, 32, 70, 16, 50, False, True, True),
+    (2, 64, 1, 3, 64 * 9, True, True, False), (1, 64, 1, 2, 2, False, False, True),
+    (4, 64, 1, 2, 16 * 5 + 1, True, False, True), (2, 32, 130, 8, 65, False, False, False)])
+def test_small_fp32_segments(R, Q, B_, H, L, gate, ph, init):
+    N = P = 16
+    say(f"small fp32 R={R} Q={Q} B={B_} H={H} L={L} gate={gate} ph={ph} init={init}")
+    inp = make_scan_inputs(B_, L, H, P, N, R, io="f32", seed=4100 + L, device=DEV, chunk=Q)
+    g = torch.Generator(DEV).manual_seed(L)
+    kw, okw = {}, {}
+    slices = [(b, h) for b in sorted({0, B_ - 1}) for h in range(H)]
+    if init:
+        h0 = torch.randn((B_, H, N, P), device=DEV, generator=g) * 0.3
+        cB = torch.randn((B_, H, R, N), device=DEV, generator=g)
+        cX = torch.randn((B_, H, R, P), device=DEV, generator=g)
+        kw = dict(init_state=h0, init_carry=(cB, cX))
+        okw = dict(init_state=oracle.slices_of_state(h0, slices), init_B=oracle.slices_of_state(cB, slices),
+                   init_X=oracle.slices_of_state(cX, slices))
+    z = torch.randn(inp.x.shape, device=DEV, generator=g) if gate else None
+    y, fs, (oB, oX) = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam,
+                                  inp.omega if ph else inp.theta, inp.D, chunk=Q, z=z, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.slices_of_scan(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, inp.theta, inp.D, slices)
+    ry, rs, rb, rx = oracle.scan(**ref, **okw)
+    for k, (b, h) in enumerate(slices):
+        want = oracle.gate(ry[k], z[b, :, h].double().cpu().numpy()) if gate else ry[k]
+        assert oracle.rel_err(y[b, :, h].double().cpu().numpy(), want) <= 1e-5, (b, h)
+        assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 1e-5, (b, h)
+        assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
+        assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
