@@ -8,6 +8,7 @@ is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -130,8 +131,16 @@ def _p(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# The raw handle of the current stream without a Stream object (half the
+# marshalling time of a decode step went into building one), where torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cur_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _cur_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_cur_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -344,18 +353,25 @@ def scan_fwd_varlen(x, Bm, Cm, dt, A, lam, theta, D, chunk: int, cu_seqlens,
     return y, fs, (cB, cX)
 
 
+@functools.lru_cache(maxsize=256)
+def _step_dims(xs, bs, dtype, ash, ast, theta_per_head):
+    """The dims of a decode step by shapes, strides and dtype (a decode loop
+    makes the same ones for every token; the library only reads them)."""
+    batch, nheads, rank, headdim = xs
+    if len(ash) == 1 and ash[0] == nheads:
+        sb, sh = 0, 1
+    elif len(ash) == 2 and tuple(ash) == (batch, nheads):
+        sb, sh = ast
+    else:
+        raise ValueError(f"A must be [H] or [B, H], got {tuple(ash)}")
+    return M3Dims(batch, 1, nheads, headdim, bs[-1], rank, 1, _IO[dtype],
+                  M3_THETA_PER_HEAD if theta_per_head else 0, sb, 0, sh, 0)
+
+
 def step_dims(x_t: torch.Tensor, B_t: torch.Tensor, A: torch.Tensor,
               theta_per_head: bool = False) -> M3Dims:
-    batch, nheads, rank, headdim = x_t.shape
-    dstate = B_t.shape[-1]
-    if A.dim() == 1 and A.shape[0] == nheads:
-        sb, sh = 0, 1
-    elif A.dim() == 2 and tuple(A.shape) == (batch, nheads):
-        sb, sh = A.stride()
-    else:
-        raise ValueError(f"A must be [H] or [B, H], got {tuple(A.shape)}")
-    return M3Dims(batch, 1, nheads, headdim, dstate, rank, 1, _IO[x_t.dtype],
-                  M3_THETA_PER_HEAD if theta_per_head else 0, sb, 0, sh, 0)
+    d = _step_dims(x_t.shape, B_t.shape, x_t.dtype, A.shape, A.stride(), bool(theta_per_head))
+    return M3Dims.from_buffer_copy(d)   # (the caller's own)
 
 
 def step(state, carry, x_t, B_t, C_t, dt_t, A, lam_t, theta_t, D, y=None, stream=None, z=None):
@@ -363,7 +379,8 @@ def step(state, carry, x_t, B_t, C_t, dt_t, A, lam_t, theta_t, D, y=None, stream
     given: y_t o SiLU(z_t); `theta_t` [B,H,N/2] angles or [H,N/2] frequencies
     omega, as in scan_fwd): advances `state` [B,H,N,P] and `carry`
     (B [B,H,R,N], X [B,H,R,P]) in place by one token; returns y_t [B,H,R,P]."""
-    d = step_dims(x_t, B_t, A, _theta_per_head(theta_t, x_t.shape[1], B_t.shape[-1]))
+    xs, bs = x_t.shape, B_t.shape
+    d = _step_dims(xs, bs, x_t.dtype, A.shape, A.stride(), _theta_per_head(theta_t, xs[1], bs[-1]))
     if y is None:
         y = torch.empty_like(x_t)
     cB, cX = carry

@@ -384,3 +384,20 @@ def test_backward_host_validation(L):
     assert call(dims(**bf), ws_bytes=need - 1) == m3.M3_ERR_WORKSPACE
     assert L.m3_scan_bwd_workspace_bytes(ctypes.byref(dims())) == 0
     assert L.m3_last_hip_error() == 0
+
+
+def test_step_dims_by_shape_and_stride(L):
+    """The decode step's dims follow the shapes, dtype and A's strides of each
+    call, and a caller's copy is its own."""
+    import torch
+    x = torch.zeros(2, 3, 4, 64, dtype=torch.bfloat16)
+    B = torch.zeros(2, 3, 4, 128, dtype=torch.bfloat16)
+    one = m3.step_dims(x, B, torch.zeros(3))
+    assert (one.batch, one.nheads, one.rank, one.headdim, one.dstate) == (2, 3, 4, 64, 128)
+    assert (one.a_stride_b, one.a_stride_h, one.flags) == (0, 1, 0)
+    per_batch = m3.step_dims(x, B, torch.zeros(4, 6)[::2, ::2], True)
+    assert (per_batch.a_stride_b, per_batch.a_stride_h, per_batch.flags) == (12, 2, m3.M3_THETA_PER_HEAD)
+    one.batch = 99
+    assert m3.step_dims(x, B, torch.zeros(3)).batch == 2
+    with pytest.raises(ValueError):
+        m3.step_dims(x, B, torch.zeros(2))
