@@ -48,7 +48,7 @@
 // steps.  One fp32 map of the state per chunk and direction, written by a
 // kernel over all chunks and folded by a second one, moved 352 KB a chunk and
 // took 8.62 ms on B=8 L=4096 H=32 rank 4 and 313 us on B=4 L=2048 H=16 SISO;
-// carrying the state through a segment in registers takes 2.90 ms and 175 us.
+// carrying the state through a segment in registers takes 2.64 ms and 173 us.
 // Operands are bf16 with fp32 accumulation (as the forward); the carried
 // state and gradient, the prefix sums, weights and every scalar gradient are
 // fp32.  Results are deterministic: no atomics.
@@ -104,6 +104,29 @@ struct Tok {
     float c2e;
 };
 
+// Sums over the 16 lanes of a row group of the values of TT tokens (v[0 ..
+// TT - 1] in every lane): the lane l16 < TT gets token l16's.  Four at once by
+// a butterfly (11 operations and one masked store, against 16 and four).
+template <int TT> __device__ __forceinline__ float sum16_each(const float (&v)[TT], int l16) {
+    if constexpr (TT == 4) {
+        const bool o1 = l16 & 1, o2 = l16 & 2;
+        const float a = (o1 ? v[1] : v[0]) + dpp_src<0xB1, 0xf>(o1 ? v[0] : v[1]);
+        const float b = (o1 ? v[3] : v[2]) + dpp_src<0xB1, 0xf>(o1 ? v[2] : v[3]);
+        float r = (o2 ? b : a) + dpp_src<0x4E, 0xf>(o2 ? a : b);
+        r += dpp_src<0x128, 0xf>(r);
+        r += dpp_src<0x124, 0xf>(r);
+        return r;
+    } else if constexpr (TT == 2) {
+        const bool o1 = l16 & 1;
+        float r = (o1 ? v[1] : v[0]) + dpp_src<0xB1, 0xf>(o1 ? v[0] : v[1]);
+        r += dpp_src<0x128, 0xf>(r);
+        r += dpp_src<0x124, 0xf>(r);
+        r += dpp_src<0x122, 0xf>(r);
+        return r;
+    } else {
+        return sum16(v[0]);
+    }
+}
 // Sum over the R lanes of a token's rank rows.
 template <int R> __device__ __forceinline__ float sum_rank(float v) {
     if constexpr (R >= 2) v += dpp_src<0xB1, 0xf>(v);   // quad_perm: lane ^ 1
@@ -781,9 +804,10 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                         for (int kk = 0; kk < 2; ++kk)
                             dg = MM::mma(MM::load(&M.Y[(16 * T + w.l16) * LDP + kk * 32 + 8 * w.g]), fX[kk], dg);
                         const f32x4 c4 = *reinterpret_cast<const f32x4 *>(&o.c2[16 * T + 4 * w.g]);
+                        float rv[TT];
 #pragma unroll
                         for (int q = 0; q < TT; ++q) {
-                            const int r0 = 16 * T + 4 * w.g + q * R, tt = r0 / R;   // a token's rows
+                            const int tt = (16 * T + 4 * w.g) / R + q;   // a token's rows
                             const bool off = tl < tt, on = tl == tt;
                             const float ex = off ? exp2_fast(c4[q * R] - c2j) : 0.f;
                             const float wt = off ? ex * sgj : on ? gmj : 0.f;
@@ -797,17 +821,17 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
                             }
                             const float od = off ? dW : 0.f;
                             if (hf == 0) {   // (the halves share the sums)
-                                const float val = od * wt;
-                                colc += val;
-                                const float rs = sum16(val);
-                                if (w.l16 == 0) M.rc[J][r0] = rs;
+                                rv[q] = od * wt;
+                                colc += rv[q];
                             } else {
+                                rv[q] = on ? dW : 0.f;
                                 cols += od * ex;
-                                if (T == J) {
-                                    const float rs = sum16(on ? dW : 0.f);
-                                    if (w.l16 == 0) M.rg[r0] = rs;
-                                }
                             }
+                        }
+                        if (hf == 0 || T == J) {
+                            const float rs = sum16_each<TT>(rv, w.l16);
+                            float *rd = hf == 0 ? M.rc[J] : M.rg;
+                            if (w.l16 < TT) rd[16 * T + 4 * w.g + w.l16 * R] = rs;
                         }
                     }
 #pragma unroll
