@@ -379,10 +379,10 @@ __device__ __forceinline__ void take_item(uint32_t *ctl, int64_t nsl, int64_t nc
 // first grp[y][c+1] - grp[y][c] slices of the group's list, so ticket k is
 // chunk level c (the last with grp[y][c] <= k) and list entry k - grp[y][c].
 // Every predecessor of an item again holds an earlier ticket of its counter.
-// janitor: the item of group 0's last ticket.
+// first: the item of group 0's first ticket; janitor: that of its last.
 __device__ __forceinline__ void take_item_var(uint32_t *ctl, const int32_t *grp, const int32_t *gstart,
                                               const int32_t *order, int maxn, int64_t *c, int64_t *sl,
-                                              uint32_t *epoch, bool *ready, bool *janitor) {
+                                              uint32_t *epoch, bool *ready, bool *first, bool *janitor) {
     const int x = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & (kGroups - 1));   // XCC id
     for (int tries = 0; tries < kGroups; ++tries) {
         const int y = (x + tries) & (kGroups - 1);
@@ -402,6 +402,7 @@ __device__ __forceinline__ void take_item_var(uint32_t *ctl, const int32_t *grp,
             *sl = order[gstart[y] + (k - gy[lo])];
             *epoch = (uint32_t)(w >> 32);
             *ready = ((uint32_t)w & kTicketReady) != 0;
+            *first = y == 0 && k == 0;
             *janitor = y == 0 && k == items - 1;
             return;
         }
@@ -410,11 +411,14 @@ __device__ __forceinline__ void take_item_var(uint32_t *ctl, const int32_t *grp,
     *sl = -1;
     *epoch = 0;
     *ready = false;
+    *first = false;
     *janitor = false;
 }
 
-// The call's first item clears the look-back flags [0, n) (all threads of the
-// workgroup), then marks them cleared: the ready bit of every group's counter
+// The call's first item (group 0's first ticket, so that no item waits for one
+// that has not started: slice 0's first chunk, or in a varlen launch, whose
+// lists run by decreasing length, that of group 0's longest slice) clears the
+// look-back flags [0, n) (all threads of the workgroup), then marks them cleared: the ready bit of every group's counter
 // (seen by the items that take their tickets after), and, once those have
 // landed, the ready word (polled by items that took theirs before, and by the
 // janitor before it resets the counters).

@@ -869,6 +869,28 @@ def test_varlen_many_short_sequences():
         say(f"varlen {S} sequences, {name}: {e0.elapsed_time(e1) / 3:.3f} ms")
 
 
+# The sequence that comes first is shorter than all others and more slices of
+# several chunks precede it in the item lists than workgroups are resident:
+# none of them may wait for it.
+@pytest.mark.parametrize("R,Q", [(1, 64), (2, 64), (4, 128)])
+def test_varlen_short_sequence_first(R, Q):
+    io, N, P, H = "bf16", 128, 64, 32
+    lens = [3] + [Q + 1 + i % 5 for i in range(80)]
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    T, S = cu[-1], len(lens)
+    say(f"varlen short sequence first R={R} Q={Q} S={S} T={T}")
+    inp = make_scan_inputs(1, T, H, P, N, R, io=io, seed=310 + R, device=DEV, chunk=Q)
+    flat = lambda t: t[0].contiguous()
+    args = (flat(inp.x), flat(inp.Bm), flat(inp.Cm), flat(inp.dt), inp.A, flat(inp.lam),
+            flat(inp.theta), inp.D, Q, cu)
+    ws = torch.zeros(m3.varlen_workspace_bytes(m3.varlen_dims(args[0], args[1], inp.A, Q, cu), cu),
+                     dtype=torch.uint8, device=DEV)
+    y, fs, (cB, cX) = m3.scan_fwd_varlen(*args, workspace=ws, check=True)
+    varlen_oracle_check(inp, y, fs, cB, cX, cu, (0, 1, S - 1), H, R, N, P, io, label="short first")
+
+
 @pytest.mark.parametrize("mode,seg,R,Q", [("per_chunk", 0, 1, 64), ("per_chunk", 0, 4, 128),
                                           ("seg", 2, 4, 64), ("seg", 4, 1, 64)])
 def test_determinism_many_items(mode, seg, R, Q):
