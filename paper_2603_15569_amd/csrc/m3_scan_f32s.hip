@@ -32,9 +32,9 @@ typedef Mma<float> MF;
 // e^x for x <= 0 to better than fp32's half unit (relative error below 1e-11),
 // in fp64: 2^n times the Taylor polynomial of 2^f, |f| <= 1/2, whose terms are
 // (ln 2)^k / k!.  Half the operations of exp, which sixteen waves of a compute
-// unit take in turn here.
+// unit take in turn here.  (The clamp is a comparison, which keeps a NaN.)
 __device__ __forceinline__ double exp_neg(double x) {
-    const double y = fmax(x, -700.0) * 1.4426950408889634074, n = rint(y), f = y - n;
+    const double y = (x < -700.0 ? -700.0 : x) * 1.4426950408889634074, n = rint(y), f = y - n;
     double p = 1.01780860092396960e-07;
     p = fma(p, f, 1.32154867901443053e-06);
     p = fma(p, f, 1.52527338040598377e-05);

@@ -1127,3 +1127,25 @@ def test_small_fp32_segments(R, Q, B_, H, L, gate, ph, init):
         assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 1e-5, (b, h)
         assert np.array_equal(oB[b, h].double().cpu().numpy(), rb[k])
         assert np.array_equal(oX[b, h].double().cpu().numpy(), rx[k])
+
+
+# A NaN in the log-decay of one token spoils what follows it in its slice (y
+# from that token's chunk on at the latest from the token itself, the final
+# state) and nothing in other slices: fp32 on one and on several segments of
+# chunks, and the smaller bf16 states.
+@pytest.mark.parametrize("io,N,P,R,Q,B_,H,L", [
+    ("f32", 16, 16, 1, 64, 1, 2, 300), ("f32", 16, 16, 4, 32, 1, 2, 64 * 40), ("f32", 16, 16, 2, 32, 130, 8, 65),
+    ("bf16", 64, 64, 1, 64, 1, 2, 700), ("bf16", 32, 64, 2, 32, 40, 8, 65)])
+def test_nan_decay_shows(io, N, P, R, Q, B_, H, L):
+    say(f"NaN decay io={io} N={N} R={R} Q={Q} B={B_} H={H} L={L}")
+    inp = make_scan_inputs(B_, L, H, P, N, R, io=io, seed=5100 + L, device=DEV, chunk=Q)
+    A = inp.A.expand(B_, L, H).clone()
+    A[0, L // 2, 1] = float("nan")
+    y, fs, _ = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, A, inp.lam, inp.theta, inp.D, chunk=Q)
+    want, wfs, _ = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A.expand(B_, L, H).contiguous(), inp.lam,
+                               inp.theta, inp.D, chunk=Q)
+    torch.cuda.synchronize()
+    assert torch.isnan(y[0, L // 2:, 1]).all() and torch.isnan(fs[0, 1]).all()
+    assert torch.equal(y[0, :L // 2, 1], want[0, :L // 2, 1])
+    y[0, :, 1], fs[0, 1] = want[0, :, 1], wfs[0, 1]
+    assert torch.equal(y, want) and torch.equal(fs, wfs)
