@@ -32,9 +32,10 @@ typedef Mma<float> MF;
 // e^x for x <= 0 to better than fp32's half unit (relative error below 1e-11),
 // in fp64: 2^n times the Taylor polynomial of 2^f, |f| <= 1/2, whose terms are
 // (ln 2)^k / k!.  Half the operations of exp, which sixteen waves of a compute
-// unit take in turn here.  (The clamp is a comparison, which keeps a NaN.)
+// unit take in turn here.  A NaN stays one; x of any finite size is allowed
+// (ldexp to an exponent below fp64's gives 0).
 __device__ __forceinline__ double exp_neg(double x) {
-    const double y = (x < -700.0 ? -700.0 : x) * 1.4426950408889634074, n = rint(y), f = y - n;
+    const double y = x * 1.4426950408889634074, n = rint(y), f = y - n;
     double p = 1.01780860092396960e-07;
     p = fma(p, f, 1.32154867901443053e-06);
     p = fma(p, f, 1.52527338040598377e-05);
@@ -65,7 +66,7 @@ struct Raw {   // a lane's loads for one chunk
 };
 
 template <int R, int kC, bool kOut>
-__global__ __launch_bounds__(256 * kC) void k_f32s(ScanArgs a) {
+__global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) {
     constexpr int Q = kRows / R;
     __shared__ __attribute__((aligned(16))) ChunkLds L[kC];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -150,7 +151,9 @@ __global__ __launch_bounds__(256 * kC) void k_f32s(ScanArgs a) {
         // 1. prefix sums over the tokens (a token's value on its first rank row)
         {
             const bool in = st < nv, lead = in && srow % R == 0;
-            const double lg = lead ? (double)raw.dt * (double)raw.A : 0.0;
+            // (e^-1e6 is 0: the clamp keeps exp_neg's exponent an int, and the
+            // decays after a token that forgets everything exact)
+            const double la = (double)raw.dt * (double)raw.A, lg = lead ? (la < -1e6 ? -1e6 : la) : 0.0;
             const double p0 = wave_incl_scan(lead ? (double)(raw.th.x * raw.dts) : 0.0, lane);
             const double p1 = wave_incl_scan(lead ? (double)(raw.th.y * raw.dts) : 0.0, lane);
             K.psi[srow][2 * wq] = p0;

@@ -1100,7 +1100,9 @@ def test_default_choice(R, Q, B_, H, L, gate, ph, init):
 @pytest.mark.parametrize("R,Q,B_,H,L,gate,ph,init", [
     (1, 64, 1, 1, 64 * 40 + 3, True, False, True), (4, 32, 70, 16, 50, False, True, True),
     (2, 64, 1, 3, 64 * 9, True, True, False), (1, 64, 1, 2, 2, False, False, True),
-    (4, 64, 1, 2, 16 * 5 + 1, True, False, True), (2, 32, 130, 8, 65, False, False, False)])
+    (4, 64, 1, 2, 16 * 5 + 1, True, False, True), (2, 32, 130, 8, 65, False, False, False),
+    (1, 64, 2, 4, 300, True, False, True), (2, 64, 2, 1, 700, False, True, True),
+    (4, 16, 1, 12, 270, False, False, True), (1, 64, 1, 2, 64 * 130 + 1, False, False, True)])
 def test_small_fp32_segments(R, Q, B_, H, L, gate, ph, init):
     N = P = 16
     say(f"small fp32 R={R} Q={Q} B={B_} H={H} L={L} gate={gate} ph={ph} init={init}")
@@ -1149,3 +1151,26 @@ def test_nan_decay_shows(io, N, P, R, Q, B_, H, L):
     assert torch.equal(y[0, :L // 2, 1], want[0, :L // 2, 1])
     y[0, :, 1], fs[0, 1] = want[0, :, 1], wfs[0, 1]
     assert torch.equal(y, want) and torch.equal(fs, wfs)
+
+
+# A token that forgets everything (A very large or -inf) leaves the tokens
+# after it as if the sequence started there from its own input.
+@pytest.mark.parametrize("a0", [-1e30, float("-inf")])
+@pytest.mark.parametrize("R,Q,L", [(1, 64, 200), (4, 16, 64 * 9)])
+def test_small_fp32_full_decay(R, Q, L, a0):
+    N = P = 16
+    say(f"small fp32 full decay R={R} Q={Q} L={L} A={a0}")
+    inp = make_scan_inputs(1, L, 2, P, N, R, io="f32", seed=5200 + L, device=DEV, chunk=Q)
+    t0 = L // 2 - 3
+    A = inp.A.expand(1, L, 2).clone()
+    A[0, t0] = a0
+    y, fs, _ = m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, A, inp.lam, inp.theta, inp.D, chunk=Q)
+    tail = [t[:, t0:].contiguous() for t in (inp.x, inp.Bm, inp.Cm, inp.dt, inp.lam, inp.theta)]
+    x, Bm, Cm, dt, lam, theta = tail
+    torch.cuda.synchronize()
+    sl = [(0, 0), (0, 1)]
+    ref = oracle.slices_of_scan(x, Bm, Cm, dt, inp.A, lam, theta, inp.D, sl)
+    ry, rs, _, _ = oracle.scan(**ref)
+    for k, (b, h) in enumerate(sl):
+        assert oracle.rel_err(y[b, t0:, h].double().cpu().numpy(), ry[k]) <= 1e-5
+        assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 1e-5
