@@ -4,17 +4,20 @@
 // tokens) whatever the caller's chunk.  A workgroup walks a segment of a
 // slice's chunks, kC chunks at a time side by side, four waves each: their
 // prologues, rotated rows and maps M, then the short chain of states through
-// the kC chunks, then their outputs.  Few and long slices are split into
-// segments: k_f32s<false> forms the segments' maps first, and each workgroup
-// folds those before its own.
+// the kC chunks, then their outputs.  Slices that leave the device idle are
+// split into segments: k_f32s<false> forms the segments' maps first, and each
+// workgroup folds those before its own.
 // Bound: the latency of a pass (a memory round trip, the fp64 scans, sines,
 // cosines and exponentials, six barriers).  Against three kernels with a
-// workgroup per chunk and a sine and cosine per element and use: B=1 L=256 H=2
-// rank 1 17.3 us (20.3), B=1 L=4096 H=8 31 (42), B=64 L=1000 H=16 234 (290),
-// B=1 L=16384 H=2 rank 4 chunk 32 77 (223), B=8 L=47 H=32 11.6 (20.3).
+// workgroup per chunk and a sine and cosine per element and use (in brackets):
+// B=1 L=256 H=2 rank 1 14.8 us (19.7), B=2 L=300 H=4 14.5 (20.5), B=1 L=4096 H=64
+// 97 (96), B=64 L=1000 H=16 235 (270), B=4 L=2048 H=16 rank 4 125 (165), B=8
+// L=1000 H=8 rank 4 68 (91); four chunks side by side wherever the slices do
+// not fill the device, in as few segments, took 17.0, 30.7, 110, 230, 144, 76.
 // Precision as there: fp64 prefix sums, angles, decays and rotations, each
 // operand rounded once to fp32, fp32 MFMA.
 #include <algorithm>
+#include <type_traits>
 
 #include "m3_device.h"
 #include "m3_internal.h"
@@ -104,9 +107,13 @@ __global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) 
         r.X = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.x) + at * kP + 4 * g);
     };
 
-    // entering state: thread (pair, column) of the first 128
+    // Entering state: thread (pair, column) of the first 128.  The workspace
+    // holds the maps of every segment but a slice's last and, after them, their
+    // decays and rotations, both in fp64: a state that enters a segment is
+    // rounded once, as the one that enters a chunk.
     const int si = (tid / kP) % kNH, sp = tid % kP;
-    float sre = 0.f, sim = 0.f;
+    typename std::conditional<kOut, float, double>::type sre = 0, sim = 0;
+    double *maps = reinterpret_cast<double *>(a.M), *tots = maps + a.batch * a.H * (a.nseg - 1) * kMap;
     if (kOut && tid < kNH * kP) {
         float re = 0.f, im = 0.f;
         if (a.init_state) {
@@ -126,8 +133,8 @@ __global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) 
             im += wb * uim;
         }
         for (int64_t s = 0; s < seg; ++s) {   // S <- e^{..} R S + map, rounded to fp32 as every chunk's state
-            const double *t = static_cast<const double *>(a.tot) + (bh * a.nseg + s) * (2 * kNH);
-            const float *m = a.M + (bh * a.nseg + s) * kMap;
+            const double *t = tots + (bh * (a.nseg - 1) + s) * (2 * kNH);
+            const double *m = maps + (bh * (a.nseg - 1) + s) * kMap;
             const double c = t[si], sn = t[kNH + si];
             const float nr = (float)(c * re - sn * im + m[si * kP + sp]);
             im = (float)(sn * re + c * im + m[(si + kNH) * kP + sp]);
@@ -232,14 +239,14 @@ __global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) 
                 if (cb + k >= c1) break;
                 ChunkLds &Z = L[k];
                 if constexpr (kOut) {
-                    Z.S[sp * LD + si] = sre;
-                    Z.S[sp * LD + si + kNH] = sim;
+                    Z.S[sp * LD + si] = (float)sre;
+                    Z.S[sp * LD + si + kNH] = (float)sim;
                 }
                 const double cn = Z.ce[si], sn = Z.se[si], e = Z.e;
                 const double ure = e * (double)sre + (double)Z.M[si * kP + sp];
                 const double uim = e * (double)sim + (double)Z.M[(si + kNH) * kP + sp];
-                sre = (float)(cn * ure - sn * uim);
-                sim = (float)(sn * ure + cn * uim);
+                sre = static_cast<decltype(sre)>(cn * ure - sn * uim);
+                sim = static_cast<decltype(sre)>(sn * ure + cn * uim);
                 if constexpr (!kOut) {
                     const double nc = e * (cn * tc - sn * ts);
                     ts = e * (sn * tc + cn * ts);
@@ -294,10 +301,10 @@ __global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) 
     }
     if constexpr (!kOut) {
         if (tid < kNH * kP) {
-            float *m = a.M + (bh * a.nseg + seg) * kMap;
+            double *m = maps + (bh * (a.nseg - 1) + seg) * kMap;
             m[si * kP + sp] = sre;
             m[(si + kNH) * kP + sp] = sim;
-            double *t = static_cast<double *>(a.tot) + (bh * a.nseg + seg) * (2 * kNH);
+            double *t = tots + (bh * (a.nseg - 1) + seg) * (2 * kNH);
             if (sp == 0) {
                 t[si] = tc;
                 t[kNH + si] = ts;
@@ -322,6 +329,20 @@ __global__ __launch_bounds__(256 * kC, kC == 1 ? 3 : 4) void k_f32s(ScanArgs a) 
     }
 }
 
+// Microseconds of a pass of one chunk (256 threads, three workgroups a CU by
+// their registers) and of four side by side (1024 threads, one a CU), by rank 1,
+// 2, 4: alone on a CU, and of each of several on it; the same of a map pass.
+// Fitted to forced kernels and counts over 1 to 1024 slices of 2 to 1024 chunks;
+// the choice is within 7% of the best of them.
+struct F32Cost { double pass, share, map, map_share; };
+constexpr F32Cost kCosts[3][2] = {
+    {{7.4, 3.2, 1.9, 2.0}, {14.3, 15.9, 5.9, 7.3}},
+    {{6.0, 2.5, 1.6, 1.4}, {11.7, 12.8, 5.6, 6.5}},
+    {{3.8, 2.5, 3.1, 0.9}, {10.5, 10.9, 5.9, 6.1}},
+};
+constexpr double kLaunch = 1.8, kFoldStep = 0.23;   // a launch; a map folded by the workgroups after it
+constexpr int64_t kMostSegs = 4096;
+
 template <int R>
 hipError_t launch_f32s(const ScanArgs &args, hipStream_t stream) {
     constexpr int Q = kRows / R;
@@ -330,36 +351,42 @@ hipError_t launch_f32s(const ScanArgs &args, hipStream_t stream) {
     const int64_t BH = a.batch * a.H, n64 = (a.L + Q - 1) / Q;
     const int ncu = cu_count(cus);
     if (ncu <= 0) return hipErrorInvalidDevice;
-    // One chunk at a time in a small workgroup where the slices fill the
-    // device (six workgroups a CU) or have one chunk each, else four side by
-    // side.
-    const bool wide = n64 > 1 && BH < 4 * ncu;
+    // The least estimate over both kernels and the segment counts whose maps
+    // and totals the workspace holds (a caller's chunk has an N x P map and state
+    // in fp32 and N/2 + 1 doubles in it, one after the other).
+    constexpr int64_t kChunkBytes = 2 * kMap * 4 + (kNH + 1) * 8, kSegBytes = (kMap + 2 * kNH) * 8;
+    const int64_t held = a.nchunks * kChunkBytes / kSegBytes + 1;
+    bool wide = false;
     a.G = std::max<int64_t>(n64, 1);
     a.nseg = 1;
-    if (wide) {
-        // a pass of four chunks takes kPass, in a map pass kMapPass; a launch
-        // and a workgroup's start kStart (microseconds)
-        constexpr double kPass = 7.0, kMapPass = 5.0, kStart = 5.0, kFoldStep = 0.2;
-        double best = 0.0;
-        const int64_t passes = (n64 + 3) / 4;
-        // (the totals of a segment take 16 doubles of the 9 a caller's chunk has)
-        for_segment_counts(std::min(passes, std::max<int64_t>(a.nchunks / 2, 1)), BH, ncu, [&](int64_t m) {
+    double best = -1.0;
+    for (int k = 0; k < 2; ++k) {
+        const int64_t kC = k ? 4 : 1, passes = (n64 + kC - 1) / kC, most = std::min({passes, held, kMostSegs});
+        const F32Cost &c = kCosts[R == 1 ? 0 : R == 2 ? 1 : 2][k];
+        auto load = [&](double alone, double share, int64_t wgs) {
+            return std::max(alone, (double)((wgs + ncu - 1) / ncu) * share);
+        };
+        auto offer = [&](int64_t m) {
             const int64_t G = (passes + m - 1) / m, ns = (passes + G - 1) / G;
-            double t = (double)((BH * ns + ncu - 1) / ncu) * G * kPass + kStart;
-            if (ns > 1) t += (double)((BH * (ns - 1) + ncu - 1) / ncu) * G * kMapPass + kStart + kFoldStep * ns;
-            if (m == 1 || t < best) {
+            double t = kLaunch + G * load(c.pass, c.share, BH * ns);
+            if (ns > 1) t += kLaunch + G * load(c.map, c.map_share, BH * (ns - 1)) + kFoldStep * ns;
+            if (best < 0.0 || t < best) {
                 best = t;
-                a.G = 4 * G;
+                wide = k == 1;
+                a.G = kC * G;
                 a.nseg = ns;
             }
-        });
+        };
+        for_segment_counts(most, BH, ncu, offer);
+        if (most > 1) offer(most);
     }
     const unsigned nsl = (unsigned)BH, ns = (unsigned)a.nseg;
-    if (!wide) {
-        hipLaunchKernelGGL((k_f32s<R, 1, true>), dim3(nsl, 1), dim3(256), 0, stream, a);
-    } else {
+    if (wide) {
         if (ns > 1) hipLaunchKernelGGL((k_f32s<R, 4, false>), dim3(nsl, ns - 1), dim3(1024), 0, stream, a);
         hipLaunchKernelGGL((k_f32s<R, 4, true>), dim3(nsl, ns), dim3(1024), 0, stream, a);
+    } else {
+        if (ns > 1) hipLaunchKernelGGL((k_f32s<R, 1, false>), dim3(nsl, ns - 1), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((k_f32s<R, 1, true>), dim3(nsl, ns), dim3(256), 0, stream, a);
     }
     return hipGetLastError();
 }
