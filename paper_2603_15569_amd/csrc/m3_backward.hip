@@ -52,6 +52,8 @@
 // Operands are bf16 with fp32 accumulation (as the forward); the carried
 // state and gradient, the prefix sums, weights and every scalar gradient are
 // fp32.  Results are deterministic: no atomics.
+#include <stddef.h>
+
 #include <algorithm>
 
 #include "m3_device.h"
@@ -98,11 +100,12 @@ typedef f32x4 State[2][2];
 
 // A chunk's scalars by row (token, rank): base-2 log-decay prefix, gamma,
 // sigma, v, e^{cum}; its total log-decay and the pairs' total angles.
-struct Tok {
+struct alignas(16) Tok {   // (read in 16-byte pieces, in every slot of an array)
     float c2[kRows], gam[kRows], sig[kRows], v[kRows], ec[kRows];
     float psie[kNH], ce[kNH], se[kNH];   // psi_e, its cosine and sine
     float c2e;
 };
+static_assert(offsetof(Tok, c2) % 16 == 0 && offsetof(Tok, sig) % 16 == 0, "16-byte pieces");
 
 // Sums over the 16 lanes of a row group of the values of TT tokens (v[0 ..
 // TT - 1] in every lane): the lane l16 < TT gets token l16's.  Four at once by
@@ -613,8 +616,9 @@ template <int R> struct MainLds {
     float rc[4][kRows], rg[kRows];     // sums of the mask terms by token row group
     float cc[kRows], csg[kRows];       // by column: cum, sigma
     float dv[2][kRows], dcy[2][kRows]; // dJ/dv_j and the y state term of cum_t, by half
-    float dps[2][kNH], dcm[kNW];       // state terms of psi_e (by column half) and cum_e
-    float dth[4][kNH];                 // dpsi totals of the row tiles
+    alignas(16) float dps[2][kNH];     // state terms of psi_e (by column half)
+    alignas(16) float dth[4][kNH];     // dpsi totals of the row tiles
+    float dcm[kNW];                    // state term of cum_e
     float red[kNW];
 };
 
@@ -625,6 +629,9 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
     __shared__ __attribute__((aligned(16))) char mem[std::max(sizeof(SweepLds<R>), sizeof(MainLds<R>))];
     SweepLds<R> &SW = *reinterpret_cast<SweepLds<R> *>(mem);
     MainLds<R> &M = *reinterpret_cast<MainLds<R> *>(mem);
+    static_assert(offsetof(SweepLds<R>, cs) % 16 == 0 && offsetof(MainLds<R>, cs) % 16 == 0 &&
+                      offsetof(MainLds<R>, S) % 16 == 0 && sizeof(MainLds<R>) <= 160 * 1024,
+                  "16-byte pieces; a compute unit's LDS");
     Lane w;
     const int64_t bh = blockIdx.x, seg = blockIdx.y;
     const Slice s = slice_of(a, bh);

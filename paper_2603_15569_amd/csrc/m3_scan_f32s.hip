@@ -16,6 +16,8 @@
 // not fill the device, in as few segments, took 17.0, 30.7, 110, 230, 144, 76.
 // Precision as there: fp64 prefix sums, angles, decays and rotations, each
 // operand rounded once to fp32, fp32 MFMA.
+#include <stddef.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -51,7 +53,7 @@ __device__ __forceinline__ double exp_neg(double x) {
     return ldexp(fma(p, f, 1.0), (int)n);
 }
 
-struct ChunkLds {   // one chunk's share
+struct alignas(16) ChunkLds {   // one chunk's share
     float B[kRows * LD], VB[kRows * LD], C[kRows * LD], X[kRows * LD];   // B^, v B^, C^, x
     double psi[kRows][kNH];        // by row (a token's rank rows agree)
     double cum[kRows];
@@ -60,6 +62,9 @@ struct ChunkLds {   // one chunk's share
     float M[kMap];                 // [n][p]
     float S[kP * LD];              // S_in^T [p][n]
 };
+// (read and written in 16-byte pieces, in every slot of an array)
+static_assert(sizeof(ChunkLds) % 16 == 0 && offsetof(ChunkLds, VB) % 16 == 0 && offsetof(ChunkLds, C) % 16 == 0 &&
+              offsetof(ChunkLds, X) % 16 == 0, "16-byte rows");
 
 struct Raw {   // a lane's loads for one chunk
     float2 th;                     // pairs 2 wq, 2 wq + 1 of its row's token

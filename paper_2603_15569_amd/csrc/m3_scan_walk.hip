@@ -26,6 +26,8 @@
 // L=2000 H=16 N=64 SISO, gated, from a state: 54 us; the three kernels with an
 // N x P map stored per chunk, element-wise loads and a sine and cosine per
 // element: 190 us.
+#include <stddef.h>
+
 #include <algorithm>
 
 #include "m3_device.h"
@@ -62,11 +64,16 @@ template <int N_, int R_> struct Walk {
 
 // A chunk's scalars by row (token, rank): base-2 log-decay prefix, gamma,
 // sigma, v, e^{cum}; its total decay and the pairs' total angles.
-template <class W> struct WTok {
+template <class W> struct alignas(16) WTok {
     float c2[kRows], gam[kRows], sig[kRows], v[kRows], ec[kRows];
     float psie[W::NH], ce[W::NH], se[W::NH];
     float c2e;
 };
+// (the tables are read in 16-byte pieces, in every slot of an array)
+template <class T> constexpr bool tok_aligned() {
+    return sizeof(T) % 16 == 0 && offsetof(T, c2) % 16 == 0 && offsetof(T, sig) % 16 == 0 &&
+           offsetof(T, ce) % 16 == 0 && offsetof(T, se) % 16 == 0;
+}
 
 template <class W> struct alignas(16) WLds {
     bf16 B[kRows * W::LDN];     // B^ rows, and v B^ (scaled before its one rounding)
@@ -337,6 +344,8 @@ __device__ __forceinline__ void fold(const ScanArgs &a, int64_t slot, int n, int
 template <int N, int R, bool kOut, bool kGate>
 __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
     typedef Walk<N, R> W;
+    static_assert(tok_aligned<WTok<W>>() && offsetof(WLds<W>, tok) % 16 == 0 && offsetof(WLds<W>, cs) % 16 == 0,
+                  "16-byte pieces");
     __shared__ WLds<W> L;
     int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
