@@ -71,6 +71,7 @@ constexpr int LDN = kN + 16;  // bf16 row strides (32-byte padding: FShape::PAD)
 constexpr int LDP = kP + 16;
 constexpr int LDC = kNH + 4;  // cos / sin rows (as many dwords apart)
 constexpr int kMap = kN * kP;
+constexpr int kTot = 1 + 2 * kNH;   // a segment's totals: log-decay (base 2), cosines and sines of its angles
 constexpr float kLog2e = 1.44269504088896340736f;
 typedef Mma<bf16> MM;
 // four floats at 4-byte alignment (the angles' arrays need no more)
@@ -405,7 +406,8 @@ __device__ __forceinline__ SBf load_sbf(const bf16 *m, const Lane &w) {
 //   G <- e^{cum_e} R(-psi_e) G + sum_t e^{cum_t} C^_t dy_t^T.
 // With Sst, the state entering each chunk is stored (and one more after the
 // last: n + 1 stores when n covers all but the segment's last chunk).
-// Returns the sums of cum_e (base 2) and of the lane's psi_e.  Two barriers a
+// Returns the sums of cum_e (base 2) and of the lane's psi_e (in fp64: thousands
+// of radians in a long segment).  Two barriers a
 // chunk; the next chunk's rows and the prologue values of the one after are in
 // flight while a chunk is worked on.
 // ---------------------------------------------------------------------------
@@ -418,7 +420,7 @@ template <int R> struct SweepLds {
 
 template <int R, bool kFwd>
 __device__ __forceinline__ void sweep(const BwdArgs &a, const Slice &s, const Lane &w, SweepLds<R> &L, int64_t c0,
-                                      int64_t n, State &st, bf16 *Sst, float *sum_c2, float *sum_psi) {
+                                      int64_t n, State &st, bf16 *Sst, double *sum_c2, double *sum_psi) {
     constexpr int Q = Shp<R>::Q, TPS = Shp<R>::TPS;
     constexpr int kDir = kFwd ? 1 : -1;
     const void *rsrc = kFwd ? a.B : a.C, *csrc = kFwd ? a.x : a.dy;
@@ -456,8 +458,8 @@ __device__ __forceinline__ void sweep(const BwdArgs &a, const Slice &s, const La
         put_rot(L.rows, ra, pr, c, sn);
         put_scaled(L.cols, ra, px, kFwd ? o.v[ra.row] : o.ec[ra.row]);
     };
-    *sum_c2 = 0.f;
-    *sum_psi = 0.f;
+    *sum_c2 = 0.0;
+    *sum_psi = 0.0;
     int p0 = 0, p1 = 1, p2 = 2;   // scalar tables of this chunk, the next, the one after
     if (n > 0) {
         const int64_t c1 = next(c0), c2 = next(c1);
@@ -529,14 +531,19 @@ __global__ __launch_bounds__(kThr, 4) void k_bwd_aggr(BwdArgs a) {
     const int64_t c0 = seg * a.G, n = min(a.G, a.nchunks - c0);
     State st;
     zero(st);
-    float sc, sp;
+    double sc, sp;
     if (fwd) sweep<R, true>(a, s, w, L, c0, n, st, nullptr, &sc, &sp);
     else sweep<R, false>(a, s, w, L, c0 + n - 1, n, st, nullptr, &sc, &sp);
     const int64_t slot = bh * a.nseg + seg;
     store_map(st, (fwd ? a.Af : a.Ar) + slot * kMap, w);
-    float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
-    if (w.ph == 0 && w.g == 0) tot[1 + w.i] = sp;
-    if (w.tid == 0) tot[0] = sc;
+    float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * kTot;
+    if (w.ph == 0 && w.g == 0) {
+        float sn, cn;
+        sincos_sum(sp, &sn, &cn);
+        tot[1 + w.i] = cn;
+        tot[1 + kNH + w.i] = sn;
+    }
+    if (w.tid == 0) tot[0] = (float)sc;
 }
 
 // ---------------------------------------------------------------------------
@@ -562,14 +569,15 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
     constexpr int DEPTH = 4;   // segments whose loads are issued together
     for (int k0 = 0; k0 < n; k0 += DEPTH) {
         f32x4 mr[DEPTH], mi[DEPTH];
-        float c2[DEPTH], ps[DEPTH];
+        float c2[DEPTH], cs[DEPTH], ss[DEPTH];
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
             const int k = min(k0 + d, n - 1);
             const int64_t slot = bh * a.nseg + (fwd ? k : a.nseg - 1 - k);
-            const float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * (1 + kNH);
+            const float *tot = a.tot + (slot * 2 + (fwd ? 0 : 1)) * kTot;
             c2[d] = tot[0];
-            ps[d] = tot[1 + w.i];
+            cs[d] = tot[1 + w.i];
+            ss[d] = tot[1 + kNH + w.i];
             const float *m = M + slot * kMap + 4 * w.tid;
             mr[d] = *reinterpret_cast<const f32x4 *>(&m[u * 4 * kThr]);
             mi[d] = *reinterpret_cast<const f32x4 *>(&m[(2 + u) * 4 * kThr]);
@@ -578,10 +586,7 @@ __global__ __launch_bounds__(kThr) void k_bwd_pass(BwdArgs a) {
         for (int d = 0; d < DEPTH; ++d) {
             if (k0 + d >= n) break;
             const int64_t slot = bh * a.nseg + (fwd ? k0 + d : a.nseg - 1 - (k0 + d));
-            const float e = exp2_fast(c2[d]);
-            float sn, cn;
-            sincos_rev(ps[d], &sn, &cn);
-            if (!fwd) sn = -sn;
+            const float e = exp2_fast(c2[d]), cn = cs[d], sn = fwd ? ss[d] : -ss[d];
             f32x4 nr, ni;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -648,7 +653,7 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
         if (seg > 0) load_map(st, a.Af + (slot - 1) * kMap, w);
         else if (a.init_state) load_np(st, a.init_state + bh * kMap, w);
         else zero(st);
-        float x0, x1;
+        double x0, x1;
         sweep<R, true>(a, s, w, SW, cb, n - 1, st, Sst, &x0, &x1);
         if (last && a.dfinal) {   // (else the end state meets a zero gradient, or is the next segment's)
             sweep<R, true>(a, s, w, SW, cb + n - 1, 1, st, nullptr, &x0, &x1);
@@ -1203,7 +1208,7 @@ BwdWorkspaceLayout bwd_workspace_layout(int64_t BH, int64_t nchunks, int64_t N, 
     w.off_Ar = up(w.off_Af + segs * np * sizeof(float));
     w.off_Sst = up(w.off_Ar + segs * np * sizeof(float));
     w.off_tot = up(w.off_Sst + (size_t)BH * (size_t)nchunks * np * 2);
-    w.off_dump = up(w.off_tot + segs * 2 * (size_t)(1 + N / 2) * sizeof(float));
+    w.off_dump = up(w.off_tot + segs * 2 * kTot * sizeof(float));
     w.off_dsig = up(w.off_dump + kDumpBytes);
     w.off_dA = up(w.off_dsig + segs * sizeof(float));
     w.off_dD = up(w.off_dA + segs * sizeof(float));

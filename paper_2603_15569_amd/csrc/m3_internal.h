@@ -95,7 +95,7 @@ struct BwdArgs {
     float *Af;      // per segment, [N][P] in thread order: its forward state map, then the state after it
     float *Ar;      // per segment: its reverse gradient map, then the gradient of the state entering it
     void *Sst;      // per chunk: the state entering it, bf16 in thread order (an MFMA operand; the decay term)
-    float *tot;     // per segment and direction: [1 + N/2] sums of cum_e (base 2) and psi_e
+    float *tot;     // per segment and direction: [1 + N] sum of cum_e (base 2), cos and sin of that of psi_e
     void *dump;     // store target of lanes past the end (never read)
     float *dsig;    // per segment: dJ/dsigma of its last token
     float *dApart;  // per segment: sum of dt dJ/d(dt A)

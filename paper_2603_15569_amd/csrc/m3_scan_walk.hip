@@ -58,7 +58,8 @@ template <int N_, int R_> struct Walk {
     static constexpr int LDN = N + 16, LDP = kP + 16, LDC = NH + 4;   // padded LDS rows
     static constexpr int BT = kRows * NH / 8;    // tasks of the B rows (a piece pair each)
     static constexpr int XT = kRows * kP / 8 / NTHR;   // x pieces a thread
-    static constexpr int kMap = N * kP;
+    static constexpr int kMap = N * kP, kTot = 2 * NH + 4;   // floats of a segment's map and totals
+    static_assert(kTot * 4 <= kMap * 2, "the totals of a segment fit a chunk's share of Sin");
     static_assert(Q % TG == 0 && U >= 1 && BT <= NTHR, "work split");
 };
 
@@ -295,21 +296,23 @@ __device__ __forceinline__ void rotate_c(WC<W> &r, const h2 *cs, int t, int g) {
 
 // The state after `n` segments of a slice whose maps start at `slot`, from the
 // state `st` before them: S <- e^{sum cum} R(sum psi) S + map; `after` is
-// called with each segment's slot once its step is done.
+// called with each segment's slot once its step is done.  A segment's totals
+// (kTot floats of the workspace's Sin): the cosines and sines of its pairs'
+// angles, and its log-decay (base 2).
 template <class W, class F>
 __device__ __forceinline__ void fold(const ScanArgs &a, int64_t slot, int n, int it, int g, int tid,
                                      f32x4 (&st)[2][W::U], F after) {
     constexpr int DEPTH = 4;   // segments whose loads are issued together
     for (int k0 = 0; k0 < n; k0 += DEPTH) {
-        f32x4 m[DEPTH][2][W::U], ps[DEPTH];
+        f32x4 m[DEPTH][2][W::U], cn[DEPTH], sn[DEPTH];
         float c2[DEPTH];
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
             const int64_t k = slot + min(k0 + d, n - 1);
-            const float *tot = static_cast<const float *>(a.tot) + k * (1 + W::NH);
-            c2[d] = tot[0];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) ps[d][v] = tot[1 + 16 * it + 4 * g + v];
+            const float *tot = static_cast<const float *>(a.Sin) + k * W::kTot;
+            cn[d] = *reinterpret_cast<const f32x4 *>(&tot[16 * it + 4 * g]);
+            sn[d] = *reinterpret_cast<const f32x4 *>(&tot[W::NH + 16 * it + 4 * g]);
+            c2[d] = tot[2 * W::NH];
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -321,15 +324,10 @@ __device__ __forceinline__ void fold(const ScanArgs &a, int64_t slot, int n, int
             if (k0 + d >= n) break;
             const float e = exp2_fast(c2[d]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float sn, cn;
-                sincos_rev(ps[d][v], &sn, &cn);
-#pragma unroll
-                for (int u = 0; u < W::U; ++u) {
-                    const float re = st[0][u][v], im = st[1][u][v];
-                    st[0][u][v] = e * (cn * re - sn * im) + m[d][0][u][v];
-                    st[1][u][v] = e * (sn * re + cn * im) + m[d][1][u][v];
-                }
+            for (int u = 0; u < W::U; ++u) {
+                const f32x4 re = st[0][u], im = st[1][u];
+                st[0][u] = e * (cn[d] * re - sn[d] * im) + m[d][0][u];
+                st[1][u] = e * (sn[d] * re + cn[d] * im) + m[d][1][u];
             }
             after(slot + k0 + d);
         }
@@ -380,7 +378,7 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
     WC<W> cf, cn;
     bf16x8 zr[2], zn[2];
     float ps[W::TPS];
-    float psum = 0.f, c2sum = 0.f;   // (maps: the segment's totals)
+    double psum = 0.0, c2sum = 0.0;   // (maps: the segment's totals, thousands of radians in a long one)
     auto put_state = [&](int lane) {
         const int g = lane >> 4, l16 = lane & 15;
 #pragma unroll
@@ -603,9 +601,14 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
 #pragma unroll
             for (int u = 0; u < W::U; ++u)
                 *reinterpret_cast<f32x4 *>(&m[((q * W::U + u) * W::NTHR + tid) * 4]) = st[q][u];
-        float *tot = static_cast<float *>(a.tot) + (bh * a.nseg + seg) * (1 + W::NH);
-        if (tid == 0) tot[0] = c2sum;
-        if (tid < W::NH) tot[1 + tid] = psum;
+        float *tot = static_cast<float *>(a.Sin) + (bh * a.nseg + seg) * W::kTot;
+        if (tid < W::NH) {
+            float sn, cn;
+            sincos_sum(psum, &sn, &cn);
+            tot[tid] = cn;
+            tot[W::NH + tid] = sn;
+        }
+        if (tid == 0) tot[2 * W::NH] = (float)c2sum;
     } else if (seg == a.nseg - 1) {
         const int lane = tid & (kWave - 1), g = lane >> 4, l16 = lane & 15;
         float *fs = a.final_state + bh * W::kMap;

@@ -205,3 +205,29 @@ def test_backward_arrays_at_four_byte_alignment():
     assert status == m3.M3_OK
     for k in want:
         assert torch.equal(got[k], want[k]), k
+
+
+# As test_small_state_long_segments_of_large_angles, for the gradient of the
+# initial state: with x = dy = 0 it is that of the final state, turned back
+# through segments of 50 chunks of about 768 rad.  Bound: as there.
+def test_backward_long_segments_of_large_angles():
+    N, P, R, Q, B_, H, L = 128, 64, 1, 64, 8, 16, 6400
+    say(f"backward long segments of large angles B={B_} H={H} L={L}")
+    g = torch.Generator(DEV).manual_seed(6200)
+    bf = dict(device=DEV, dtype=torch.bfloat16)
+    x = torch.zeros((B_, L, H, R, P), **bf)
+    Bm = torch.ones((B_, L, H, R, N), **bf)
+    dt = torch.full((B_, L, H), 0.05, device=DEV)
+    lam = torch.full((B_, L, H), 0.5, device=DEV)
+    theta = 12.0 + torch.randint(0, 4096, (B_, L, H, N // 2), device=DEV, generator=g) / 8192.0
+    A, D = torch.full((H,), -1e-6, device=DEV), torch.zeros(H, device=DEV)
+    dfin = torch.randn((B_, H, N, P), device=DEV, generator=g)
+    out = m3.scan_bwd(x, Bm, Bm, dt, A, lam, theta, D, x, Q, dfinal=dfin, want_dinit=True)
+    torch.cuda.synchronize()
+    psi = theta.double().sum(1)
+    c, sn = torch.cos(psi)[..., None], -torch.sin(psi)[..., None]
+    re, im = dfin.double().chunk(2, dim=2)
+    want = torch.exp(-1e-6 * dt.double().sum(1))[..., None, None] * torch.cat([c * re - sn * im, sn * re + c * im], 2)
+    e = float((out["dinit"].double() - want).norm() / want.norm())
+    say(f"backward long segments of large angles: dinit {e:.3g}")
+    assert e <= 5e-5

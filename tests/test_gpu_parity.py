@@ -1174,3 +1174,33 @@ def test_small_fp32_full_decay(R, Q, L, a0):
     for k, (b, h) in enumerate(sl):
         assert oracle.rel_err(y[b, t0:, h].double().cpu().numpy(), ry[k]) <= 1e-5
         assert oracle.rel_err(fs[b, h].double().cpu().numpy(), rs[k]) <= 1e-5
+
+
+# Segments of tens of chunks whose angles add to tens of thousands of radians:
+# the state is turned by the sum of every chunk's angle, not by a rounded one.
+# With x = 0 and (almost) no decay the final state is the initial one, turned.
+# The angles are multiples of 2^-13 near 12, so that a chunk's own sums are
+# exact in fp32.  Bound: each of the 100 chunks turns the state by a sine and
+# cosine within 2.6e-7 and rounds it four times (2.4e-7): 5e-5.
+def test_small_state_long_segments_of_large_angles():
+    N, P, R, Q, B_, H, L = 64, 64, 1, 64, 8, 16, 6400
+    say(f"long segments of large angles N={N} B={B_} H={H} L={L}")
+    g = torch.Generator(DEV).manual_seed(6100)
+    bf = dict(device=DEV, dtype=torch.bfloat16)
+    x = torch.zeros((B_, L, H, R, P), **bf)
+    Bm = torch.ones((B_, L, H, R, N), **bf)
+    dt = torch.full((B_, L, H), 0.05, device=DEV)
+    lam = torch.full((B_, L, H), 0.5, device=DEV)
+    theta = 12.0 + torch.randint(0, 4096, (B_, L, H, N // 2), device=DEV, generator=g) / 8192.0
+    A, D = torch.full((H,), -1e-6, device=DEV), torch.zeros(H, device=DEV)
+    h0 = torch.randn((B_, H, N, P), device=DEV, generator=g)
+    z = torch.zeros((B_, H, R, N), **bf), torch.zeros((B_, H, R, P), **bf)
+    _, fs, _ = m3.scan_fwd(x, Bm, Bm, dt, A, lam, theta, D, chunk=Q, init_state=h0, init_carry=z)
+    torch.cuda.synchronize()
+    psi = theta.double().sum(1)   # [B, H, N/2]
+    c, sn = torch.cos(psi)[..., None], torch.sin(psi)[..., None]
+    re, im = h0.double().chunk(2, dim=2)
+    want = torch.exp(-1e-6 * dt.double().sum(1))[..., None, None] * torch.cat([c * re - sn * im, sn * re + c * im], 2)
+    e = float((fs.double() - want).norm() / want.norm())
+    say(f"long segments of large angles: state {e:.3g}")
+    assert e <= 5e-5
