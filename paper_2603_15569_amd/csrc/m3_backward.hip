@@ -674,7 +674,8 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 
     // ---- reverse
     const float Dh = a.D[s.h];
-    float xdy = 0.f, dAsum = 0.f;
+    double xdy = 0.0;   // (a chunk's terms in fp32, the segment's chunks in fp64: dD has no other rounding)
+    float dAsum = 0.f;
     float pend_dt = 0.f, pend_lam = 0.f, first_dt = 0.f, first_lam = 0.f;   // (wave 0: chunk c + 1's first token)
     RawTok<R> raw;
     float ps[Shp<R>::TPS];
@@ -919,16 +920,17 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
             }
             const bf16x8 xv = get_tile_order(&M.X[row * LDP], 4 * hf + w.g);
             const bf16x8 yv = get_tile_order(&M.Y[row * LDP], 4 * hf + w.g);
-            float dvp = 0.f;
+            float dvp = 0.f, xy = 0.f;
             bf16x8 out;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float xe = (float)xv[e], ye = (float)yv[e], be = bu[e / 4][e % 4];
                 dvp += xe * be;
-                xdy += xe * ye;
+                xy += xe * ye;
                 out[e] = (bf16)(d[e / 4][e % 4] + vj * be + Dh * ye);
             }
             *reinterpret_cast<bf16x8 *>(gx) = out;
+            xdy += (double)xy;
             dvp = sum_g(dvp);
             if (w.g == 0) M.dv[hf][row] = dvp;
         }
@@ -1088,8 +1090,8 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
     }
     if (seg == 0 && a.dinit) store_np(G, a.dinit + bh * kMap, w);
     // per-segment partials of dD and dA
-    xdy = sum_wave(xdy);
-    if (w.lane == 0) M.red[w.wave] = xdy;
+    const float xs = sum_wave((float)xdy);
+    if (w.lane == 0) M.red[w.wave] = xs;
     dAsum = sum_wave(dAsum);
     __syncthreads();
     if (w.tid == 0) {
