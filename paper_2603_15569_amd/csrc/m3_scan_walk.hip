@@ -23,9 +23,11 @@
 //
 // Bound: issue and LDS of a CU (a chunk 3.5 us of a CU's time against 1.1 us
 // for its bytes), and the second read of B, x and the angles.  Measured on B=4
-// L=2000 H=16 N=64 SISO, gated, from a state: 54 us; the three kernels with an
+// L=2000 H=16 N=64 SISO, gated, from a state: 51 us; the three kernels with an
 // N x P map stored per chunk, element-wise loads and a sine and cosine per
-// element: 190 us.
+// element: 163 us (both timed in a loop).  The cosines and sines are held in
+// fp32, as those kernels formed them (in fp16 the state is 0.5% further from
+// fp64; y 2.87e-3 and state 1.67e-3 are theirs to four digits).
 #include <stddef.h>
 
 #include <algorithm>
@@ -55,20 +57,27 @@ template <int N_, int R_> struct Walk {
     static constexpr int NIT = N / 32;           // 16-row tiles of rotation pairs
     static constexpr int U = NIT * (kP / 16) / NW;   // (pair tile, column tile) units a wave
     static constexpr int KC = N / 32;            // K steps along the state
-    static constexpr int LDN = N + 16, LDP = kP + 16, LDC = NH + 4;   // padded LDS rows
+    static constexpr int LDN = N + 16, LDP = kP + 16;   // padded LDS rows
     static constexpr int BT = kRows * NH / 8;    // tasks of the B rows (a piece pair each)
     static constexpr int XT = kRows * kP / 8 / NTHR;   // x pieces a thread
+    // LDS besides the cos / sin table, and the workgroups of a CU with rows of
+    // `w` pairs in that (the LDS is given out in pieces of 2 KB)
+    static constexpr int kFixed = 2 * kRows * LDN * 2 + kRows * LDP * 2 + kP * LDN * 2 + NTHR * 4 +
+                                  3 * (3 * kRows + 2 * NH) * 4;
+    static constexpr int per_cu(int w) { return 160 * 1024 / ((kFixed + Q * w * 8 + 2047) / 2048 * 2048); }
+    static constexpr bool kPadCs = per_cu(NH + 2) == per_cu(NH);
+    static constexpr int LDC = kPadCs ? NH + 2 : NH;
     static constexpr int kMap = N * kP, kTot = 2 * NH + 4;   // floats of a segment's map and totals
     static_assert(kTot * 4 <= kMap * 2, "the totals of a segment fit a chunk's share of Sin");
     static_assert(Q % TG == 0 && U >= 1 && BT <= NTHR, "work split");
 };
 
 // A chunk's scalars by row (token, rank): base-2 log-decay prefix, gamma,
-// sigma, v, e^{cum}; its total decay and the pairs' total angles.
+// sigma (rows past the end: the total decay, so that c2[kRows - 1] always is it,
+// and zeros); the cosines and sines of the pairs' total angles.
 template <class W> struct alignas(16) WTok {
-    float c2[kRows], gam[kRows], sig[kRows], v[kRows], ec[kRows];
-    float psie[W::NH], ce[W::NH], se[W::NH];
-    float c2e;
+    float c2[kRows], gam[kRows], sig[kRows];
+    float ce[W::NH], se[W::NH];
 };
 // (the tables are read in 16-byte pieces, in every slot of an array)
 template <class T> constexpr bool tok_aligned() {
@@ -81,10 +90,30 @@ template <class W> struct alignas(16) WLds {
     bf16 VB[kRows * W::LDN];
     bf16 X[kRows * W::LDP];     // x rows, channels in tile order (chan_at)
     bf16 S[kP * W::LDN];        // S^T entering the chunk [p in tile order][n]
-    h2 cs[W::Q * W::LDC];
+    float2 cs[W::Q * W::LDC];   // cosine and sine of psi_t, in the order of cs_unit
     float seg[W::TG][W::NH];
     WTok<W> tok[3];
 };
+
+// Two pairs' entries (16 bytes, unit u of a row's NH / 2) of the table's row t.
+// Rows padded by 16 bytes let 16 lanes read one unit of 16 rows, or four units
+// of four rows, from different banks.  Where the padding would cost a CU a
+// workgroup (N = 64 at rank 2, N = 32 at rank 1: 15% on B=155 L=363 H=8), the units
+// of a row are exchanged by its number instead (the address takes 2% more time).
+template <class W> __device__ __forceinline__ int cs_unit(int t, int u) {
+    constexpr int UN = W::NH / 2;
+    return t * W::LDC + 2 * (W::kPadCs ? u : u ^ (t / (16 / UN) % UN));
+}
+template <class W> __device__ __forceinline__ void cs_get8(const float2 *cs, int t, int i, float (&c)[8], float (&s)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const f32x4 w = *reinterpret_cast<const f32x4 *>(&cs[cs_unit<W>(t, i / 2 + j)]);
+        c[2 * j] = w[0];
+        s[2 * j] = w[1];
+        c[2 * j + 1] = w[2];
+        s[2 * j + 1] = w[3];
+    }
+}
 
 struct WAt {   // the slice's offsets
     int64_t b, h, tok, L, H;
@@ -191,45 +220,37 @@ __device__ __forceinline__ void tok_scan(const ScanArgs &a, const WAt &s, int ti
     if (__builtin_amdgcn_readfirstlane(tid) < kWave) {
         const int t = tid / W::R;
         const bool in = t < nvalid;
-        const float c2 = lane_scan(in && tid % W::R == 0 ? r.dt * r.A : 0.f) * kLog2e;
+        const float c2 = lane_scan(in && tid % W::R == 0 ? r.dt * r.A * kLog2e : 0.f);
         const float c2e = lane_bcast(c2, nvalid * W::R - 1);
         const float gam = in ? r.lam * r.dt : 0.f;
         float sig = gam;
         if (in && ct + t + 1 < s.L) sig += (1.f - r.lamn) * r.dtn;
-        o.c2[tid] = c2;
+        o.c2[tid] = in ? c2 : c2e;
         o.gam[tid] = gam;
         o.sig[tid] = sig;
-        o.v[tid] = in ? exp2_fast(c2e - c2) * sig : 0.f;
-        o.ec[tid] = in ? exp2_fast(c2) : 0.f;
-        if (tid == 0) o.c2e = c2e;
     }
 }
 
-// The cos / sin table of psi_t, and psi_e with its own in fp32.
+// The cos / sin table of psi_t, in fp32, and that of psi_e, which turns the
+// state in every chunk, to the last bit.  Returns psi_e of its pair in the
+// threads that hold the last token.
 template <class W>
-__device__ __forceinline__ void tok_table(int tid, int nvalid, const float (&ps)[W::TPS], WLds<W> &L, WTok<W> &o) {
+__device__ __forceinline__ float tok_table(int tid, int nvalid, const float (&ps)[W::TPS], WLds<W> &L, WTok<W> &o) {
     const int i = tid % W::NH, tg = tid / W::NH;
     float off = 0.f;
 #pragma unroll
     for (int q = 0; q < W::TG - 1; ++q) off += q < tg ? L.seg[q][i] : 0.f;
-    float pe = 0.f, se = 0.f, ce = 0.f;
+    float pe = 0.f;
 #pragma unroll
     for (int k = 0; k < W::TPS; ++k) {
         const float psi = ps[k] + off;
         float sn, cn;
         sincos_rev(psi, &sn, &cn);
-        cs_put(&L.cs[(tg * W::TPS + k) * W::LDC + i], cn, sn);
-        if (k == (nvalid - 1) % W::TPS) {
-            pe = psi;
-            se = sn;
-            ce = cn;
-        }
+        L.cs[cs_unit<W>(tg * W::TPS + k, i / 2) + i % 2] = make_float2(cn, sn);
+        if (k == (nvalid - 1) % W::TPS) pe = psi;
     }
-    if (tg == (nvalid - 1) / W::TPS) {
-        o.psie[i] = pe;
-        o.ce[i] = ce;
-        o.se[i] = se;
-    }
+    if (tg == (nvalid - 1) / W::TPS) sincos_full(pe, &o.se[i], &o.ce[i]);
+    return pe;
 }
 
 template <class W, bool kOut>
@@ -243,9 +264,9 @@ __device__ __forceinline__ void stage(int tid, int nvalid, WRows<W> &r, WLds<W> 
     }
     if (W::BT == W::NTHR || tid < W::BT) {
         const int row = tid / (W::NH / 8), cp = tid % (W::NH / 8);
-        const float v = o.v[row];
+        const float v = exp2_fast(o.c2[kRows - 1] - o.c2[row]) * o.sig[row];
         float c[8], sn[8];
-        cs_getn<8>(&L.cs[row / W::R * W::LDC + cp * 8], c, sn);
+        cs_get8<W>(L.cs, row / W::R, cp * 8, c, sn);
         bf16x8 lo, hi, vlo, vhi;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -271,11 +292,10 @@ __device__ __forceinline__ void stage(int tid, int nvalid, WRows<W> &r, WLds<W> 
 }
 
 template <class W>
-__device__ __forceinline__ void rotate_c(WC<W> &r, const h2 *cs, int t, int g) {
-    cs += t * W::LDC;
+__device__ __forceinline__ void rotate_c(WC<W> &r, const float2 *cs, int t, int g) {
     if constexpr (W::N == 32) {
         float c[8], sn[8];
-        cs_getn<8>(cs + 8 * (g & 1), c, sn);
+        cs_get8<W>(cs, t, 8 * (g & 1), c, sn);
         const float sg = g < 2 ? 1.f : -1.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) r.f[0][e] = (bf16)(c[e] * (float)r.f[0][e] + sg * sn[e] * (float)r.o[e]);
@@ -283,7 +303,7 @@ __device__ __forceinline__ void rotate_c(WC<W> &r, const h2 *cs, int t, int g) {
 #pragma unroll
         for (int kk = 0; kk < W::KC / 2; ++kk) {
             float c[8], sn[8];
-            cs_getn<8>(cs + kk * 32 + 8 * g, c, sn);
+            cs_get8<W>(cs, t, kk * 32 + 8 * g, c, sn);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float u = (float)r.f[kk][e], v = (float)r.f[kk + W::KC / 2][e];
@@ -344,6 +364,7 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
     typedef Walk<N, R> W;
     static_assert(tok_aligned<WTok<W>>() && offsetof(WLds<W>, tok) % 16 == 0 && offsetof(WLds<W>, cs) % 16 == 0,
                   "16-byte pieces");
+    static_assert(sizeof(WLds<W>) == W::kFixed + W::Q * W::LDC * 8, "LDS as counted");
     __shared__ WLds<W> L;
     int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -378,7 +399,9 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
     WC<W> cf, cn;
     bf16x8 zr[2], zn[2];
     float ps[W::TPS];
-    double psum = 0.0, c2sum = 0.0;   // (maps: the segment's totals, thousands of radians in a long one)
+    // (maps: the segment's totals, thousands of radians in a long one; its chunks
+    // are whole, so the last threads hold every psi_e)
+    double psum = 0.0, c2sum = 0.0;
     auto put_state = [&](int lane) {
         const int g = lane >> 4, l16 = lane & 15;
 #pragma unroll
@@ -452,7 +475,7 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
         tok_scan<W>(a, s, tid, c0 * W::Q, valid(c0), raw, ps, L, L.tok[0]);
         fetch_tok(c1);
         __syncthreads();
-        tok_table<W>(tid, valid(c0), ps, L, L.tok[0]);
+        psum = tok_table<W>(tid, valid(c0), ps, L, L.tok[0]);
         __syncthreads();
         stage<W, kOut>(tid, valid(c0), rows, L, L.tok[0]);
         if constexpr (kOut) {
@@ -489,7 +512,7 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
                     for (int kk = 0; kk < W::KC; ++kk)
                         y[hp][ab] = MM::mma(MM::load(&L.S[(32 * hp + 16 * ab + l16) * W::LDN + 32 * kk + 8 * g]), cf.f[kk], y[hp][ab]);
                 }
-            const float ec = o.ec[row], c2t = o.c2[row], gmt = o.gam[row];
+            const float c2t = o.c2[row], gmt = o.gam[row], ec = exp2_fast(c2t);
 #pragma unroll
             for (int hp = 0; hp < 2; ++hp)
 #pragma unroll
@@ -544,7 +567,7 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
             ycur += W::Q * u.sx;
         }
         {
-            const float e = exp2_fast(o.c2e);
+            const float e = exp2_fast(o.c2[kRows - 1]);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -569,12 +592,10 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
                 st[0][v] = cn4 * re - sn4 * im;
                 st[1][v] = sn4 * re + cn4 * im;
             }
-            if constexpr (!kOut) {
-                psum += o.psie[tid % W::NH];
-                c2sum += o.c2e;
-            }
+            if constexpr (!kOut) c2sum += o.c2[kRows - 1];
         }
-        tok_table<W>(tid, nv1, ps, L, L.tok[p1]);
+        const float pe1 = tok_table<W>(tid, nv1, ps, L, L.tok[p1]);
+        if (!kOut && c < ce) psum += pe1;
         __syncthreads();
         // ======== chunk c + 1's rows, C and state; the scans of chunk c + 2 ========
         if constexpr (kOut) {
@@ -602,11 +623,11 @@ __global__ __launch_bounds__(256, 2) void k_walk(ScanArgs a) {
             for (int u = 0; u < W::U; ++u)
                 *reinterpret_cast<f32x4 *>(&m[((q * W::U + u) * W::NTHR + tid) * 4]) = st[q][u];
         float *tot = static_cast<float *>(a.Sin) + (bh * a.nseg + seg) * W::kTot;
-        if (tid < W::NH) {
+        if (tid >= W::NTHR - W::NH) {
             float sn, cn;
             sincos_sum(psum, &sn, &cn);
-            tot[tid] = cn;
-            tot[W::NH + tid] = sn;
+            tot[tid % W::NH] = cn;
+            tot[W::NH + tid % W::NH] = sn;
         }
         if (tid == 0) tot[2 * W::NH] = (float)c2sum;
     } else if (seg == a.nseg - 1) {
@@ -666,7 +687,8 @@ __global__ __launch_bounds__(256) void k_walk_pass(ScanArgs a) {
 // a workgroup that has its CU to itself, and 0.87 of that for each of several
 // on it (a CU's issue slots and LDS are then full); a map's chunk kMapChunk;
 // a workgroup kStart besides, and kFoldStep for each map it folds.
-// (4 chunks a segment: 54 us; 3: 58; 8: 63; 32, one segment: 132.)
+// (4 chunks a segment: 54 us; 3: 58; 8: 63; 32, one segment: 132, with the
+// table still in fp16.)
 int64_t walk_chunks(int64_t BH, int64_t n64, int64_t most, int64_t ncu) {
     constexpr double kChunk = 4.1, kMapChunk = 2.5, kStart = 5.0, kFoldStep = 0.3;   // us
     double best = 0.0;
