@@ -220,8 +220,9 @@ __device__ __forceinline__ void tok_scan(const BwdArgs &a, const Lane &w, int64_
     if (w.wave == 0) {
         const int t = w.lane / R;
         const bool in = t < nvalid;
-        const float cum = lane_scan(in && w.lane % R == 0 ? r.dt * r.A : 0.f);
-        const float c2 = cum * kLog2e, c2e = lane_bcast(c2, nvalid * R - 1);
+        // (scaled before the sum, so that a prefix is rounded once)
+        const float c2 = lane_scan(in && w.lane % R == 0 ? r.dt * r.A * kLog2e : 0.f);
+        const float c2e = lane_bcast(c2, nvalid * R - 1);
         const float gam = in ? r.lam * r.dt : 0.f;
         float sig = gam;
         if (in && c * Q + t + 1 < a.L) sig += (1.f - r.lamn) * r.dtn;
@@ -1109,7 +1110,7 @@ __global__ __launch_bounds__(kThr, 2) void k_bwd_main(BwdArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kThrF = 256;
 __global__ __launch_bounds__(kThrF) void k_bwd_finish(BwdArgs a, int Q) {
-    __shared__ float s_a[kThrF], s_d[kThrF];
+    __shared__ double s_a[kThrF], s_d[kThrF];
     const int tid = threadIdx.x;
     if (blockIdx.x >= a.H) {
         const int64_t q = ((int64_t)blockIdx.x - a.H) * kThrF + tid;
@@ -1122,7 +1123,7 @@ __global__ __launch_bounds__(kThrF) void k_bwd_finish(BwdArgs a, int Q) {
         return;
     }
     const int64_t h = blockIdx.x, n = a.batch * a.nseg;
-    float sa = 0.f, sd = 0.f;
+    double sa = 0.0, sd = 0.0;
     for (int64_t q = tid; q < n; q += kThrF) {
         const int64_t s = (q / a.nseg * a.H + h) * a.nseg + q % a.nseg;
         sa += a.dApart[s];
@@ -1139,8 +1140,8 @@ __global__ __launch_bounds__(kThrF) void k_bwd_finish(BwdArgs a, int Q) {
         __syncthreads();
     }
     if (tid == 0) {
-        a.dD[h] = s_d[0];
-        if (!a.dA_per_token) a.dA[h] = s_a[0];
+        a.dD[h] = (float)s_d[0];
+        if (!a.dA_per_token) a.dA[h] = (float)s_a[0];
     }
 }
 
