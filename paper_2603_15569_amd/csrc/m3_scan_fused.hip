@@ -147,12 +147,11 @@ void k_scan_fused(ScanArgs a) {
     if (tid == 0) {
         int64_t ci, si;
         uint32_t ep;
-        bool rd, first, jan;
+        bool rd, jan, first = false;
         if constexpr (kVar) {
             take_item_var(a.ctl, a.vl_grp, a.vl_gstart, a.vl_order, a.vl_maxn, &ci, &si, &ep, &rd, &first, &jan);
         } else {
             take_item(a.ctl, nsl, a.nchunks, &ci, &si, &ep, &rd);
-            first = ci == 0 && si == 0;
             jan = is_janitor(ci, si, nsl, a.nchunks);
         }
         s_i[0] = (int)ci;
@@ -165,8 +164,8 @@ void k_scan_fused(ScanArgs a) {
     __syncthreads();
     const int64_t c = s_i[0], sl = s_i[1];
     const uint32_t epoch = (uint32_t)s_i[2];
-    const bool first = (s_i[3] & 2) != 0;
-    bool flags_ready = (s_i[3] & 1) != 0;
+    const bool first = kVar ? (s_i[3] & 2) != 0 : c == 0 && sl == 0;
+    bool flags_ready = kVar ? (s_i[3] & 1) != 0 : s_i[3] != 0;
     __syncthreads();
     if (c < 0) return;   // (cannot happen: one workgroup per item)
     if (first) {   // the call's first item clears the look-back flags
