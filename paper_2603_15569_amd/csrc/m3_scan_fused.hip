@@ -1184,16 +1184,28 @@ void k_scan_fused(ScanArgs a) {
         janitor_reset(a.ctl, nsl, a.nchunks, s_ctl[0], a.spin_max, kVar ? a.vl_grp : nullptr, a.vl_maxn);
 }
 
+// LDS asked for on top of the kernel's own, so that one workgroup of a 128-row
+// bf16 chunk sits on a CU instead of two.  With one slice for each group (XCD)
+// the chain of a slice's chunks bounds the scan, and the chunks that wait for
+// it slow its loads: B=1 L=20000 H=8, rank 1 / 2 / 4 with 128 / 64 / 32 tokens 183 /
+// 354 / 714 us with two, 162 / 310 / 594 with one; with the prologue rank 1 L=30000
+// 290 and 249.  (Fewer slices share the XCDs, whose CUs then need the second:
+// H=4 rank 1 167 and 205; with 16 slices two chains fill it: 234 and 242.)
+template <class S> unsigned extra_lds(int64_t nsl) {
+    return sizeof(typename S::Acc) == 4 && S::QR == 128 && nsl == kGroups ? 48 * 1024 : 0;
+}
+
 template <typename T, int Q, int R, bool kPro = false>
 hipError_t launch_fused(const ScanArgs &a, hipStream_t stream) {
     typedef FShape<T, Q, R> S;
     const int64_t nsl = a.batch * a.H;
+    const unsigned lds = extra_lds<S>(nsl);
     if (a.z)
         hipLaunchKernelGGL((k_scan_fused<T, Q, R, true, kPro>), dim3((unsigned)(nsl * a.nchunks)),
-                           dim3(S::NTHR), 0, stream, a);
+                           dim3(S::NTHR), lds, stream, a);
     else
         hipLaunchKernelGGL((k_scan_fused<T, Q, R, false, kPro>), dim3((unsigned)(nsl * a.nchunks)),
-                           dim3(S::NTHR), 0, stream, a);
+                           dim3(S::NTHR), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -1201,12 +1213,13 @@ hipError_t launch_fused(const ScanArgs &a, hipStream_t stream) {
 template <typename T, int Q, int R>
 hipError_t launch_fused_var(const ScanArgs &a, hipStream_t stream) {
     typedef FShape<T, Q, R> S;
+    const unsigned lds = extra_lds<S>(a.batch * a.H);
     if (a.z)
         hipLaunchKernelGGL((k_scan_fused<T, Q, R, true, false, true>), dim3((unsigned)a.vl_slots),
-                           dim3(S::NTHR), 0, stream, a);
+                           dim3(S::NTHR), lds, stream, a);
     else
         hipLaunchKernelGGL((k_scan_fused<T, Q, R, false, false, true>), dim3((unsigned)a.vl_slots),
-                           dim3(S::NTHR), 0, stream, a);
+                           dim3(S::NTHR), lds, stream, a);
     return hipGetLastError();
 }
 

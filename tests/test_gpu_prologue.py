@@ -142,6 +142,18 @@ def test_prologue_scan(R, Q, L, variant):
     compare(y, fs, cB, cX, ref, zref, slices, f"pro R={R} Q={Q} L={L} {variant}")
 
 
+# Eight slices (one for each slice group): the 128-row kernels ask for more LDS.
+@pytest.mark.parametrize("R,Q", [(1, 128), (2, 64), (4, 32)])
+def test_prologue_scan_eight_slices(R, Q):
+    say(f"prologue scan of eight slices R={R} Q={Q}")
+    inp, pin = make_case(2, 500, 4, R, Q, seed=R * 100 + Q)
+    zfull = torch.randn(inp.x.shape, device=DEV, generator=torch.Generator(DEV).manual_seed(9)).to(torch.bfloat16)
+    y, fs, cB, cX = run_pro(inp, pin, "full", Q, zfull=zfull)
+    slices = [(b, h) for b in range(2) for h in range(4)]
+    ref, zref = oracle_prologue(inp, pin, "full", slices, zfull=zfull)
+    compare(y, fs, cB, cX, ref, zref, slices, f"eight slices R={R} Q={Q}")
+
+
 @pytest.mark.parametrize("R,Q", [(1, 64), (4, 128)])
 def test_prologue_continuation(R, Q):
     """scan(0:L1) then scan(L1:L) from its state and carry (the prologue's B
