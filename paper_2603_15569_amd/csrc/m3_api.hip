@@ -155,17 +155,23 @@ extern "C" size_t m3_scan_workspace_bytes(const m3_dims *d) {
 // Kernel choice of the default bf16 scan (no M3_SCAN_* flag, seg_chunks 0).
 // The result does not depend on the chunk, so a scan may run on a longer chunk
 // than the caller's (never a shorter one: the workspace is sized for the
-// caller's, and holds what a longer one needs).  The estimates below are
-// fitted to MI355X times at N = 128, P = 64 over 1 to 512 slices and 1 to 256
-// chunks a slice, within about 10%:
-//   per chunk   the larger of all items at `item` each and a slice's chain of
-//               chunks at kLink a link, and `base`, one item's lifetime
-//   one segment `single` a chunk, once per batch of resident slices
-//   segments    `two` a chunk (two passes over each), a link per segment
+// caller's, and holds what a longer one needs).  The estimates below are fitted
+// to MI355X times at N = 128, P = 64 of every kernel, chunk and segment count
+// that serves a shape, over 671 shapes (175 of them with the block prologue)
+// of 4096 to 2 million rows, 1 to 8500 slices and 1 to 2000 chunks a slice; the
+// choice costs 0.5% (0.1%) more than the best of them on average:
+//   per chunk   a slice's chain of chunks takes kLink a chunk, and the items of
+//               all slices `item` each; the two add as squares.  (Slices are
+//               handed out in eight groups, one per XCD: counted in whole rows of
+//               eight.)  And `base`, one item's lifetime.
+//   one segment `single` a chunk and kSingleBase, per batch of resident slices
+//   segments    `two` a chunk (two passes over each) and kTwoBase, per batch of
+//               resident segments, and kLink a segment of a slice
 // Longer chunks have fewer links and maps but grow the quadratic part: B=1
 // L=2048 H=16 rank 1, chunk 64: 49 us per chunk of 64, 35 of 128; B=4 L=2048
-// H=16 rank 2, chunk 32: 156, 103 and 99 us of 32, 64 and 128 tokens; B=1
-// L=16384 H=8 rank 1, chunk 64: 305 and 147 us per chunk, 109 us in segments.
+// H=16 rank 2, chunk 32: 156, 103 and 99 us of 32, 64 and 128 tokens.  Segments
+// serve long scans of few slices: B=7 L=42121 H=2 rank 1, chunk 128: 528 us per
+// chunk, 308 in segments; B=1 L=20000 H=8 rank 2, chunk 64: 179 and 152.
 // ---------------------------------------------------------------------------
 namespace m3 {
 namespace {
@@ -175,12 +181,14 @@ struct ScanCost {   // microseconds
     double item, item_pro, base, single, two;   // (single, two: 0 where no such kernel is built)
 };
 constexpr ScanCost kScanCosts[] = {
-    {1, 64, .036, .039, 11.7, 6.6, 10.0},   {1, 128, .0515, .059, 14.0, 13.4, 20.0},
-    {2, 64, .033, .036, 11.0, 6.1, 9.0},    {2, 128, .0444, .0477, 12.7, 9.2, 13.6},
-    {2, 256, .084, .101, 18.3, 20.0, 30.0}, {4, 128, .0416, .0461, 12.0, 8.4, 12.6},
-    {4, 256, .076, .095, 17.8, 13.2, 22.5}, {4, 512, .135, .196, 29.6, 0.0, 0.0},
+    {1, 64, .0296, .0316, 8.2, 5.5, 9.3},    {1, 128, .0422, .0505, 10.7, 11.0, 14.8},
+    {2, 64, .0355, .0235, 8.3, 6.1, 9.0},    {2, 128, .0366, .0427, 11.0, 7.2, 11.3},
+    {2, 256, .0713, .0882, 15.4, 16.9, 27.7}, {4, 128, .0325, .0458, 11.0, 6.5, 11.0},
+    {4, 256, .0632, .0899, 14.4, 9.7, 21.3}, {4, 512, .110, .194, 23.0, 0.0, 0.0},
 };
-constexpr double kLink = 1.0, kSingleBase = 8.0, kTwoBase = 10.0;
+constexpr double kLink = 1.064, kSingleBase = 8.2, kTwoBase = 4.7;
+// with the prologue: its link, and `base` and `single` times these
+constexpr double kProLink = 1.03, kProBase = 1.34, kProSingle = 1.75;
 
 struct ScanChoice {
     int64_t chunk, G;   // G: chunks per segment (0: one chunk per workgroup)
@@ -190,6 +198,7 @@ ScanChoice choose_scan(const m3_dims *d, bool pro, int ncu) {
     ScanChoice best{d->chunk, 0};
     double tbest = -1.0;
     const double nsl = (double)(d->batch * d->nheads);
+    const double lanes = nsl > 4 ? std::ceil(nsl / 8) * 8 : nsl;
     auto rounds = [&](double wgs) { return std::ceil(wgs / ncu); };
     auto offer = [&](double t, int64_t chunk, int64_t G) {
         if (tbest < 0.0 || t < tbest) {
@@ -204,18 +213,19 @@ ScanChoice choose_scan(const m3_dims *d, bool pro, int ncu) {
                   : find_fused_impl(d->io, d->dstate, d->headdim, d->rank, chunk)))
             continue;
         const int64_t n = (d->seqlen + chunk - 1) / chunk;
-        offer(std::max(nsl * n * (pro ? c.item_pro : c.item), n * kLink) + c.base, chunk, 0);
+        const double row = lanes * (pro ? c.item_pro : c.item);
+        const double link = pro ? kProLink : kLink;
+        offer(n * std::sqrt(link * link + row * row) + c.base * (pro ? kProBase : 1.0), chunk, 0);
         // (with the prologue only the warp-specialised one-segment kernel)
         const bool seg = pro ? find_ws_pro_impl(d->io, d->dstate, d->headdim, d->rank, chunk) != nullptr
                              : find_seg_impl(d->io, d->dstate, d->headdim, d->rank, chunk) != nullptr;
         if (!seg) continue;
-        offer(rounds(nsl) * n * c.single * (pro ? 1.2 : 1.0) + kSingleBase, chunk, n);
+        offer(rounds(nsl) * (n * c.single * (pro ? kProSingle : 1.0) + kSingleBase), chunk, n);
         if (pro) continue;
         for_segment_counts(std::min<int64_t>(n, 256), d->batch * d->nheads, ncu, [&](int64_t m) {
             const int64_t G = (n + m - 1) / m, segs = (n + G - 1) / G;
             if (G == n) return;
-            offer(rounds(nsl * segs) * G * c.two * (nsl * segs < 0.75 * ncu ? 0.8 : 1.0) + segs * kLink + kTwoBase,
-                  chunk, G);
+            offer(rounds(nsl * segs) * (G * c.two + kTwoBase) + segs * kLink, chunk, G);
         });
     }
     return best;
