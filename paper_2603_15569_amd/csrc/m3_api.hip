@@ -290,17 +290,15 @@ static m3_status scan_fwd(const m3_dims *d, const void *x, const void *B, const 
         static int cus[64];
         const int ncu = scan::cu_count(cus);
         const ScanChoice ch = ncu > 0 ? choose_scan(d, pr.on, ncu) : ScanChoice{d->chunk, 0};
-        const scan_launch_fn pc = pr.on ? find_fused_pro_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk)
-                                        : find_fused_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk);
-        const int64_t tok_bytes = d->nheads * d->rank * d->dstate * 2;   // (rows within 32-bit offsets)
-        if (pc && ch.chunk * tok_bytes < (INT64_C(1) << 31)) {
-            impl.per_chunk = pc;
-            impl.launch = ch.G > 0 ? find_seg_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk) : pc;
-            seg_chunks = ch.G;
-            nc = (d->seqlen + ch.chunk - 1) / ch.chunk;
-            wl = scan_workspace_layout(d->batch * d->nheads, nc, d->dstate, d->headdim, io_bytes_of(d->io),
-                                       impl.acc_bytes, impl.fused);
-        }
+        // (the choice's chunk has a per-chunk kernel, and its rows stay within 32-bit
+        // offsets: at most 128 tokens of less than 16 MiB)
+        impl.per_chunk = pr.on ? find_fused_pro_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk)
+                               : find_fused_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk);
+        impl.launch = ch.G > 0 ? find_seg_impl(d->io, d->dstate, d->headdim, d->rank, ch.chunk) : impl.per_chunk;
+        seg_chunks = ch.G;
+        nc = (d->seqlen + ch.chunk - 1) / ch.chunk;
+        wl = scan_workspace_layout(d->batch * d->nheads, nc, d->dstate, d->headdim, io_bytes_of(d->io),
+                                   impl.acc_bytes, impl.fused);
     }
 
     ScanArgs a;
