@@ -99,8 +99,10 @@ typedef enum { M3_F32 = 0, M3_BF16 = 1 } m3_dtype;
  * waves form the outputs while half stage the inputs and carry the state).
  * With seg_chunks 0, bf16 scans run whichever is estimated to be fastest for
  * the batch, and may run on a longer chunk than dims->chunk (the results do
- * not depend on it).  seg_chunks > 0 asks for the segmented kernel on
- * dims->chunk.
+ * not depend on it up to rounding).  seg_chunks > 0 asks for the segmented
+ * kernel on dims->chunk.  A non-finite input of token t spoils what follows it
+ * in its slice; of the tokens before it, it can spoil y only within its group
+ * of 64 rows (tokens from floor(t rank / 64) 64 / rank on), on every path.
  * bf16 states of 64 and 32: each workgroup walks a segment of a slice's chunks
  * with the state in registers, after a pass over the segments' maps when a
  * slice needs several; every flag selects it, and its own chunk is 64 rows.
@@ -169,7 +171,7 @@ size_t m3_scan_workspace_bytes(const m3_dims *dims);
  * Supported shapes (else M3_ERR_UNSUPPORTED): io bf16 with dstate 128,
  * headdim 64, rank 1/2/4 and chunk*rank a multiple of 64 with chunk in
  * {32, 64, 128}; io bf16 with headdim 64 and the smaller states of the
- * paper's state-size sweep (kernels of their own, below): dstate 64 with (rank,
+ * paper's state-size sweep (the walked segments above): dstate 64 with (rank,
  * chunk) in {(1, 64), (1, 128), (2, 32), (2, 64), (4, 16), (4, 32)}, dstate 32
  * with (1, 64), (2, 32), (4, 16); io fp32 with (dstate, headdim) = (16, 16) or
  * (128, 64), rank 1/2/4, chunk in {16, 32, 64} and chunk*rank a multiple of

@@ -48,7 +48,7 @@
 // steps.  One fp32 map of the state per chunk and direction, written by a
 // kernel over all chunks and folded by a second one, moved 352 KB a chunk and
 // took 8.62 ms on B=8 L=4096 H=32 rank 4 and 313 us on B=4 L=2048 H=16 SISO;
-// carrying the state through a segment in registers takes 2.64 ms and 173 us.
+// carrying the state through a segment in registers takes 2.65 ms and 157 us.
 // Operands are bf16 with fp32 accumulation (as the forward); the carried
 // state and gradient, the prefix sums, weights and every scalar gradient are
 // fp32.  Results are deterministic: no atomics.

@@ -35,7 +35,8 @@ struct ScanArgs {
     void *cB, *cX;
     // workspace regions (see scan_workspace_layout)
     float *M;        // [BH][nchunks][N][P] fp32  per-chunk state contributions
-    void *Sin;       // [BH][nchunks][P][N] io    state entering each chunk
+    void *Sin;       // [BH][nchunks][P][N] io    state entering each chunk (the walked segments: their totals;
+                     // the small fp32 scan: its maps and totals run on from M through it)
     void *tot;       // [BH][nchunks][1+N/2] acc  chunk log-decay and angle totals
     // single-pass (look-back) scan only
     uint32_t *ctl;   // control block (ticket counters, epoch, timeout counts)

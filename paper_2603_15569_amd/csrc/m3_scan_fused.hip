@@ -59,7 +59,9 @@ using namespace scan;
 
 template <typename T, int Q, int R, bool kGate, bool kPro, bool kVar = false>
 // Two waves per SIMD: two 4-wave workgroups or one 8-wave workgroup per CU
-// (more waves spill the tile registers of the output phase).  kGate: the
+// (more waves spill the tile registers of the output phase); four for chunks of
+// 128 rows, below, which spill up to 4 registers a lane, 8 to 14 with the
+// prologue.  kGate: the
 // stored y is multiplied by SiLU(z) (the block's output gate).  kPro: the
 // block prologue is applied as the rows arrive (B and C: RMS norm over N,
 // gain, bias; x and z: X = W_X o X', Z = W_Z o Z'), from per-head tables in

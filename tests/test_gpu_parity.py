@@ -1063,7 +1063,9 @@ def test_small_state_segments(N, R, Q, B_, H, L, gate, ph, init):
     (2, 32, 1, 16, 1001, True, False, True), (4, 32, 1, 8, 707, False, True, True),
     (1, 64, 1, 4, 64 * 150 + 9, False, False, True), (1, 64, 2, 8, 65, True, True, False),
     (4, 32, 40, 8, 40, False, False, True), (4, 64, 2, 16, 900, True, False, False),
-    (2, 32, 1, 2, 3, True, False, True), (1, 64, 9, 32, 200, False, False, True)])
+    (2, 32, 1, 2, 3, True, False, True), (1, 64, 9, 32, 200, False, False, True),
+    (2, 32, 1, 8, 64 * 20 + 5, True, False, True), (4, 32, 2, 4, 650, False, True, False),
+    (1, 128, 1, 8, 1500, True, False, True), (2, 64, 1, 3, 64 * 140 + 1, False, False, True)])
 def test_default_choice(R, Q, B_, H, L, gate, ph, init):
     N, P = 128, 64
     say(f"default choice R={R} Q={Q} B={B_} H={H} L={L} gate={gate} ph={ph} init={init}")
@@ -1204,3 +1206,27 @@ def test_small_state_long_segments_of_large_angles():
     e = float((fs.double() - want).norm() / want.norm())
     say(f"long segments of large angles: state {e:.3g}")
     assert e <= 5e-5
+
+
+# A non-finite x, B or dt of one token reaches y of the tokens before it only
+# within its group of 64 rows (64 / R tokens from a chunk's start), whatever
+# kernel, chunk and segments the default choice runs; other slices keep their
+# bits.
+@pytest.mark.parametrize("what", ["x", "Bm", "dt"])
+@pytest.mark.parametrize("N,R,Q,B_,H,L", [(128, 2, 32, 1, 16, 1001), (128, 4, 32, 1, 8, 300), (128, 1, 64, 1, 4, 64 * 150),
+                                          (128, 4, 64, 2, 16, 900), (128, 1, 64, 9, 32, 200), (64, 1, 64, 2, 4, 700),
+                                          (32, 4, 16, 2, 4, 200)])
+def test_nan_token_reach(N, R, Q, B_, H, L, what):
+    say(f"NaN token reach N={N} R={R} Q={Q} B={B_} H={H} L={L} {what}")
+    inp = make_scan_inputs(B_, L, H, 64, N, R, io="bf16", seed=5300 + L, device=DEV, chunk=Q)
+    run = lambda: m3.scan_fwd(inp.x, inp.Bm, inp.Cm, inp.dt, inp.A, inp.lam, inp.theta, inp.D, chunk=Q)
+    want, wfs, _ = run()
+    t0 = L // 2 + 5
+    getattr(inp, what)[0, t0, 1] = float("nan")
+    y, fs, _ = run()
+    torch.cuda.synchronize()
+    first = t0 * R // 64 * 64 // R
+    assert torch.isnan(y[0, t0, 1]).any() and torch.isnan(fs[0, 1]).any()
+    assert torch.equal(y[0, :first, 1], want[0, :first, 1])
+    y[0, :, 1], fs[0, 1] = want[0, :, 1], wfs[0, 1]
+    assert torch.equal(y, want) and torch.equal(fs, wfs)
